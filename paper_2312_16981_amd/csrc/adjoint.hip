@@ -9,13 +9,6 @@
 
 namespace ugk {
 
-__constant__ HeadSeries c_head_adj;
-
-hipError_t set_head_series_adj(const HeadSeries& hs)
-{
-    return hipMemcpyToSymbol(HIP_SYMBOL(c_head_adj), &hs, sizeof(HeadSeries));
-}
-
 constexpr int ADJ_THREADS = 256;
 
 // Heat-capacity weight dt / (eps^2 C_v) of the temperature update; 0 in pinned cells.
@@ -158,14 +151,14 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_prep(Dev D, Consts K, Adj A
     }
     // lane g: lower edge of group g; the upper edge comes from lane g+1
     const double xe = edge_lane ? nu_lo / T : 0.0;
-    const double ve = edge_lane ? planck_edge_value(xe, c_head_adj) : 0.0;
+    const double ve = edge_lane ? planck_edge_value(xe) : 0.0;
     const double we = edge_lane ? planck_edge_weight(xe) : 0.0;
     double xh = __shfl_down(xe, 1, Gp < 2 ? 2 : Gp);
     double vh = __shfl_down(ve, 1, Gp < 2 ? 2 : Gp);
     double wh = __shfl_down(we, 1, Gp < 2 ? 2 : Gp);
     if (work && g == G - 1 && G == Gp) {
         xh = nu_top / T;
-        vh = planck_edge_value(xh, c_head_adj);
+        vh = planck_edge_value(xh);
         wh = planck_edge_weight(xh);
     }
     if (j < K.n_cg) {
@@ -173,7 +166,7 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_prep(Dev D, Consts K, Adj A
             const double phi = phi_from_band(K.a, K.c, T, planck_band_from_edges(xe, ve, xh, vh));
             const double T3 = T * T * T;
             A.phi[j] = phi;
-            A.dphi[j] = 4.0 * phi / T + K.a * K.c * T3 * (we - wh) / UGK_PI4_15;
+            A.dphi[j] = 4.0 * phi / T + K.a * K.c * T3 * (we - wh) * UGK_15_PI4;
         } else {
             A.phi[j] = 0.0;
             A.dphi[j] = 0.0;

@@ -54,7 +54,6 @@ struct Adj {
     unsigned long long* status;   // ADJ_* words
 };
 
-hipError_t set_head_series_adj(const HeadSeries& hs);
 void launch_rec_store(const Dev& D, const Consts& K, const Adj& A, int r, hipStream_t st);
 void launch_adj_coef(const Dev& D, const Consts& K, const Adj& A, hipStream_t st);
 void launch_adj_face(const Dev& D, const Consts& K, const Adj& A, int inst, int axis, int64_t nslots,

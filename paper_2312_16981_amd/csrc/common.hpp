@@ -32,6 +32,7 @@ struct Inst {
     int64_t fy_off;        // first y-face slot (nx*(ny+1) faces, stride Gp)
     double x0, y0, dx, dy, V;
     double dt_V;           // dt / V
+    double fcx, fcy;       // -(c/eps)^2 dt / (3 dx) and / (3 dy): the face coefficients' factors
     double bcT[4];
     double w_ref;
     uint64_t seed;

@@ -15,7 +15,7 @@ namespace ugk {
 // s = c sigma dt / eps^2 of a slot from its opacity, in one evaluation order:
 // the coefficient tables store it and the sweeps re-form it from sigma alone
 // (the same bits), so that they need not read both.
-__device__ inline double s_of_sigma(const Consts& K, double sg) { return K.c * sg * K.dt / (K.eps * K.eps); }
+__device__ inline double s_of_sigma(const Consts& K, double sg) { return K.lam_scale * sg; }
 
 __device__ inline bool gate_open(const Dev& D, const Consts& K, uint32_t after)
 {

@@ -22,6 +22,7 @@ enum : uint32_t { PURPOSE_BIRTH = 1, PURPOSE_FLIGHT = 2 };
 
 // pi^4 / 15 = int_0^inf t^3/(e^t-1) dt
 #define UGK_PI4_15 6.49393940226682914909602217
+#define UGK_15_PI4 0.153989733820265027837291749
 
 struct Philox4 { uint32_t v[4]; };
 
@@ -111,66 +112,98 @@ __host__ __device__ inline double neg_log_unit(double u)
 }
 
 // ---------------------------------------------------------------------------
-// Planck band integrals.  head(x) = int_0^x t^3/(e^t-1) dt by its Taylor series
-// in x (x < 2, coefficients in constant memory supplied by the host);
-// tail(x) = int_x^inf t^3/(e^t-1) dt = sum_n e^{-nx}(x^3/n + 3x^2/n^2 + 6x/n^3 + 6/n^4).
-
-constexpr int HEAD_TERMS = 18;  // even-power terms after x^3, x^4: truncation below 4e-20 of head(x) for x < 2
-
-struct HeadSeries {
-    int nterm;                 // HEAD_TERMS
-    double c[40];              // coefficient of x^(5 + 2j)
-    double inv[64];            // inv[n] = 1/n (correctly rounded), n >= 1
+// Planck band integrals.  head(x) = int_0^x t^3/(e^t-1) dt below x = 2,
+// tail(x) = int_x^inf t^3/(e^t-1) dt = sum_n e^{-nx}(x^3/n + 3x^2/n^2 + 6x/n^3 + 6/n^4) from 2 on.
+//
+// Both are evaluated with polynomials of fixed degree, whose coefficients were
+// interpolated in 60-digit arithmetic at the Chebyshev nodes of their interval:
+//  - head = x^3 (1/3 - x/8 + x^2 q(x^2)), q of degree 10 on x^2 < 4 (the Bernoulli
+//    series of the integrand; error 4e-19 of q);
+//  - with z = e^{-x} <= e^{-2}, tail = z (x^3 + 3x^2 + 6x + 6) +
+//    z^2 (x^3 L1(z) + 3x^2 L2(z) + 6x L3(z) + 6 L4(z)), L_m = sum_{n>=2} z^{n-2} / n^m of
+//    degrees 10, 9, 9, 8: the z^2 part is at most 3% of the value and each L_m is within
+//    5e-17 of its series, so that the rounding of the first part is what is left;
+//  - the edge weight x^4/(e^x-1) = x head'(x) from the Bernoulli series below 2 and
+//    x^4 z/(1-z) above, where nothing cancels.
+// A fixed count of multiply-adds (four short chains for the tail) replaces a
+// series of up to 60 terms that ran until its slowest lane was done: the
+// sweeps are bound by their double-precision instructions, and a wavefront
+// holds both sides of x = 2.
+constexpr double kPlanckHead[11] = {
+    0x1.1111111111111p-6, -0x1.a01a01a01a00cp-13, 0x1.ed284dc73913ap-19,
+    -0x1.42cb40de6ce69p-24, 0x1.b96d78ff346dfp-30, -0x1.35de2d321efc1p-35,
+    0x1.bb24e628870e6p-41, -0x1.4129968cff7fdp-46, 0x1.d2ff446f590b8p-52,
+    -0x1.4167e3777db0cp-57, 0x1.3c38f7b6766edp-63,
+};
+constexpr double kPlanckWeight[11] = {
+    0x1.5555555555555p-4, -0x1.6c16c16c16be9p-10, 0x1.1566abc00dc60p-15,
+    -0x1.bbd7792fd1d51p-21, 0x1.66a8f1dec7df9p-26, -0x1.22803c5468dd9p-31,
+    0x1.d6d514ef48785p-37, -0x1.7d480a243cf13p-42, 0x1.31c14b6cc26a3p-47,
+    -0x1.c85ef977724aep-53, 0x1.db16cc9ec36f6p-59,
+};
+constexpr double kPlanckL1[11] = {
+    0x1.0000000000000p-1, 0x1.55555555552abp-2, 0x1.0000000031175p-2,
+    0x1.9999996d9bf5ep-3, 0x1.55555f69ddceep-3, 0x1.2490f16d2c5aap-3,
+    0x1.001c65f48b967p-3, 0x1.c41ed2a88b55ap-4, 0x1.b32a2f68f50a9p-4,
+    0x1.e02d976230df8p-5, 0x1.5fe2649cd3a3bp-3,
+};
+constexpr double kPlanckL2[10] = {
+    0x1.ffffffffffffep-3, 0x1.c71c71c71dbeap-4, 0x1.fffffffd87c9cp-5,
+    0x1.47ae156328546p-5, 0x1.c71c1b62233dap-6, 0x1.4e673a88c4a0ep-6,
+    0x1.fed17383d92dep-7, 0x1.a073e8eee8b18p-7, 0x1.00b994566244cp-7,
+    0x1.ec3cb78ada50ap-7,
+};
+constexpr double kPlanckL3[10] = {
+    0x1.0000000000000p-3, 0x1.2f684bda132b7p-5, 0x1.ffffffff37066p-7,
+    0x1.0624dd78f9432p-7, 0x1.2f68305bc51abp-8, 0x1.7e282f8ebf2f2p-9,
+    0x1.ff3ef85d092edp-10, 0x1.6f35ac8fe074fp-10, 0x1.b130dc87cf843p-11,
+    0x1.543bfa02e9c77p-10,
+};
+constexpr double kPlanckL4[9] = {
+    0x1.0000000000001p-4, 0x1.948b0fcd6c85bp-7, 0x1.0000000337272p-8,
+    0x1.a36e2ae7b4a04p-10, 0x1.948c2d1b9aa6ap-11, 0x1.b48aa20035ed0p-12,
+    0x1.023e6d3996791p-12, 0x1.2022a1c4b980ep-13, 0x1.4405e264f325cp-13,
 };
 
-__device__ inline double planck_head(double x, const HeadSeries& hs)
+template <int N>
+__host__ __device__ inline double poly(const double (&c)[N], double x)
 {
-    // x^3/3 - x^4/8 + sum_j c_j x^(5+2j), Horner in x^2 (a fixed number of
-    // terms: the coefficients are loaded together)
-    const double x2 = x * x;
-    double acc = 0.0;
+    double acc = c[N - 1];
 #pragma unroll
-    for (int j = HEAD_TERMS - 1; j >= 0; --j) acc = fma(acc, x2, hs.c[j]);
-    const double x3 = x2 * x;
-    return x3 * (1.0 / 3.0) - x3 * x * 0.125 + acc * x3 * x2;
+    for (int j = N - 2; j >= 0; --j) acc = fma(acc, x, c[j]);
+    return acc;
 }
 
-// Four terms per pass (their 1/n loaded together), stopping after the pass
-// whose last term is below 1e-18 of the sum: at most 60 terms, 21 at x = 2.
-__device__ inline double planck_tail_series(double x, const HeadSeries& hs)
+__host__ __device__ inline double planck_head(double x)
 {
-    const double e1 = exp(-x);
-    if (e1 == 0.0) return 0.0;
-    const double x2 = x * x, x3 = x2 * x, x6 = 6.0 * x, x23 = 3.0 * x2;
-    double en = e1, sum = 0.0;
-    for (int n = 1; n <= 57; n += 4) {
-        double last = 0.0;
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const double in = hs.inv[n + m];
-            const double p = fma(fma(fma(6.0, in, x6), in, x23), in, x3);
-            last = en * p * in;
-            sum += last;
-            en *= e1;
-        }
-        if (last <= 1e-18 * sum) break;
-    }
-    return sum;
+    const double x2 = x * x;
+    return x2 * x * fma(x2, poly(kPlanckHead, x2), fma(x, -0.125, 1.0 / 3.0));
+}
+
+// z = e^{-x} > 0
+__host__ __device__ inline double planck_tail(double x, double z)
+{
+    const double p1 = fma(fma(x + 3.0, x, 6.0), x, 6.0);
+    const double hi = fma(fma(poly(kPlanckL1, z), x, 3.0 * poly(kPlanckL2, z)), x, 6.0 * poly(kPlanckL3, z));
+    return z * fma(z, fma(hi, x, 6.0 * poly(kPlanckL4, z)), p1);
+}
+
+// Edge value used by group bands: head(x) below 2, tail(x) from 2 on.
+__host__ __device__ inline double planck_edge_value(double x)
+{
+    if (x < 2.0) return planck_head(x);
+    const double z = exp(-x);
+    return z == 0.0 ? 0.0 : planck_tail(x, z);
 }
 
 // x^4 / (e^x - 1): the edge term of d phi_g / dT (the band integral of a
 // group differentiated through its limits nu / T)
-__device__ inline double planck_edge_weight(double x)
+__host__ __device__ inline double planck_edge_weight(double x)
 {
-    if (x > 700.0) return 0.0;
     const double x2 = x * x;
-    return x2 * x2 / expm1(x);
-}
-
-// Edge value used by group bands: head(x) below 2, tail(x) from 2 on.
-__device__ inline double planck_edge_value(double x, const HeadSeries& hs)
-{
-    return x < 2.0 ? planck_head(x, hs) : planck_tail_series(x, hs);
+    if (x < 2.0) return x2 * x * fma(x2, poly(kPlanckWeight, x2), fma(x, -0.5, 1.0));
+    const double z = exp(-x);
+    return z == 0.0 ? 0.0 : x2 * x2 * (z / (1.0 - z));
 }
 
 // int_{xl}^{xh} t^3/(e^t-1) from edge values vl = edge_value(xl), vh = edge_value(xh).
@@ -185,7 +218,7 @@ __device__ inline double planck_band_from_edges(double xl, double vl, double xh,
 __device__ inline double phi_from_band(double a, double c, double T, double band)
 {
     const double T2 = T * T;
-    return a * c * T2 * T2 * band / UGK_PI4_15;
+    return a * c * T2 * T2 * band * UGK_15_PI4;
 }
 
 // ---------------------------------------------------------------------------
@@ -201,7 +234,6 @@ __host__ __device__ inline double coef_c4(double s)
 // and no division.  Index n is the series' own summation index.
 struct SeriesCoefs {
     double w[61];     // n / (n+1)!                       C4 - e^{-s}
-    double c2[81];    // (n-1) / (n+1)!                   C2/dt
     double c5[81];    // 1 / (n! (n+2))                   C5/dt
     double w5[81];    // n / (2 n! (n+2))                 (C5 + dt/2 e^{-s})/dt
     double wos[61];   // n / (n+1)!                       (C4 - e^{-s})/s
@@ -219,7 +251,6 @@ constexpr SeriesCoefs make_series_coefs()
             t.w[n] = (double)n / fact1;
             t.wos[n] = (double)n / fact1;
         }
-        t.c2[n] = (double)(n - 1) / fact1;
         t.c5[n] = 1.0 / (fact * (double)(n + 2));
         t.w5[n] = (double)n / (2.0 * fact * (double)(n + 2));
         t.c2ds[n] = (double)((n - 1) * (n - 1)) / fact1;
@@ -246,20 +277,31 @@ __host__ __device__ inline double coef_w(double s)
     return coef_c4(s) - exp(-s);
 }
 
-// C2/dt = [2 C4 - 1 - e^{-s}] / s; series sum_{n>=2} (-1)^{n+1} (n-1) s^{n-1}/(n+1)! below s = 2.
+// n / d with r = 1/d at hand: one correction of n r (the quotient to the last
+// bit but for rare half-way cases), 3 instructions instead of a division's 11.
+__host__ __device__ inline double quotient(double n, double d, double r)
+{
+    const double q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+
+// C2/dt = [2 C4 - 1 - e^{-s}] / s from s = 2 on; below, where that cancels, s times a
+// polynomial interpolated in 60 digits at 15 Chebyshev nodes of [0, 2] (1e-18 of the
+// series sum_{n>=2} (-1)^{n+1} (n-1) s^{n-1}/(n+1)!, whose terms ran to a stopping test).
+constexpr double kC2[15] = {
+    -0x1.5555555555555p-3, 0x1.5555555555554p-4, -0x1.99999999998f7p-6,
+    0x1.6c16c16c146a9p-8, -0x1.04104103c7cf0p-10, 0x1.3813812d8237ep-13,
+    -0x1.43a27208d508ap-16, 0x1.27e4ea93c9d63p-19, -0x1.e42f503d5530dp-23,
+    0x1.669b8c12ac8e5p-26, -0x1.e4ebe34da03a0p-30, 0x1.2bcb054dfb2d6p-33,
+    -0x1.4b6b8af1e10c9p-37, 0x1.29366afc1960cp-41, -0x1.3d06be2fd103fp-46,
+};
+
 __host__ __device__ inline double coef_c2_over_dt(double s)
 {
-    if (s < 2.0) {
-        double p = 1.0, sum = 0.0;                       // p = s^{n-1}
-        for (int n = 2; n < 80; ++n) {
-            p *= s;
-            const double t = kSeries.c2[n] * p;
-            sum += (n & 1) ? t : -t;
-            if (t < 1e-18 * fabs(sum)) break;
-        }
-        return sum;
-    }
-    return (2.0 * coef_c4(s) - 1.0 - exp(-s)) / s;
+    if (s < 2.0) return s * poly(kC2, s);
+    const double e = exp(-s), r = 1.0 / s;
+    const double c4 = quotient(1.0 - e, s, r);
+    return quotient(2.0 * c4 - 1.0 - e, s, r);
 }
 
 // C5/dt of the slope term of the UGKS free-transport flux (Sec. 2.2):

@@ -33,8 +33,6 @@
 
 namespace ugk {
 
-__constant__ HeadSeries c_head;
-
 // What a particle flight reads of its instance, copied into registers once
 // (scalar registers when the whole launch serves one instance).
 struct Geo {
@@ -97,7 +95,7 @@ __device__ inline double group_factor(const Dev& D, const Consts& K, int edge_of
     if (!K.stim) return D.simpson[edge_off + g];
     const double nl = D.nu[edge_off + g], nh = D.nu[edge_off + g + 1], nm = 0.5 * (nl + nh);
     return (nu_pow(nl, K.nu_power) * stim_factor(K, nl, T) + 4.0 * nu_pow(nm, K.nu_power) * stim_factor(K, nm, T)
-            + nu_pow(nh, K.nu_power) * stim_factor(K, nh, T)) / 6.0;
+            + nu_pow(nh, K.nu_power) * stim_factor(K, nh, T)) * (1.0 / 6.0);
 }
 
 // Group opacity of material m at T from the table (Sec. 3.4-3.5's printed
@@ -121,8 +119,11 @@ __device__ inline double table_group_sigma(const Dev& D, const Consts& K, int m,
         const double lo = (1.0 - a) * L[0] + a * L[1], hi = (1.0 - a) * L[n] + a * L[n + 1];
         v[p] = exp((1.0 - b) * lo + b * hi);
     }
-    return (v[0] + 4.0 * v[1] + v[2]) / 6.0;
+    return (v[0] + 4.0 * v[1] + v[2]) * (1.0 / 6.0);
 }
+
+// T^-q; the paper's q = 1/2 without pow().
+__device__ inline double temp_pow(double T, double q) { return q == 0.5 ? 1.0 / sqrt(T) : pow(T, -q); }
 
 // The volumetric source acts in the steps that start before its switch-off time.
 __device__ inline bool source_on(const Consts& K, uint32_t step)
@@ -147,8 +148,8 @@ __device__ inline double tau_factor(const Dev& D, const Consts& K, const Geo& I,
 __device__ inline double phi_group_direct(double T, double nl, double nh, double a, double c)
 {
     const double xl = nl / T, xh = nh / T;
-    const double band = planck_band_from_edges(xl, planck_edge_value(xl, c_head), xh,
-                                               planck_edge_value(xh, c_head));
+    const double band = planck_band_from_edges(xl, planck_edge_value(xl), xh,
+                                               planck_edge_value(xh));
     return phi_from_band(a, c, T, band);
 }
 
@@ -176,7 +177,7 @@ __global__ void k_tables(Dev D, Consts K)
     }
     const Inst& I = D.inst[s.inst];
     const double Tc = D.T[I.cell_off + s.lcell];
-    const double kap = K.t_power != 0.0 ? D.kappa[j] * pow(Tc, -K.t_power) : D.kappa[j];
+    const double kap = K.t_power != 0.0 ? D.kappa[j] * temp_pow(Tc, K.t_power) : D.kappa[j];
     const double sg = K.table ? table_group_sigma(D, K, D.tab_mat[I.cell_off + s.lcell], I.edge_off + s.g, Tc)
                               : kap * group_factor(D, K, I.edge_off, s.g, Tc);
     // flights: tau = (eps^2/c) f(nu)^-1 / kappa; with the stimulated-emission
@@ -234,12 +235,11 @@ __global__ void k_tab_logs(double* v, int64_t n)
     if (j < n) v[j] = log(v[j]);
 }
 
-// D of a face with face opacity sf and centre distance h (Appendix B, Eq. C2Formula).
-__device__ inline double face_coef(const Consts& K, double sf, double h)
+// D of a face with face opacity sf (Appendix B, Eq. C2Formula); fc is the axis'
+// factor -(c/eps)^2 dt / (3 h), h the centre distance (Inst::fcx, fcy).
+__device__ inline double face_coef(const Consts& K, double sf, double fc)
 {
-    const double s = s_of_sigma(K, sf);
-    const double c2 = K.dt * coef_c2_over_dt(s);
-    return -(K.c * K.c / (3.0 * K.eps * K.eps)) * c2 / h;
+    return fc * coef_c2_over_dt(s_of_sigma(K, sf));
 }
 
 // One instance, one axis: faces (nx+1)*ny (axis 0) or nx*(ny+1) (axis 1), Gp groups each.
@@ -254,17 +254,17 @@ __global__ void k_face_D(Dev D, Consts K, int inst, int axis)
     double* Dout = axis == 0 ? D.Dx + I.fx_off : D.Dy + I.fy_off;
     if (g >= I.G) { Dout[j] = 0.0; return; }
     int cl, cr;     // local cells on the low / high side (-1 = outside)
-    double h;
+    double fc;
     if (axis == 0) {
         const int iy = (int)(f / (I.nx + 1)), fx = (int)(f % (I.nx + 1));
         cl = fx > 0 ? iy * I.nx + fx - 1 : -1;
         cr = fx < I.nx ? iy * I.nx + fx : -1;
-        h = I.dx;
+        fc = I.fcx;
     } else {
         const int fy = (int)(f / I.nx), ix = (int)(f % I.nx);
         cl = fy > 0 ? (fy - 1) * I.nx + ix : -1;
         cr = fy < I.ny ? fy * I.nx + ix : -1;
-        h = I.dy;
+        fc = I.fcy;
     }
     double sf;
     if (cl >= 0 && cr >= 0) {
@@ -274,7 +274,7 @@ __global__ void k_face_D(Dev D, Consts K, int inst, int axis)
     } else {
         sf = D.sig[I.cg_off + ((int64_t)(cl >= 0 ? cl : cr) << I.lgGp) + g];
     }
-    Dout[j] = face_coef(K, sf, h);
+    Dout[j] = face_coef(K, sf, fc);
 }
 
 // Planckian ghost values phi_g(T_b) per instance and side.
@@ -1827,14 +1827,14 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         const double we = edge_lane ? planck_edge_weight(nu_lo / Tk) : 0.0;
         double wh = __shfl_down(we, 1, Gp < 2 ? 2 : Gp);
         if (work && g == G - 1 && G == Gp) wh = planck_edge_weight(nu_top / Tk);
-        if (work && s.active) dph = 4.0 * phi / Tk + K.a * K.c * (Tk * Tk * Tk) * (we - wh) / UGK_PI4_15;
+        if (work && s.active) dph = 4.0 * phi / Tk + K.a * K.c * (Tk * Tk * Tk) * (we - wh) * UGK_15_PI4;
     }
-    double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0;
+    double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0, rl = 1.0;    // rl = 1 / (1 + lambda)
     if (work && s.active) {
         if (TDEP) {
             // the coefficient step of Algorithm 2: sigma, lambda and the face
             // coefficients of this sweep from the iterate T^k
-            const double sk = K.table ? tsig_j : kap_j * pow(Tk, -K.t_power) * Sg;
+            const double sk = K.table ? tsig_j : kap_j * temp_pow(Tk, K.t_power) * Sg;
             sig = sk;
             lam = s_of_sigma(K, sk);
 #pragma unroll
@@ -1842,10 +1842,10 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
                 if (q >= nf) continue;
                 double sf = sk;
                 if (F.inside[q]) {
-                    const double sn = K.table ? tsig_n[q] : kap_n[q] * pow(T_nb[q], -K.t_power) * Sn[q];
+                    const double sn = K.table ? tsig_n[q] : kap_n[q] * temp_pow(T_nb[q], K.t_power) * Sn[q];
                     sf = (sk + sn > 0.0) ? 2.0 * (sk * sn) / (sk + sn) : 0.0;
                 }
-                Df[q] = face_coef(K, sf, q < 2 ? I.dx : I.dy);
+                Df[q] = face_coef(K, sf, q < 2 ? I.fcx : I.fcy);
             }
         }
         double lap = 0.0;
@@ -1856,12 +1856,13 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
             lap += F.S[q] * Df[q] * (p - phi);
         }
         b = Qj + I.dt_V * lap;
-        const double em = (b - phi) / (1.0 + lam);
+        rl = 1.0 / (1.0 + lam);
+        const double em = quotient(b - phi, 1.0 + lam, rl);
         contrib = sig * em;
         if (LIN) {
-            dcon = sig * dph / (1.0 + lam);
+            dcon = quotient(sig * dph, 1.0 + lam, rl);
         } else {
-            r = (b + lam * phi) / (1.0 + lam);
+            r = quotient(b + lam * phi, 1.0 + lam, rl);
             dr = fabs(r - rho_prev);
             mr = fabs(r);
         }
@@ -1896,7 +1897,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         if (LIN && s.active) {
             // rho^{k+1} with the linearized emission of T^{k+1}
             const double pe = pinned ? phi : phi + dph * (Tnew - Tk);
-            r = (b + lam * pe) / (1.0 + lam);
+            r = quotient(b + lam * pe, 1.0 + lam, rl);
             dr = fabs(r - rho_prev);
             mr = fabs(r);
         }
@@ -1915,12 +1916,12 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     {
         const bool edge_lane = work && g <= G;
         const double xe = edge_lane ? nu_lo / Tnew : 0.0;
-        const double ve = edge_lane ? planck_edge_value(xe, c_head) : 0.0;
+        const double ve = edge_lane ? planck_edge_value(xe) : 0.0;
         double xh = __shfl_down(xe, 1, Gp < 2 ? 2 : Gp);
         double vh = __shfl_down(ve, 1, Gp < 2 ? 2 : Gp);
         if (work && g == G - 1 && (G == Gp)) {
             xh = nu_top / Tnew;
-            vh = planck_edge_value(xh, c_head);
+            vh = planck_edge_value(xh);
         }
         if (work && s.active) phi_new = phi_from_band(K.a, K.c, Tnew, planck_band_from_edges(xe, ve, xh, vh));
     }
@@ -2171,10 +2172,10 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
         // step's final temperature (the iteration has converged on it)
         const double Tf = D.T_new[cell];
         const double sk = K.table ? table_group_sigma(D, K, D.tab_mat[cell], I.edge_off + g, Tf)
-                                  : D.kappa[j] * pow(Tf, -K.t_power) * group_factor(D, K, I.edge_off, g, Tf);
+                                  : D.kappa[j] * temp_pow(Tf, K.t_power) * group_factor(D, K, I.edge_off, g, Tf);
 #pragma unroll
         for (int q = 0; q < 2 * DIM; ++q)
-            if (bnd[q]) Df[q] = face_coef(K, sk, (q >> 1) == 0 ? I.dx : I.dy);
+            if (bnd[q]) Df[q] = face_coef(K, sk, (q >> 1) == 0 ? I.fcx : I.fcy);
     }
     if (in && s.active) {
         D.phi0[j] = phi_next;
@@ -2295,11 +2296,6 @@ __global__ void k_eval_sample_nu(int n, const double* nl, const double* nh, cons
 // launchers
 
 static inline unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
-
-hipError_t set_head_series(const HeadSeries& hs)
-{
-    return hipMemcpyToSymbol(HIP_SYMBOL(c_head), &hs, sizeof(HeadSeries));
-}
 
 void launch_tables(const Dev& D, const Consts& K, hipStream_t st)
 {

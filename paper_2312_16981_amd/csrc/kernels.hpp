@@ -12,8 +12,6 @@ struct ZeroList {
     int64_t words[8];
 };
 
-hipError_t set_head_series(const HeadSeries& hs);
-
 void launch_tables(const Dev& D, const Consts& K, hipStream_t st);
 // ln of n doubles in place (the opacity table's nodes and values at set-up).
 void launch_tab_logs(double* v, int64_t n, hipStream_t st);

@@ -49,47 +49,6 @@ struct ApiError {
     throw ApiError{code, buf};
 }
 
-// Taylor coefficients of int_0^x t^3/(e^t-1) dt beyond x^3/3 - x^4/8:
-// c_j multiplies x^(5+2j) and equals B_{2k} / ((2k)! (2k+3)), k = j+1, with
-// B_{2k}/(2k)! = (-1)^{k+1} 2 zeta(2k) / (2 pi)^{2k}.  zeta(2k) is summed directly
-// (closed forms for k = 1, 2) in long double.
-HeadSeries make_head_series()
-{
-    HeadSeries hs;
-    hs.nterm = HEAD_TERMS;
-    const long double pi = 3.141592653589793238462643383279502884L;
-    for (int j = 0; j < hs.nterm; ++j) {
-        const int k = j + 1;
-        long double zeta;
-        if (k == 1) zeta = pi * pi / 6.0L;
-        else if (k == 2) zeta = pi * pi * pi * pi / 90.0L;
-        else {
-            zeta = 0.0L;
-            const int N = 4000;
-            for (int n = N; n >= 1; --n) zeta += powl((long double)n, -2.0L * k);
-            zeta += powl((long double)N, 1.0L - 2.0L * k) / (2.0L * k - 1.0L) - 0.5L * powl((long double)N, -2.0L * k);
-        }
-        long double v = 2.0L * zeta / powl(2.0L * pi, 2.0L * k) / (2.0L * k + 3.0L);
-        if (!(k & 1)) v = -v;
-        hs.c[j] = (double)v;
-    }
-    hs.inv[0] = 0.0;
-    for (int n = 1; n < 64; ++n) hs.inv[n] = 1.0 / (double)n;
-    return hs;
-}
-
-bool g_head_ready = false;
-
-void ensure_head_series()
-{
-    if (!g_head_ready) {
-        const HeadSeries hs = make_head_series();
-        HIPCHK(set_head_series(hs));
-        HIPCHK(set_head_series_adj(hs));
-        g_head_ready = true;
-    }
-}
-
 struct HostInst {
     int dim = 1, nx = 0, ny = 1;
     double x0 = 0, x1 = 1, y0 = 0, y1 = 1;
@@ -295,7 +254,6 @@ struct ugkwp_ctx {
     // ---------------------------------------------------------------- set-up
     void setup(const std::vector<HostInst>& in)
     {
-        ensure_head_series();
         if (in.empty()) fail(UGKWP_EINVAL, "no instances");
         const int d0 = in[0].dim;
         for (const auto& h : in) {
@@ -356,6 +314,8 @@ struct ugkwp_ctx {
             I.dy = h.dim == 2 ? (h.y1 - h.y0) / h.ny : 1.0;
             I.V = I.dx * I.dy;
             I.dt_V = P.dt / I.V;
+            I.fcx = -(P.c * P.c / (3.0 * P.eps * P.eps)) * P.dt / I.dx;
+            I.fcy = -(P.c * P.c / (3.0 * P.eps * P.eps)) * P.dt / I.dy;
             I.w_ref = h.w_ref;
             I.seed = h.seed;
             cells += I.ncell;
@@ -2226,7 +2186,6 @@ int ugkwp_eval_phi(int n, const double* T, int G, const double* nu_edges, double
 {
     if (n < 0 || G < 1 || !T || !nu_edges || !out) return UGKWP_EINVAL;
     return guarded(nullptr, [&] {
-        ensure_head_series();
         Tmp t;
         double* dT = t.up(T, n);
         double* dnu = t.up(nu_edges, G + 1);

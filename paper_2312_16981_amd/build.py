@@ -12,7 +12,11 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libugkwp.so")
-SOURCES = ["kernels.hip", "adjoint.hip", "runtime.hip"]
+SOURCES = ["kernels.hip", "si_tile.hip", "adjoint.hip", "runtime.hip"]
+# The tile sweeps loop over code full of 64-bit constants (exp, the Planck
+# polynomials); hoisted out of the loop they fill the register file (256 VGPRs and
+# spills instead of 76-135), so they are formed where they are used.
+EXTRA = {"si_tile.hip": ["-mllvm", "-disable-machine-licm"]}
 ARCH = os.environ.get("UGKWP_OFFLOAD_ARCH", "gfx950")
 
 
@@ -31,7 +35,7 @@ def build(verbose=False, jobs=2):
     procs = []
     for src in SOURCES:
         obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc(), *flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc(), *flags, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((subprocess.Popen(cmd), cmd))

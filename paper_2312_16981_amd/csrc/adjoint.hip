@@ -119,7 +119,7 @@ __global__ void k_adj_face(Dev D, Consts K, Adj A, int inst, int axis)
         if (cl >= 0) dl = 1.0; else dr = 1.0;
     }
     const double ks = K.c * K.dt / (K.eps * K.eps);
-    const double dDdsf = -(K.c * K.c / (3.0 * K.eps * K.eps)) * K.dt * ks * coef_c2_over_dt_ds(ks * sf) / h;
+    const double dDdsf = -(K.c * K.c / (3.0 * K.eps * K.eps)) * K.dt * ks * coef_c2_over_dt_ds(math_tab(), ks * sf) / h;
     Dl[j] = dDdsf * dl;
     Dh[j] = dDdsf * dr;
 }
@@ -151,15 +151,15 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_prep(Dev D, Consts K, Adj A
     }
     // lane g: lower edge of group g; the upper edge comes from lane g+1
     const double xe = edge_lane ? nu_lo / T : 0.0;
-    const double ve = edge_lane ? planck_edge_value(xe) : 0.0;
-    const double we = edge_lane ? planck_edge_weight(xe) : 0.0;
-    double xh = __shfl_down(xe, 1, Gp < 2 ? 2 : Gp);
-    double vh = __shfl_down(ve, 1, Gp < 2 ? 2 : Gp);
-    double wh = __shfl_down(we, 1, Gp < 2 ? 2 : Gp);
+    const TabPtr mt = math_tab();
+    double ve = 0.0, we = 0.0;
+    if (edge_lane) planck_edge_both(mt, xe, &ve, &we);
+    double xh = next_lane(xe);
+    double vh = next_lane(ve);
+    double wh = next_lane(we);
     if (work && g == G - 1 && G == Gp) {
         xh = nu_top / T;
-        vh = planck_edge_value(xh);
-        wh = planck_edge_weight(xh);
+        planck_edge_both(mt, xh, &vh, &wh);
     }
     if (j < K.n_cg) {
         if (s.active) {

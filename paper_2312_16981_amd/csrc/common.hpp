@@ -17,6 +17,11 @@ constexpr int MAX_G = 64;
 constexpr int RES_SLOTS = 3;     // rotating residual slots of the source iteration
 constexpr int RES_SUB = 64;      // sub-slots per residual slot (spread the atomics of many blocks)
 constexpr int DIAG_SUB = 16;     // sub-slots of the per-instance energy sums
+constexpr int TILE_S_MAX = 8;    // most source-iteration sweeps per launch (1-D, si_tile.hip)
+
+// Threads per tile block: the sweeps that follow the opacity and those that keep the
+// Planck coefficients in registers hold too many for 16 wavefronts per CU.
+constexpr int tile_max_threads(bool tdep, bool reg) { return tdep || reg ? 512 : 1024; }
 
 enum { BC_VACUUM = 0, BC_PLANCK = 1, BC_REFLECT = 2 };
 enum { XLO = 0, XHI = 1, YLO = 2, YHI = 3 };
@@ -59,6 +64,12 @@ struct Consts {
     int has_src;           // 1: a volumetric source D.qsrc
     double q_toff;         // the source acts in steps that start before this time
     double si_tol;
+    int si_max;            // most sweeps of a source iteration
+    // the 1-D iteration in tiles (si_tile.hpp): sweeps per round, cells computed along on either side
+    // of a tile, sweep planes kept per round parity, sweeps of a step's first round
+    // beyond the step before's, blocks, threads per block and cells per thread
+    int tile_S, tile_H, tile_cap, tile_extra, tile_blocks, tile_threads, tile_cpt;
+    int tile_reg;          // the Planck coefficients of the tile sweeps in registers
     int64_t n_cap;
     int64_t pool_cap;
     uint32_t flags;
@@ -80,7 +91,8 @@ struct Resid {
 
 // Per-instance step state.
 struct InstState {
-    int conv_sweeps;       // sweeps used by the converged source iteration, 0 = running
+    int conv_sweeps;       // sweeps used by the converged source iteration, 0 = running (-1: a
+                           // temperature failed, 1-D)
     int bad;               // non-finite / non-positive temperature seen
     uint64_t births;       // birth counter B_n (carried from step to step)
 };
@@ -166,6 +178,7 @@ struct Dev {
     double* rhoh;               // rho^h = rho^n - rhop (start of step)
     double* Q;
     double* phi0;               // phi(T^n): the source iteration's phi^0
+    double* phi0n;              // phi(T^{n+1}) (the two swap when the step commits)
     double* phi1;               // phi^{k+1} of the even sweeps
     double* phi2;               // phi^{k+1} of the odd sweeps
     int32_t* nb;                // births per slot
@@ -176,7 +189,8 @@ struct Dev {
     double* sy;
     double* bcoef;              // slope coefficient of the wave flux: C5 or C5 + dt/2 e^{-s}, over dt
     double* rho_alt;            // rho^k of the even sweeps with UGKWP_FLAG_WAVE_ITER
-    double* winflow;            // [2][slot] boundary wave inflow of the last even / odd sweep (WAVE_ITER)
+    double* winflow;            // boundary wave inflow of the last sweeps (WAVE_ITER): 2-D [2][slot], the
+                                // last even and odd one; 1-D by plane, see tile_inflow
     int32_t* nbi;               // interior births per slot (nb adds the boundary-source births)
     double* beta;
     double* dep;
@@ -212,6 +226,17 @@ struct Dev {
     int32_t* tab_gi;            // [edge][3] nu interval of each group's Simpson points
     double* tab_ga;             // [edge][3] and the weight of its upper node
     double* tab_sig;            // [2][slot] group sigma at the iterate written by sweep k for sweep k+1
+    // the 1-D iteration in tiles: outputs of a round's sweeps by plane, residuals
+    // per round parity, sweep and block, and for batches each block's instance and
+    // tile and each instance's first block
+    double* tile_rho;
+    double* tile_phi;
+    double* tile_T;
+    double* tile_u;
+    double* tile_Q;             // (WAVE_ITER)
+    Resid* tile_res;
+    const int2* tile_blk;
+    const int32_t* tile_start;
     // per instance
     InstState* ist;
     Resid* res;                 // [RES_SLOTS][n_inst][RES_SUB]

@@ -22,6 +22,35 @@ __device__ inline bool gate_open(const Dev& D, const Consts& K, uint32_t after)
     return K.gate == GATE_OFF || *D.step == K.gate + after;
 }
 
+// The kernels of a small step are chains of waits a few hundred cycles long: on the
+// arguments (over a kilobyte, 64 bytes to a line of the scalar cache, fetched line by
+// line as the code reaches them) and on single words that the launch before wrote.
+// warm_args touches every line of the first BYTES of the arguments at once, so that one
+// wait covers them all.
+template <int BYTES>
+__device__ inline void warm_args()
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    const auto* p = (const __attribute__((address_space(4))) uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t x = 0;
+#pragma unroll
+    for (int i = 0; i < BYTES; i += 64) x |= p[i / 4];
+    asm volatile("" ::"s"(x));
+#endif
+}
+
+// A zero the compiler does not know, one per lane: a uniform word read at p + lane_zero()
+// is a vector load, which is in flight beside the slot's own loads; a scalar load of it
+// would be waited for together with every argument read after it.
+__device__ inline int lane_zero()
+{
+    int z = 0;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(z));
+#endif
+    return z;
+}
+
 struct Slot {
     int inst, lcell, g;
     bool cell_ok, active;
@@ -74,6 +103,9 @@ __device__ inline unsigned long long dbits(double v) { return (unsigned long lon
 __device__ inline double bitsd(unsigned long long v) { return __longlong_as_double((long long)v); }
 
 
+// The larger of two non-negative doubles, NaN above everything (the order of their bits).
+__device__ inline double nan_max(double a, double b) { return bitsd(max(dbits(a), dbits(b))); }
+
 // Largest value over the wavefront by DPP row steps: within quads, half rows,
 // rows, then across rows (row broadcasts 15 and 31); lane 63 ends with the
 // maximum, which is returned to every lane.
@@ -106,19 +138,45 @@ __device__ inline double dpp_f64(double v)
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
+// The value of the next lane (0 in lane 63), by a wavefront shift.
+__device__ inline double next_lane(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, 0x130, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x130, 0xF, 0xF, true);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
+// v + (v of the lane 16 or 32 lanes across) by row and half swaps of registers:
+// the same sum, with the same bits, in both lanes, without the shuffles' trip
+// through the LDS unit.
+template <int N>
+__device__ inline double add_across(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+    const auto l = N == 16 ? __builtin_amdgcn_permlane16_swap(lo, lo, false, false)
+                           : __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = N == 16 ? __builtin_amdgcn_permlane16_swap(hi, hi, false, false)
+                           : __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    const double a = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0]));
+    const double c = __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+    return a + c;
+}
+
 // Sum over aligned groups of n lanes (n a power of two up to 64, the same in
 // every lane).  Each step adds two partial sums that every lane of a group
 // holds with the same bits, so all lanes of a group end with the same bits:
 // pairs and quads (quad permutes), 8 and 16 lanes (half-row and row mirrors),
-// then 32 and 64 lanes by shuffles.
+// then 32 and 64 lanes by row and half swaps.
 __device__ inline double group_sum(double v, int n)
 {
     if (n > 1) v += dpp_f64<0xB1, 0xF>(v);     // quad_perm 1,0,3,2
     if (n > 2) v += dpp_f64<0x4E, 0xF>(v);     // quad_perm 2,3,0,1
     if (n > 4) v += dpp_f64<0x141, 0xF>(v);    // row_half_mirror
     if (n > 8) v += dpp_f64<0x140, 0xF>(v);    // row_mirror
-    if (n > 16) v += __shfl_xor(v, 16, WAVE);
-    if (n > 32) v += __shfl_xor(v, 32, WAVE);
+    if (n > 16) v = add_across<16>(v);
+    if (n > 32) v = add_across<32>(v);
     return v;
 }
 

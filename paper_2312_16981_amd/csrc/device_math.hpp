@@ -112,11 +112,217 @@ __host__ __device__ inline double neg_log_unit(double u)
 }
 
 // ---------------------------------------------------------------------------
+// Polynomial coefficients of the functions below, interpolated in 60-digit
+// arithmetic at the Chebyshev nodes of each interval, in ascending order.  They
+// are read from constant memory with scalar loads (math_tab) and enter each
+// multiply-add as a scalar operand (horner): as literals every one of them cost two
+// vector moves beside its multiply-add, 40% of a source-iteration sweep's vector
+// instructions.
+struct MathTab {
+    double head[11], weight[11], L1[11], L2[10], L3[10], L4[9];   // Planck edge integrals
+    double ex[10];        // (e^{-r} - 1 + r) / r^2 on |r| <= ln 2 / 2
+    double one_ex[15];    // (1 - e^{-x}) / x on [0, 2]
+    double w[12];         // (C4 - e^{-s}) / s on [0, 1]
+    double c2[15];        // (C2/dt) / s on [0, 2]
+};
+
+static __device__ __constant__ MathTab g_math_tab = {
+    // head
+    {
+        0x1.1111111111111p-6, -0x1.a01a01a01a00cp-13, 0x1.ed284dc73913ap-19,
+        -0x1.42cb40de6ce69p-24, 0x1.b96d78ff346dfp-30, -0x1.35de2d321efc1p-35,
+        0x1.bb24e628870e6p-41, -0x1.4129968cff7fdp-46, 0x1.d2ff446f590b8p-52,
+        -0x1.4167e3777db0cp-57, 0x1.3c38f7b6766edp-63},
+    // weight
+    {
+        0x1.5555555555555p-4, -0x1.6c16c16c16be9p-10, 0x1.1566abc00dc60p-15,
+        -0x1.bbd7792fd1d51p-21, 0x1.66a8f1dec7df9p-26, -0x1.22803c5468dd9p-31,
+        0x1.d6d514ef48785p-37, -0x1.7d480a243cf13p-42, 0x1.31c14b6cc26a3p-47,
+        -0x1.c85ef977724aep-53, 0x1.db16cc9ec36f6p-59},
+    // L1, L2, L3, L4
+    {
+        0x1.0000000000000p-1, 0x1.55555555552abp-2, 0x1.0000000031175p-2,
+        0x1.9999996d9bf5ep-3, 0x1.55555f69ddceep-3, 0x1.2490f16d2c5aap-3,
+        0x1.001c65f48b967p-3, 0x1.c41ed2a88b55ap-4, 0x1.b32a2f68f50a9p-4,
+        0x1.e02d976230df8p-5, 0x1.5fe2649cd3a3bp-3},
+    {
+        0x1.ffffffffffffep-3, 0x1.c71c71c71dbeap-4, 0x1.fffffffd87c9cp-5,
+        0x1.47ae156328546p-5, 0x1.c71c1b62233dap-6, 0x1.4e673a88c4a0ep-6,
+        0x1.fed17383d92dep-7, 0x1.a073e8eee8b18p-7, 0x1.00b994566244cp-7,
+        0x1.ec3cb78ada50ap-7},
+    {
+        0x1.0000000000000p-3, 0x1.2f684bda132b7p-5, 0x1.ffffffff37066p-7,
+        0x1.0624dd78f9432p-7, 0x1.2f68305bc51abp-8, 0x1.7e282f8ebf2f2p-9,
+        0x1.ff3ef85d092edp-10, 0x1.6f35ac8fe074fp-10, 0x1.b130dc87cf843p-11,
+        0x1.543bfa02e9c77p-10},
+    {
+        0x1.0000000000001p-4, 0x1.948b0fcd6c85bp-7, 0x1.0000000337272p-8,
+        0x1.a36e2ae7b4a04p-10, 0x1.948c2d1b9aa6ap-11, 0x1.b48aa20035ed0p-12,
+        0x1.023e6d3996791p-12, 0x1.2022a1c4b980ep-13, 0x1.4405e264f325cp-13},
+    // ex
+    {
+        0x1.0000000000001p-1, -0x1.5555555555556p-3, 0x1.5555555553d63p-5, -0x1.11111111109b3p-7, 0x1.6c16c1788bd90p-10,
+        -0x1.a01a01a7c41d5p-13, 0x1.a019b90d2ae7ap-16, -0x1.71de0dae63bb3p-19, 0x1.289185613a3d6p-22,
+        -0x1.af38a9b0ec855p-26},
+    // one_ex
+    {
+        0x1.0000000000000p+0, -0x1.ffffffffffffbp-2, 0x1.55555555553e2p-3, -0x1.555555554ff99p-5, 0x1.111111106b15bp-7,
+        -0x1.6c16c153ded1bp-10, 0x1.a019ff50cb17dp-13, -0x1.a019dae22ccbcp-16, 0x1.71dc6e07bfee1p-19,
+        -0x1.27d5968445595p-22, 0x1.ada5400e8ee01p-26, -0x1.1b960644cf556p-29, 0x1.4bed628f79b85p-33,
+        -0x1.375240aee064dp-37, 0x1.566ca7300ffc9p-42},
+    // w
+    {
+        0x1.0000000000000p-1, -0x1.5555555555519p-2, 0x1.fffffffffd314p-4, -0x1.11111110a7febp-5, 0x1.c71c71a754d26p-8,
+        -0x1.38137e610a937p-10, 0x1.6c166edfaf704p-13, -0x1.71d809f19c654p-16, 0x1.4c91f8a6b2e53p-19,
+        -0x1.0a541db8a7dfdp-22, 0x1.6d0ad6972752dp-26, -0x1.4e8a878a9e670p-30},
+    // c2
+    {
+        -0x1.5555555555555p-3, 0x1.5555555555554p-4, -0x1.99999999998f7p-6,
+        0x1.6c16c16c146a9p-8, -0x1.04104103c7cf0p-10, 0x1.3813812d8237ep-13,
+        -0x1.43a27208d508ap-16, 0x1.27e4ea93c9d63p-19, -0x1.e42f503d5530dp-23,
+        0x1.669b8c12ac8e5p-26, -0x1.e4ebe34da03a0p-30, 0x1.2bcb054dfb2d6p-33,
+        -0x1.4b6b8af1e10c9p-37, 0x1.29366afc1960cp-41, -0x1.3d06be2fd103fp-46},
+};
+
+#ifdef __HIP_DEVICE_COMPILE__
+typedef const __attribute__((address_space(4))) MathTab* TabPtr;
+typedef const __attribute__((address_space(4))) double* CoefPtr;
+#else
+typedef const MathTab* TabPtr;
+typedef const double* CoefPtr;
+#endif
+
+// The table, by an address the compiler does not know: a loop that asks for it
+// in its body loads the coefficients there instead of keeping all of them in
+// registers throughout.
+__device__ inline TabPtr math_tab()
+{
+    TabPtr p = (TabPtr)&g_math_tab;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+s"(p));
+#endif
+    return p;
+}
+
+// Horner steps a = a x + c with the coefficients in scalar registers: the compiler
+// prefers the two-operand multiply-add, whose addend is also its destination, and
+// copies each coefficient to vector registers first.  The s_nop covers the two wait
+// states between a vector instruction that writes a scalar register (a spilled
+// coefficient read back from a lane) and its use here, which the compiler counts only
+// for instructions it knows; callers likewise pass the result through an operation of
+// their own before any cross-lane move.
+#ifdef __HIP_DEVICE_COMPILE__
+#define UGK_FMA "v_fma_f64 %0, %0, %1, "
+#endif
+template <int N>
+__device__ inline double horner(CoefPtr c, double a, double x)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    if constexpr (N >= 4) {
+        asm("s_nop 1\n\t" UGK_FMA "%2\n\t" UGK_FMA "%3\n\t" UGK_FMA "%4\n\t" UGK_FMA "%5"
+            : "+&v"(a) : "v"(x), "s"(c[N - 1]), "s"(c[N - 2]), "s"(c[N - 3]), "s"(c[N - 4]));
+        return horner<N - 4>(c, a, x);
+    } else if constexpr (N == 3) {
+        asm("s_nop 1\n\t" UGK_FMA "%2\n\t" UGK_FMA "%3\n\t" UGK_FMA "%4"
+            : "+&v"(a) : "v"(x), "s"(c[2]), "s"(c[1]), "s"(c[0]));
+    } else if constexpr (N == 2) {
+        asm("s_nop 1\n\t" UGK_FMA "%2\n\t" UGK_FMA "%3" : "+&v"(a) : "v"(x), "s"(c[1]), "s"(c[0]));
+    } else if constexpr (N == 1) {
+        asm("s_nop 1\n\t" UGK_FMA "%2" : "+&v"(a) : "v"(x), "s"(c[0]));
+    }
+    return a;
+#else
+    for (int j = N - 1; j >= 0; --j) a = fma(a, x, c[j]);
+    return a;
+#endif
+}
+
+// c[0] + x (c[1] + ... + x c[N-1])
+#ifdef __HIP_DEVICE_COMPILE__
+template <int N>
+__device__ inline double poly(const __attribute__((address_space(4))) double (&c)[N], double x)
+{
+    return horner<N - 2>((CoefPtr)&c[0], fma(x, c[N - 1], c[N - 2]), x);
+}
+#endif
+
+template <int N>
+__device__ inline double poly(const double (&c)[N], double x)
+{
+    double acc = c[N - 1];
+#pragma unroll
+    for (int j = N - 2; j >= 0; --j) acc = fma(acc, x, c[j]);
+    return acc;
+}
+
+// The coefficients of the Planck integrals and the exponential kept in vector
+// registers: for blocks too few to hide the scalar loads' latency behind each other.
+struct RegTab {
+    double head[11], weight[11], L1[11], L2[10], L3[10], L4[9], ex[10];
+    __device__ inline const RegTab* operator->() const { return this; }
+};
+
+// W: with the edge weights' coefficients.
+template <bool W>
+__device__ inline RegTab reg_tab()
+{
+    const TabPtr t = math_tab();
+    RegTab r;
+#ifdef __HIP_DEVICE_COMPILE__
+#define UGK_KEEP(x) asm volatile("" : "+v"(x))
+#else
+#define UGK_KEEP(x)
+#endif
+#pragma unroll
+    for (int j = 0; j < 11; ++j) {
+        r.head[j] = t->head[j];
+        r.L1[j] = t->L1[j];
+        r.weight[j] = W ? t->weight[j] : 0.0;
+        UGK_KEEP(r.head[j]);
+        UGK_KEEP(r.L1[j]);
+        if (W) UGK_KEEP(r.weight[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 10; ++j) {
+        r.L2[j] = t->L2[j];
+        r.L3[j] = t->L3[j];
+        r.ex[j] = t->ex[j];
+        UGK_KEEP(r.L2[j]);
+        UGK_KEEP(r.L3[j]);
+        UGK_KEEP(r.ex[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 9; ++j) {
+        r.L4[j] = t->L4[j];
+        UGK_KEEP(r.L4[j]);
+    }
+#undef UGK_KEEP
+    return r;
+}
+
+// e^{-x} for any x (inf for NaN): x = k ln 2 + r with |r| <= ln 2 / 2 (ln 2
+// in two parts, k times the first exact), e^{-r} = 1 - r + r^2 q(r), q of degree 9 within 2e-16.
+template <class Tab>
+__device__ inline double exp_neg(const Tab& t, double x)
+{
+    x = fmin(fmax(x, -800.0), 800.0);
+    const double k = rint(x * 0x1.71547652b82fep+0);
+    const double r = fma(-k, 0x1.473de6af278edp-34, fma(-k, 0x1.62e42fef00000p-1, x));
+    const double p = fma(r, fma(r, poly<10>(t->ex, r), -1.0), 1.0);
+    return ldexp(p, -(int)k);
+}
+
+// 1 - e^{-x} for x >= 0, without cancellation below 2.
+__device__ inline double one_less_exp_neg(TabPtr t, double x)
+{
+    return x < 2.0 ? x * poly<15>(t->one_ex, x) : 1.0 - exp_neg(t, x);
+}
+
+// ---------------------------------------------------------------------------
 // Planck band integrals.  head(x) = int_0^x t^3/(e^t-1) dt below x = 2,
 // tail(x) = int_x^inf t^3/(e^t-1) dt = sum_n e^{-nx}(x^3/n + 3x^2/n^2 + 6x/n^3 + 6/n^4) from 2 on.
 //
-// Both are evaluated with polynomials of fixed degree, whose coefficients were
-// interpolated in 60-digit arithmetic at the Chebyshev nodes of their interval:
+// Both are evaluated with polynomials of fixed degree:
 //  - head = x^3 (1/3 - x/8 + x^2 q(x^2)), q of degree 10 on x^2 < 4 (the Bernoulli
 //    series of the integrand; error 4e-19 of q);
 //  - with z = e^{-x} <= e^{-2}, tail = z (x^3 + 3x^2 + 6x + 6) +
@@ -128,82 +334,61 @@ __host__ __device__ inline double neg_log_unit(double u)
 // A fixed count of multiply-adds (four short chains for the tail) replaces a
 // series of up to 60 terms that ran until its slowest lane was done: the
 // sweeps are bound by their double-precision instructions, and a wavefront
-// holds both sides of x = 2.
-constexpr double kPlanckHead[11] = {
-    0x1.1111111111111p-6, -0x1.a01a01a01a00cp-13, 0x1.ed284dc73913ap-19,
-    -0x1.42cb40de6ce69p-24, 0x1.b96d78ff346dfp-30, -0x1.35de2d321efc1p-35,
-    0x1.bb24e628870e6p-41, -0x1.4129968cff7fdp-46, 0x1.d2ff446f590b8p-52,
-    -0x1.4167e3777db0cp-57, 0x1.3c38f7b6766edp-63,
-};
-constexpr double kPlanckWeight[11] = {
-    0x1.5555555555555p-4, -0x1.6c16c16c16be9p-10, 0x1.1566abc00dc60p-15,
-    -0x1.bbd7792fd1d51p-21, 0x1.66a8f1dec7df9p-26, -0x1.22803c5468dd9p-31,
-    0x1.d6d514ef48785p-37, -0x1.7d480a243cf13p-42, 0x1.31c14b6cc26a3p-47,
-    -0x1.c85ef977724aep-53, 0x1.db16cc9ec36f6p-59,
-};
-constexpr double kPlanckL1[11] = {
-    0x1.0000000000000p-1, 0x1.55555555552abp-2, 0x1.0000000031175p-2,
-    0x1.9999996d9bf5ep-3, 0x1.55555f69ddceep-3, 0x1.2490f16d2c5aap-3,
-    0x1.001c65f48b967p-3, 0x1.c41ed2a88b55ap-4, 0x1.b32a2f68f50a9p-4,
-    0x1.e02d976230df8p-5, 0x1.5fe2649cd3a3bp-3,
-};
-constexpr double kPlanckL2[10] = {
-    0x1.ffffffffffffep-3, 0x1.c71c71c71dbeap-4, 0x1.fffffffd87c9cp-5,
-    0x1.47ae156328546p-5, 0x1.c71c1b62233dap-6, 0x1.4e673a88c4a0ep-6,
-    0x1.fed17383d92dep-7, 0x1.a073e8eee8b18p-7, 0x1.00b994566244cp-7,
-    0x1.ec3cb78ada50ap-7,
-};
-constexpr double kPlanckL3[10] = {
-    0x1.0000000000000p-3, 0x1.2f684bda132b7p-5, 0x1.ffffffff37066p-7,
-    0x1.0624dd78f9432p-7, 0x1.2f68305bc51abp-8, 0x1.7e282f8ebf2f2p-9,
-    0x1.ff3ef85d092edp-10, 0x1.6f35ac8fe074fp-10, 0x1.b130dc87cf843p-11,
-    0x1.543bfa02e9c77p-10,
-};
-constexpr double kPlanckL4[9] = {
-    0x1.0000000000001p-4, 0x1.948b0fcd6c85bp-7, 0x1.0000000337272p-8,
-    0x1.a36e2ae7b4a04p-10, 0x1.948c2d1b9aa6ap-11, 0x1.b48aa20035ed0p-12,
-    0x1.023e6d3996791p-12, 0x1.2022a1c4b980ep-13, 0x1.4405e264f325cp-13,
-};
-
-template <int N>
-__host__ __device__ inline double poly(const double (&c)[N], double x)
-{
-    double acc = c[N - 1];
-#pragma unroll
-    for (int j = N - 2; j >= 0; --j) acc = fma(acc, x, c[j]);
-    return acc;
-}
-
-__host__ __device__ inline double planck_head(double x)
+// holds both sides of x = 2.  Tab: TabPtr or RegTab.
+template <class Tab>
+__device__ inline double planck_head(const Tab& t, double x)
 {
     const double x2 = x * x;
-    return x2 * x * fma(x2, poly(kPlanckHead, x2), fma(x, -0.125, 1.0 / 3.0));
+    return x2 * x * fma(x2, poly<11>(t->head, x2), fma(x, -0.125, 1.0 / 3.0));
 }
 
 // z = e^{-x} > 0
-__host__ __device__ inline double planck_tail(double x, double z)
+template <class Tab>
+__device__ inline double planck_tail(const Tab& t, double x, double z)
 {
     const double p1 = fma(fma(x + 3.0, x, 6.0), x, 6.0);
-    const double hi = fma(fma(poly(kPlanckL1, z), x, 3.0 * poly(kPlanckL2, z)), x, 6.0 * poly(kPlanckL3, z));
-    return z * fma(z, fma(hi, x, 6.0 * poly(kPlanckL4, z)), p1);
+    const double hi = fma(fma(poly<11>(t->L1, z), x, 3.0 * poly<10>(t->L2, z)), x, 6.0 * poly<10>(t->L3, z));
+    return z * fma(z, fma(hi, x, 6.0 * poly<9>(t->L4, z)), p1);
+}
+
+template <class Tab>
+__device__ inline double planck_weight_head(const Tab& t, double x)
+{
+    const double x2 = x * x;
+    return x2 * x * fma(x2, poly<11>(t->weight, x2), fma(x, -0.5, 1.0));
 }
 
 // Edge value used by group bands: head(x) below 2, tail(x) from 2 on.
-__host__ __device__ inline double planck_edge_value(double x)
+template <class Tab>
+__device__ inline double planck_edge_value(const Tab& t, double x)
 {
-    if (x < 2.0) return planck_head(x);
-    const double z = exp(-x);
-    return z == 0.0 ? 0.0 : planck_tail(x, z);
+    if (x < 2.0) return planck_head(t, x);
+    const double z = exp_neg(t, x);
+    return z == 0.0 ? 0.0 : planck_tail(t, x, z);
 }
 
 // x^4 / (e^x - 1): the edge term of d phi_g / dT (the band integral of a
 // group differentiated through its limits nu / T)
-__host__ __device__ inline double planck_edge_weight(double x)
+template <class Tab>
+__device__ inline double planck_edge_weight(const Tab& t, double x)
 {
-    const double x2 = x * x;
-    if (x < 2.0) return x2 * x * fma(x2, poly(kPlanckWeight, x2), fma(x, -0.5, 1.0));
-    const double z = exp(-x);
+    if (x < 2.0) return planck_weight_head(t, x);
+    const double z = exp_neg(t, x), x2 = x * x;
     return z == 0.0 ? 0.0 : x2 * x2 * (z / (1.0 - z));
+}
+
+// Both, with one exponential.
+template <class Tab>
+__device__ inline void planck_edge_both(const Tab& t, double x, double* v, double* w)
+{
+    if (x < 2.0) {
+        *v = planck_head(t, x);
+        *w = planck_weight_head(t, x);
+        return;
+    }
+    const double z = exp_neg(t, x), x2 = x * x;
+    *v = z == 0.0 ? 0.0 : planck_tail(t, x, z);
+    *w = z == 0.0 ? 0.0 : x2 * x2 * (z / (1.0 - z));
 }
 
 // int_{xl}^{xh} t^3/(e^t-1) from edge values vl = edge_value(xl), vh = edge_value(xh).
@@ -224,16 +409,15 @@ __device__ inline double phi_from_band(double a, double c, double T, double band
 // ---------------------------------------------------------------------------
 // Flux coefficients as functions of s = c sigma dt / eps^2.
 
-__host__ __device__ inline double coef_c4(double s)
+__device__ inline double coef_c4(TabPtr t, double s)
 {
-    return s == 0.0 ? 1.0 : -expm1(-s) / s;
+    return s < 2.0 ? poly<15>(t->one_ex, s) : (1.0 - exp_neg(t, s)) / s;
 }
 
 // The power-series coefficients of the functions below, fixed at compile time
 // (each a ratio of integers rounded once), so that a term costs a multiply
 // and no division.  Index n is the series' own summation index.
 struct SeriesCoefs {
-    double w[61];     // n / (n+1)!                       C4 - e^{-s}
     double c5[81];    // 1 / (n! (n+2))                   C5/dt
     double w5[81];    // n / (2 n! (n+2))                 (C5 + dt/2 e^{-s})/dt
     double wos[61];   // n / (n+1)!                       (C4 - e^{-s})/s
@@ -247,10 +431,7 @@ constexpr SeriesCoefs make_series_coefs()
     for (int n = 0; n < 81; ++n) {
         if (n > 0) fact *= (double)n;
         const double fact1 = fact * (double)(n + 1);     // (n+1)!
-        if (n < 61) {
-            t.w[n] = (double)n / fact1;
-            t.wos[n] = (double)n / fact1;
-        }
+        if (n < 61) t.wos[n] = (double)n / fact1;
         t.c5[n] = 1.0 / (fact * (double)(n + 2));
         t.w5[n] = (double)n / (2.0 * fact * (double)(n + 2));
         t.c2ds[n] = (double)((n - 1) * (n - 1)) / fact1;
@@ -260,21 +441,11 @@ constexpr SeriesCoefs make_series_coefs()
 
 constexpr SeriesCoefs kSeries = make_series_coefs();
 
-// C4 - e^{-s}; alternating series sum_{n>=1} (-1)^{n+1} n s^n/(n+1)! below s = 1 to
-// avoid cancellation.
-__host__ __device__ inline double coef_w(double s)
+// C4 - e^{-s}: below s = 1, where that cancels, s times the polynomial of its series
+// sum_{n>=1} (-1)^{n+1} n s^n/(n+1)! (within 4e-17).
+__device__ inline double coef_w(TabPtr t, double s)
 {
-    if (s < 1.0) {
-        double p = 1.0, sum = 0.0;
-        for (int n = 1; n < 60; ++n) {
-            p *= s;
-            const double t = kSeries.w[n] * p;
-            sum += (n & 1) ? t : -t;
-            if (t < 1e-18 * fabs(sum)) break;
-        }
-        return sum;
-    }
-    return coef_c4(s) - exp(-s);
+    return s < 1.0 ? s * poly<12>(t->w, s) : coef_c4(t, s) - exp_neg(t, s);
 }
 
 // n / d with r = 1/d at hand: one correction of n r (the quotient to the last
@@ -285,21 +456,12 @@ __host__ __device__ inline double quotient(double n, double d, double r)
     return fma(fma(-d, q, n), r, q);
 }
 
-// C2/dt = [2 C4 - 1 - e^{-s}] / s from s = 2 on; below, where that cancels, s times a
-// polynomial interpolated in 60 digits at 15 Chebyshev nodes of [0, 2] (1e-18 of the
-// series sum_{n>=2} (-1)^{n+1} (n-1) s^{n-1}/(n+1)!, whose terms ran to a stopping test).
-constexpr double kC2[15] = {
-    -0x1.5555555555555p-3, 0x1.5555555555554p-4, -0x1.99999999998f7p-6,
-    0x1.6c16c16c146a9p-8, -0x1.04104103c7cf0p-10, 0x1.3813812d8237ep-13,
-    -0x1.43a27208d508ap-16, 0x1.27e4ea93c9d63p-19, -0x1.e42f503d5530dp-23,
-    0x1.669b8c12ac8e5p-26, -0x1.e4ebe34da03a0p-30, 0x1.2bcb054dfb2d6p-33,
-    -0x1.4b6b8af1e10c9p-37, 0x1.29366afc1960cp-41, -0x1.3d06be2fd103fp-46,
-};
-
-__host__ __device__ inline double coef_c2_over_dt(double s)
+// C2/dt = [2 C4 - 1 - e^{-s}] / s from s = 2 on; below, where that cancels, s times the
+// polynomial of the series sum_{n>=2} (-1)^{n+1} (n-1) s^{n-1}/(n+1)! (within 1e-18).
+__device__ inline double coef_c2_over_dt(TabPtr t, double s)
 {
-    if (s < 2.0) return s * poly(kC2, s);
-    const double e = exp(-s), r = 1.0 / s;
+    if (s < 2.0) return s * poly<15>(t->c2, s);
+    const double e = exp_neg(t, s), r = 1.0 / s;
     const double c4 = quotient(1.0 - e, s, r);
     return quotient(2.0 * c4 - 1.0 - e, s, r);
 }
@@ -357,26 +519,26 @@ __host__ __device__ inline double coef_w_over_s(double s)
         }
         return sum;
     }
-    return coef_w(s) / s;
+    return (-expm1(-s) / s - exp(-s)) / s;
 }
 
 __host__ __device__ inline double coef_c4_ds(double s) { return -coef_w_over_s(s); }
 
 __host__ __device__ inline double coef_w_ds(double s) { return exp(-s) - coef_w_over_s(s); }
 
-__host__ __device__ inline double coef_c2_over_dt_ds(double s)
+__device__ inline double coef_c2_over_dt_ds(TabPtr t, double s)
 {
     if (s < 2.0) {
         double p = 1.0, sum = -1.0 / 6.0;               // n = 2 term
         for (int n = 3; n < 80; ++n) {
             p *= s;                                     // s^{n-2}
-            const double t = kSeries.c2ds[n] * p;
-            sum += (n & 1) ? t : -t;
-            if (t < 1e-18 * fabs(sum)) break;
+            const double q = kSeries.c2ds[n] * p;
+            sum += (n & 1) ? q : -q;
+            if (q < 1e-18 * fabs(sum)) break;
         }
         return sum;
     }
-    return (exp(-s) - 2.0 * coef_w_over_s(s) - coef_c2_over_dt(s)) / s;
+    return (exp(-s) - 2.0 * coef_w_over_s(s) - coef_c2_over_dt(t, s)) / s;
 }
 
 // ---------------------------------------------------------------------------

@@ -29,6 +29,8 @@
 #include "device_math.hpp"
 #include "kernels.hpp"
 #include "device_common.hpp"
+#include "si_common.hpp"
+#include "si_tile.hpp"
 #include "../../include/ugkwp.h"
 
 namespace ugk {
@@ -82,55 +84,6 @@ __device__ inline Geo geo_of(const Inst& I)
 // particle's own nu interval, evaluated at every cell entry.
 enum { SIG_NU3 = 0, SIG_POW = 1, SIG_GROUP = 2, SIG_STIM = 3, SIG_TAB = 4 };
 
-// Stimulated-emission factor 1 - e^{-nu/T} (Sec. 3.3's opacity), or 1 without it.
-__device__ inline double stim_factor(const Consts& K, double nu, double T)
-{
-    return K.stim ? -expm1(-nu / T) : 1.0;
-}
-
-// Frequency factor of group g at temperature T: Simpson's mean of nu^-p over
-// the group, times the stimulated-emission factor when that is on.
-__device__ inline double group_factor(const Dev& D, const Consts& K, int edge_off, int g, double T)
-{
-    if (!K.stim) return D.simpson[edge_off + g];
-    const double nl = D.nu[edge_off + g], nh = D.nu[edge_off + g + 1], nm = 0.5 * (nl + nh);
-    return (nu_pow(nl, K.nu_power) * stim_factor(K, nl, T) + 4.0 * nu_pow(nm, K.nu_power) * stim_factor(K, nm, T)
-            + nu_pow(nh, K.nu_power) * stim_factor(K, nh, T)) * (1.0 / 6.0);
-}
-
-// Group opacity of material m at T from the table (Sec. 3.4-3.5's printed
-// opacities, tabulated by the caller): sigma is bilinear in (ln nu, ln T) on
-// ln sigma, constant beyond the end nodes, and the group value is Simpson's rule
-// over the group (edge index e = edge_off + g).  The nu intervals and weights of the group's
-// three Simpson points are fixed by the edges and read from tab_gi / tab_ga
-// (k_tab_groups at set-up); only T is located here.
-__device__ inline double table_group_sigma(const Dev& D, const Consts& K, int m, int e, double T)
-{
-    double b;
-    const int jt = table_locate_guess(D.tab_lT, K.tab_nT, log(T), K.tab_lT_inv, &b);
-    const int n = K.tab_nnu;
-    const double* L0 = D.tab_lsig + ((int64_t)m * K.tab_nT + jt) * n;
-    double v[3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        const int i = D.tab_gi[3 * e + p];
-        const double a = D.tab_ga[3 * e + p];
-        const double* L = L0 + i;
-        const double lo = (1.0 - a) * L[0] + a * L[1], hi = (1.0 - a) * L[n] + a * L[n + 1];
-        v[p] = exp((1.0 - b) * lo + b * hi);
-    }
-    return (v[0] + 4.0 * v[1] + v[2]) * (1.0 / 6.0);
-}
-
-// T^-q; the paper's q = 1/2 without pow().
-__device__ inline double temp_pow(double T, double q) { return q == 0.5 ? 1.0 / sqrt(T) : pow(T, -q); }
-
-// The volumetric source acts in the steps that start before its switch-off time.
-__device__ inline bool source_on(const Consts& K, uint32_t step)
-{
-    return K.has_src && (double)step * K.dt < K.q_toff;
-}
-
 // The flight scale of a particle, tau = eps^2 / (c sigma), with sigma = kappa
 // nu^-p (Remark 2; Simpson's group factor S_g instead of nu^-p with
 // UGKWP_FLAG_GROUP_SIGMA), is evaluated as the particle's factor eps^2 nu^p
@@ -148,8 +101,8 @@ __device__ inline double tau_factor(const Dev& D, const Consts& K, const Geo& I,
 __device__ inline double phi_group_direct(double T, double nl, double nh, double a, double c)
 {
     const double xl = nl / T, xh = nh / T;
-    const double band = planck_band_from_edges(xl, planck_edge_value(xl), xh,
-                                               planck_edge_value(xh));
+    const TabPtr t = math_tab();
+    const double band = planck_band_from_edges(xl, planck_edge_value(t, xl), xh, planck_edge_value(t, xh));
     return phi_from_band(a, c, T, band);
 }
 
@@ -190,9 +143,10 @@ __global__ void k_tables(Dev D, Consts K)
     const double sv = s_of_sigma(K, sg);
     D.sig[j] = sg;
     D.sv[j] = sv;
-    D.es[j] = exp(-sv);
-    D.c4[j] = coef_c4(sv);
-    D.wc[j] = coef_w(sv);
+    const TabPtr t = math_tab();
+    D.es[j] = exp_neg(t, sv);
+    D.c4[j] = coef_c4(t, sv);
+    D.wc[j] = coef_w(t, sv);
 }
 
 // The push's rows of a tabulated opacity: for every cell and nu node, ln sigma of
@@ -235,13 +189,6 @@ __global__ void k_tab_logs(double* v, int64_t n)
     if (j < n) v[j] = log(v[j]);
 }
 
-// D of a face with face opacity sf (Appendix B, Eq. C2Formula); fc is the axis'
-// factor -(c/eps)^2 dt / (3 h), h the centre distance (Inst::fcx, fcy).
-__device__ inline double face_coef(const Consts& K, double sf, double fc)
-{
-    return fc * coef_c2_over_dt(s_of_sigma(K, sf));
-}
-
 // One instance, one axis: faces (nx+1)*ny (axis 0) or nx*(ny+1) (axis 1), Gp groups each.
 __global__ void k_face_D(Dev D, Consts K, int inst, int axis)
 {
@@ -274,7 +221,7 @@ __global__ void k_face_D(Dev D, Consts K, int inst, int axis)
     } else {
         sf = D.sig[I.cg_off + ((int64_t)(cl >= 0 ? cl : cr) << I.lgGp) + g];
     }
-    Dout[j] = face_coef(K, sf, fc);
+    Dout[j] = face_coef(K, math_tab(), sf, fc);
 }
 
 // Planckian ghost values phi_g(T_b) per instance and side.
@@ -786,12 +733,6 @@ __global__ void k_sample(Dev D, Consts K, Pool P)
 // scaled so that the linear profile stays non-negative over the cell
 // (|s_x| dx + |s_y| dy <= 2 rho^h); zero where rho^h <= 0.  rho^h of a slot is
 // src[j], minus rhop[j] when sub_rhop (the iterate's wave part, Algorithm 2).
-__device__ inline double minmod_diff(double a, double b)
-{
-    if (!(a * b > 0.0)) return 0.0;
-    return fabs(a) < fabs(b) ? a : b;
-}
-
 template <int DIM>
 __global__ void k_slopes(Dev D, Consts K, const double* src, int sub_rhop)
 {
@@ -850,6 +791,7 @@ __global__ void k_slopes(Dev D, Consts K, const double* src, int sub_rhop)
 
 constexpr int PUSH_THREADS = 256;
 constexpr int PUSH_PPT_DEFAULT = 4;
+constexpr uint32_t PUSH_FILL = 512;      // chunks a small pool is cut into: two per CU
 constexpr int HT_BITS = 10;
 constexpr int HT_SIZE = 1 << HT_BITS;
 constexpr uint32_t HT_EMPTY = 0xFFFFFFFFu;
@@ -1180,7 +1122,11 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
     if (D.counters[CNT_ERR] & ERR_POOL) return;
     const int64_t n_slots = (int64_t)D.counters[CNT_SLOTS];
     const int64_t n_total = (int64_t)D.counters[CNT_PUSHED];
-    const int64_t chunk = (int64_t)BS * ppt;
+    // ppt particles per thread and chunk, fewer in a pool too small to give every CU a
+    // chunk: a pool of 4e4 particles ran on 38 blocks, each thread four flights deep
+    const int fill = (int)(((uint32_t)n_total + PUSH_FILL * BS - 1) / (PUSH_FILL * BS));
+    const int nloop = max(1, min(ppt, fill));
+    const int64_t chunk = (int64_t)BS * nloop;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
     unsigned long long nsurv = 0;
     Geo geo0{};
@@ -1198,13 +1144,14 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
         __syncthreads();
         // 2-D: the records of the next round are read while this round's flights
         // run (1-D: the registers this takes would cost a wavefront per SIMD)
+        const int64_t cend = min(c0 + chunk, n_total);
         PoolRec<DIM> nxt;
         if (PUSH_PREFETCH) {
             const int64_t i0 = c0 + threadIdx.x;
-            if (i0 < n_total) nxt.load(In, (uint32_t)i0);
+            if (i0 < cend) nxt.load(In, (uint32_t)i0);
         }
 #pragma unroll 1
-        for (int r = 0; r < ppt; ++r) {
+        for (int r = 0; r < nloop; ++r) {
             const int64_t i = c0 + (int64_t)r * BS + threadIdx.x;
             const uint32_t iu = (uint32_t)i;
             // the outcome tally of this lane's particle (survival or deposition)
@@ -1214,14 +1161,14 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
             PoolRec<DIM> cur;
             if (PUSH_PREFETCH) {
                 cur = nxt;
-                if (r + 1 < ppt && i + BS < n_total) nxt.load(In, iu + BS);
-            } else if (i < n_total) {
+                if (r + 1 < nloop && i + BS < cend) nxt.load(In, iu + BS);
+            } else if (i < cend) {
                 cur.word = ldnt(In.cell, iu);      // the rest only for a live slot
             }
             const int32_t word = cur.word;
             const int cell = word & CELL_MASK;
-            if (i >= n_total) {
-                // past the end of the pool: nothing
+            if (i >= cend) {
+                // past the end of the chunk or the pool: nothing
             } else if (word < 0) {                 // empty slot stays empty
                 stnt(Out.cell, iu, DEAD);
             } else if (cell >= K.ncell) {
@@ -1458,167 +1405,11 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(Dev D, Consts K, 
 // ---------------------------------------------------------------------------
 // A4: wave free-transport flux and the static source Q
 
-// The faces of a slot's cell in the order XLO, XHI, YLO, YHI (the first two in
-// 1-D): whether the neighbour across lies in the instance, its slot, the face's
-// tally slot and area.  Index arithmetic only, so that a kernel can issue every
-// load of the stencil before it waits for the first.
-struct CellFaces {
-    bool inside[4];
-    int64_t nbj[4], fslot[4];
-    double S[4];
-};
-
-template <int DIM>
-__device__ inline CellFaces cell_faces(const Inst& I, int64_t j, int ix, int iy, int g)
-{
-    CellFaces F;
-    const int Gp = I.Gp, nx = I.nx;
-#pragma unroll
-    for (int q = 0; q < 2 * DIM; ++q) {
-        const bool lo = (q & 1) == 0;
-        if (q < 2) {
-            F.inside[q] = lo ? ix > 0 : ix < nx - 1;
-            F.nbj[q] = j + (lo ? -Gp : Gp);
-            F.fslot[q] = I.fx_off + (((int64_t)iy * (nx + 1) + ix + (lo ? 0 : 1)) << I.lgGp) + g;
-            F.S[q] = I.dy;
-        } else {
-            F.inside[q] = lo ? iy > 0 : iy < I.ny - 1;
-            F.nbj[q] = j + (lo ? -(int64_t)nx * Gp : (int64_t)nx * Gp);
-            F.fslot[q] = I.fy_off + (((int64_t)(iy + (lo ? 0 : 1)) * nx + ix) << I.lgGp) + g;
-            F.S[q] = I.dx;
-        }
-    }
-    return F;
-}
-
-// Wave flux through the faces of slot j and its static source Q (Remark 3:
-// coefficient C4 - e^{-s} where the cell sampled particles, C4 where it did
-// not).  *inflow gets the energy the wave flux brings in through the domain
-// boundary.
-// EXT: compiled with the slope terms and the boundary-source ghosts (which the
-// flags then switch); without it the base flux only, at fewer registers.
-template <int DIM, bool EXT>
-__device__ inline double wave_source(const Dev& D, const Consts& K, const Inst& I, int64_t j, const Slot& s,
-                                     const CellFaces& F, double* inflow_out, const double* src, bool sub_rhop)
-{
-    const int g = s.g, nx = I.nx;
-    const int ix = DIM == 1 ? s.lcell : s.lcell % nx, iy = DIM == 1 ? 0 : s.lcell / nx;
-    const double cq = K.cq;
-    const double* phib = D.phib + (int64_t)s.inst * 4 * MAX_G;
-    constexpr int nf = 2 * DIM;
-    const bool slopes = EXT && (K.flags & UGKWP_FLAG_SLOPES) != 0;
-    const bool bpart = EXT && (K.flags & UGKWP_FLAG_BOUNDARY_PARTICLES) != 0;
-    // every load first
-    // the wave coefficient of a sampled slot: W(s), or this step's joint-cell value
-    const double* wsamp = K.tau_C > 0.0 ? D.wsn : D.wc;
-    const int nb_here = D.nbi[j];
-    const double wc_here = wsamp[j], c4_here = D.c4[j], rho_here = D.rho[j];
-    const double rhoh_here = sub_rhop ? src[j] - D.rhop[j] : src[j];
-    double sl_here[2] = {0.0, 0.0}, b_here = 0.0, es_here = 0.0, wphys_here = 0.0;
-    if (slopes) {
-        sl_here[0] = D.sx[j];
-        if (DIM == 2) sl_here[1] = D.sy[j];
-        b_here = D.bcoef[j];
-    }
-    if (bpart) {
-        es_here = D.es[j];
-        wphys_here = D.wc[j];
-    }
-    int nb_n[4];
-    double wc_n[4], c4_n[4], rhoh_n[4], pb[4], sl_n[4], b_n[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        nb_n[q] = 0;
-        wc_n[q] = c4_n[q] = rhoh_n[q] = pb[q] = sl_n[q] = b_n[q] = 0.0;
-        if (q >= nf) continue;
-        if (F.inside[q]) {
-            const int64_t n = F.nbj[q];
-            nb_n[q] = D.nbi[n];
-            wc_n[q] = wsamp[n];
-            c4_n[q] = D.c4[n];
-            rhoh_n[q] = sub_rhop ? src[n] - D.rhop[n] : src[n];
-            if (slopes) {
-                sl_n[q] = q < 2 ? D.sx[n] : D.sy[n];
-                b_n[q] = D.bcoef[n];
-            }
-        } else if (I.bc[q] == BC_PLANCK) {
-            pb[q] = phib[q * MAX_G + g];
-        }
-    }
-    // gross particle crossings into / out of the cell
-    const int64_t fl = I.fx_off + (((int64_t)iy * (nx + 1) + ix) << I.lgGp) + g;
-    const int64_t fr = fl + I.Gp;
-    const double tx0 = D.ftx[fl * 2 + 0], tx1 = D.ftx[fr * 2 + 1], tx2 = D.ftx[fl * 2 + 1], tx3 = D.ftx[fr * 2 + 0];
-    double ty0 = 0.0, ty1 = 0.0, ty2 = 0.0, ty3 = 0.0;
-    if (DIM == 2) {
-        const int64_t fb = I.fy_off + (((int64_t)iy * nx + ix) << I.lgGp) + g;
-        const int64_t ft = fb + ((int64_t)nx << I.lgGp);
-        ty0 = D.fty[fb * 2 + 0]; ty1 = D.fty[ft * 2 + 1];
-        ty2 = D.fty[fb * 2 + 1]; ty3 = D.fty[ft * 2 + 0];
-    }
-    const double Ah = nb_here > 0 ? wc_here : c4_here;
-    const double here = Ah * rhoh_here;
-    const double cs = K.c * K.c * K.dt / (6.0 * K.eps * K.eps);
-    double fsum = 0.0, inflow = 0.0;
-    // flux through a face along +axis: cq (A_low rho^h_low - A_high rho^h_high), with
-    // slopes the upwind profiles at the face and cs (B_low s_low + B_high s_high)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (q >= nf) continue;
-        const bool lo = (q & 1) == 0;
-        double Fpos;
-        double there;
-        if (!F.inside[q]) {
-            const int bc = I.bc[q];
-            if (bc == BC_REFLECT) continue;
-            // a Planckian ghost that emitted boundary-source particles keeps C4 - e^{-s}
-            double Ag = c4_here;
-            if (bpart && bc == BC_PLANCK) {
-                const double eov = es_here * pb[q];
-                if (eov * I.V > 0.0 && K.n_cap >= 1 && eov / I.w_ref >= 1.0) Ag = wphys_here;
-            }
-            there = bc == BC_PLANCK ? Ag * pb[q] : 0.0;
-        }
-        if (!slopes) {
-            if (F.inside[q]) {
-                const double An = nb_n[q] > 0 ? wc_n[q] : c4_n[q];
-                there = An * rhoh_n[q];
-            }
-            Fpos = lo ? cq * (there - here) : cq * (here - there);
-        } else {
-            const double slh = sl_here[q >> 1], h = q < 2 ? I.dx : I.dy;
-            // this cell is the high cell of a LO face and the low cell of a HI face
-            const double hv = Ah * (rhoh_here + (lo ? -0.5 : 0.5) * h * slh);
-            const double hs = b_here * slh;
-            double ts = 0.0;
-            if (F.inside[q]) {
-                const double An = nb_n[q] > 0 ? wc_n[q] : c4_n[q];
-                there = An * (rhoh_n[q] + (lo ? 0.5 : -0.5) * h * sl_n[q]);
-                ts = b_n[q] * sl_n[q];
-            }
-            Fpos = lo ? cq * (there - hv) + cs * (ts + hs) : cq * (hv - there) + cs * (hs + ts);
-        }
-        const double Fin = lo ? Fpos : -Fpos;
-        fsum += F.S[q] * Fin;
-        if (!F.inside[q]) inflow += K.dt * F.S[q] * Fin / K.c;
-    }
-    double a_in = tx0 + tx1;
-    double a_out = tx2 + tx3;
-    if (DIM == 2) {
-        a_in += ty0 + ty1;
-        a_out += ty2 + ty3;
-    }
-    *inflow_out = inflow;
-    const double Q = rho_here + I.dt_V * fsum + (a_in - a_out) / I.V;
-    // a volumetric source adds dt q in the steps it is on
-    return source_on(K, *D.step) ? Q + K.dt * D.qsrc[j] : Q;
-}
-
 // Q of sweep k >= 1 with UGKWP_FLAG_WAVE_ITER: the wave flux from the iterate
 // rho^k (src) less rho^p (Algorithm 2), and the boundary wave inflow of the
 // sweep into winflow[k & 1] (the commit takes that of the last sweep).
-// Instances whose iteration has converged are left alone.
-template <int DIM>
+// Instances whose iteration has converged are left alone.  (2-D; the 1-D sweeps form it
+// themselves: si_tile.hip.)
 __global__ __launch_bounds__(256) void k_wave_q(Dev D, Consts K, int k, const double* src)
 {
     if (!gate_open(D, K, 0)) return;
@@ -1629,10 +1420,10 @@ __global__ __launch_bounds__(256) void k_wave_q(Dev D, Consts K, int k, const do
     if (D.ist[s.inst].conv_sweeps != 0) return;
     const Inst& I = D.inst[s.inst];
     const int nx = I.nx;
-    const int ix = DIM == 1 ? s.lcell : s.lcell % nx, iy = DIM == 1 ? 0 : s.lcell / nx;
-    const CellFaces F = cell_faces<DIM>(I, j, ix, iy, s.g);
+    const int ix = s.lcell % nx, iy = s.lcell / nx;
+    const CellFaces F = cell_faces<2>(I, j, ix, iy, s.g);
     double inflow = 0.0;
-    D.Q[j] = wave_source<DIM, true>(D, K, I, j, s, F, &inflow, src, true);
+    D.Q[j] = wave_source<2, true>(D, K, I, j, s, F, &inflow, src, true);
     D.winflow[(int64_t)(k & 1) * K.n_cg + j] = inflow;
 }
 
@@ -1680,16 +1471,17 @@ __device__ inline bool si_converged(const Dev& D, const Consts& K, int inst, int
 // decide launch sits between sweeps; block 0 records it.
 // FIRST: sweep 0 (its own instantiation, so that the wave-flux code does not
 // weigh on the registers of the later sweeps); SINGLE: a context of one
-// instance; DIM: the dimension of every instance of the context.
+// instance.  (1-D contexts take several sweeps per launch: si_tile.hip.)
 // LIN: the linearized iteration. A sweep takes the new temperature's emission
 // as phi^k + phi'(T^k) (T^{k+1} - T^k) and solves each cell's energy balance
 // for T^{k+1}, a local Newton step with the literal iteration's fixed point
 // (Eq. macroSysFinal) that also converges under stiff material coupling.
-template <bool FIRST, bool SINGLE, int DIM, bool TDEP, bool LIN, bool EXT>
+template <bool FIRST, bool SINGLE, bool TDEP, bool LIN, bool EXT>
 __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k, const double* phi_in,
                                                           double* phi_out, int decide_prev, const double* rho_in,
                                                           double* rho_out)
 {
+    constexpr int DIM = 2;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
     const int64_t j = (int64_t)blockIdx.x * SI_THREADS + threadIdx.x;
     // The gate (step count), for batches the flags of the block's wavefronts
@@ -1820,13 +1612,14 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     const bool run = wave_on && cs_inst == 0 && j < K.n_cg;
     double dr = 0.0, mr = 0.0, dT = 0.0, mT = 0.0;
     const bool work = run && s.cell_ok;
+    const TabPtr mt = math_tab();
     // linearized iteration: d phi_g / dT at T^k, its upper-edge term from lane g+1
     double dph = 0.0;
     if (LIN) {
         const bool edge_lane = work && g <= G;
-        const double we = edge_lane ? planck_edge_weight(nu_lo / Tk) : 0.0;
-        double wh = __shfl_down(we, 1, Gp < 2 ? 2 : Gp);
-        if (work && g == G - 1 && G == Gp) wh = planck_edge_weight(nu_top / Tk);
+        const double we = edge_lane ? planck_edge_weight(mt, nu_lo / Tk) : 0.0;
+        double wh = next_lane(we);
+        if (work && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / Tk);
         if (work && s.active) dph = 4.0 * phi / Tk + K.a * K.c * (Tk * Tk * Tk) * (we - wh) * UGK_15_PI4;
     }
     double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0, rl = 1.0;    // rl = 1 / (1 + lambda)
@@ -1845,7 +1638,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
                     const double sn = K.table ? tsig_n[q] : kap_n[q] * temp_pow(T_nb[q], K.t_power) * Sn[q];
                     sf = (sk + sn > 0.0) ? 2.0 * (sk * sn) / (sk + sn) : 0.0;
                 }
-                Df[q] = face_coef(K, sf, q < 2 ? I.fcx : I.fcy);
+                Df[q] = face_coef(K, mt, sf, q < 2 ? I.fcx : I.fcy);
             }
         }
         double lap = 0.0;
@@ -1916,12 +1709,12 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     {
         const bool edge_lane = work && g <= G;
         const double xe = edge_lane ? nu_lo / Tnew : 0.0;
-        const double ve = edge_lane ? planck_edge_value(xe) : 0.0;
-        double xh = __shfl_down(xe, 1, Gp < 2 ? 2 : Gp);
-        double vh = __shfl_down(ve, 1, Gp < 2 ? 2 : Gp);
+        const double ve = edge_lane ? planck_edge_value(mt, xe) : 0.0;
+        double xh = next_lane(xe);
+        double vh = next_lane(ve);
         if (work && g == G - 1 && (G == Gp)) {
             xh = nu_top / Tnew;
-            vh = planck_edge_value(xh);
+            vh = planck_edge_value(mt, xh);
         }
         if (work && s.active) phi_new = phi_from_band(K.a, K.c, Tnew, planck_band_from_edges(xe, ve, xh, vh));
     }
@@ -2026,27 +1819,27 @@ constexpr int DIAG_THREADS = 256;
 // last_sweep >= 0 (single instance): the convergence decision of that sweep
 // is taken here rather than by a decide launch; wavefront 0 of every block
 // takes it from the same residual sub-slots, and block 0 records it.
-// Occupancy floor of the commit, whose loads are all issued before its first
-// wait: 8 wavefronts per SIMD for batches (at 64 VGPRs, with some spilling: 3%
-// off a step of 512 slabs), 6 in 2-D; single 1-D instances, whose commits are
-// small and latency bound, are left to the compiler.
-template <bool SINGLE, int DIM>
-constexpr int finish_min_waves() { return DIM == 2 ? 6 : (SINGLE ? 1 : 8); }
-
-template <bool SINGLE, int DIM>
-__global__ __launch_bounds__(DIAG_THREADS) __attribute__((amdgpu_waves_per_eu(finish_min_waves<SINGLE, DIM>())))
+// TDEP: a temperature-dependent opacity or Olson's heat capacity (kept apart for their
+// registers).
+template <bool SINGLE, int DIM, bool TDEP>
+__global__ __launch_bounds__(DIAG_THREADS)
 void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
 {
     const int64_t j = (int64_t)blockIdx.x * DIAG_THREADS + threadIdx.x;
     // the loads come first (nothing is stored before the gate): step count,
     // the stopping state of the last sweep (one instance), the slot's data
-    const uint32_t now = *D.step;
+    warm_args<sizeof(Dev) + sizeof(Consts)>();
+    const int z = lane_zero();
+    const uint32_t now = D.step[z];
     Inst I;
     const Slot s = decode_slot_rec<SINGLE>(D, K, j, I);
-    const int cs0 = last_sweep >= 0 ? D.ist[0].conv_sweeps : 0;
+    constexpr bool tiled = DIM == 1;            // the iteration in tiles (si_tile.hpp)
+    const int cs0 = last_sweep >= 0 ? D.ist[z].conv_sweeps : 0;
+    const int prev_sweeps = tiled ? D.prev_ist[s.inst + z].conv_sweeps : 0;
     Resid rl = {0ull, 0ull, 0ull, 0ull};
-    if (last_sweep >= 0 && threadIdx.x < WAVE) rl = res_slot(D, K, 0, last_sweep)[threadIdx.x];
-    const int cs_inst = D.ist[s.inst].conv_sweeps;
+    if (!tiled && last_sweep >= 0 && threadIdx.x < WAVE) rl = res_slot(D, K, 0, last_sweep)[threadIdx.x];
+    const int cs_inst = D.ist[s.inst + z].conv_sweeps;
+    const unsigned long long err0 = last_sweep >= 0 ? D.counters[CNT_ERR + z] : 0ull;   // raised by the launches before
     const bool in = j < K.n_cg;
     const int g = s.g, nx = I.nx;
     const int ix = DIM == 1 ? s.lcell : s.lcell % nx, iy = DIM == 1 ? 0 : s.lcell / nx;
@@ -2056,20 +1849,19 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     int src = 0;
     uint8_t pin = 0;
     bool bnd[4] = {false, false, false, false};
-    int64_t fs[4] = {0, 0, 0, 0};
     double Df[4] = {0.0, 0.0, 0.0, 0.0}, tal[4] = {0.0, 0.0, 0.0, 0.0}, pb[4] = {0.0, 0.0, 0.0, 0.0};
     double tal_in[4] = {0.0, 0.0, 0.0, 0.0};
     const bool witer = (K.flags & UGKWP_FLAG_WAVE_ITER) != 0;
     if (in && s.active) {
         surv = D.surv[j];
         rho = D.rho[j];
-        if (!witer) rho_new = D.rho_new[j];
+        if (tiled || !witer) rho_new = D.rho_new[j];
         pin = D.pinned[cell];
         if (g == 0) {
             cv = D.cvol[cell];
             T0 = D.T[cell];
             T1 = D.T_new[cell];
-            if (K.olson) {
+            if (TDEP && K.olson) {
                 olH = D.olH[cell];
                 olchi = D.olchi[cell];
                 if (olH > 0.0) uend = D.uend[cell];
@@ -2079,21 +1871,34 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
             src = *D.src_on;
             qs = D.qsrc[j];
         }
+#pragma unroll
+        for (int q = 0; q < 2 * DIM; ++q) {
+            const bool lo = (q & 1) == 0;
+            bnd[q] = q < 2 ? (lo ? ix == 0 : ix == nx - 1) : (lo ? iy == 0 : iy == I.ny - 1);
+        }
+    }
+    // a boundary slot's faces: with the other loads for a single 1-D instance, whose
+    // commit is as long as its longest wavefront; else where they are used (the few
+    // boundary wavefronts wait once more, and the others keep fewer registers)
+    auto load_faces = [&]() {
         const double* phib = D.phib + (int64_t)s.inst * 4 * MAX_G;
 #pragma unroll
         for (int q = 0; q < 2 * DIM; ++q) {
-            const int axis = q >> 1;
-            const bool lo = (q & 1) == 0;
-            bnd[q] = axis == 0 ? (lo ? ix == 0 : ix == nx - 1) : (lo ? iy == 0 : iy == I.ny - 1);
             if (!bnd[q]) continue;
-            fs[q] = axis == 0 ? I.fx_off + (((int64_t)iy * (nx + 1) + ix + (lo ? 0 : 1)) << I.lgGp) + g
-                              : I.fy_off + (((int64_t)(iy + (lo ? 0 : 1)) * nx + ix) << I.lgGp) + g;
-            Df[q] = axis == 0 ? D.Dx[fs[q]] : D.Dy[fs[q]];
-            tal[q] = (axis == 0 ? D.ftx : D.fty)[fs[q] * 2 + (lo ? 1 : 0)];
-            tal_in[q] = (axis == 0 ? D.ftx : D.fty)[fs[q] * 2 + (lo ? 0 : 1)];
+            const bool lo = (q & 1) == 0;
+            const int64_t fs = q < 2 ? I.fx_off + (((int64_t)iy * (nx + 1) + ix + (lo ? 0 : 1)) << I.lgGp) + g
+                                     : I.fy_off + (((int64_t)(iy + (lo ? 0 : 1)) * nx + ix) << I.lgGp) + g;
+            Df[q] = q < 2 ? D.Dx[fs] : D.Dy[fs];
+            tal[q] = (q < 2 ? D.ftx : D.fty)[fs * 2 + (lo ? 1 : 0)];
+            tal_in[q] = (q < 2 ? D.ftx : D.fty)[fs * 2 + (lo ? 0 : 1)];
             if (I.bc[q] == BC_PLANCK) pb[q] = phib[q * MAX_G + g];
         }
-    }
+    };
+    constexpr bool faces_early = SINGLE && DIM == 1;
+    if (faces_early) load_faces();
+    __shared__ int dec[TILE_S_MAX + 1];
+    if (tiled && SINGLE) tile_gather(D, K, last_sweep, dec);
+    const int s0 = tiled ? __builtin_amdgcn_readfirstlane(tile_first(K, prev_sweeps)) : 0;
     // the commit below advances *D.step while other blocks may still start:
     // both the step's own value and the next one open this launch
     if (!(K.gate == GATE_OFF || now == K.gate || now == K.gate + 1)) return;
@@ -2102,8 +1907,9 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     // per instance
     const int ns_guess = last_sweep >= 0 ? (cs0 != 0 ? cs0 : last_sweep + 1) : cs_inst;
     double winf = 0.0;
-    if (in && s.active && ns_guess >= 1) {
-        phi = sweep_in(D, ns_guess - 1)[j];          // phi^k of the last sweep
+    if (!tiled && in && s.active && ns_guess >= 1) {
+        // phi^k of the last sweep, which matters on the boundary and in pinned cells only
+        if (pin || bnd[0] || bnd[1] || bnd[2] || bnd[3]) phi = sweep_in(D, ns_guess - 1)[j];
         phi_next = sweep_out(D, ns_guess - 1)[j];    // phi(T^{n+1}): the next step's phi^0
         if (witer) {
             // the last sweep's output and the boundary wave inflow of its wave flux
@@ -2112,7 +1918,12 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
         }
     }
     int ns_single = 0;
-    if (last_sweep >= 0) {
+    if (tiled && SINGLE) {
+        __syncthreads();
+        ns_single = tile_outcome(K, last_sweep, s0, dec);
+        if (blockIdx.x == 0 && threadIdx.x == 0 && ns_single != 0 && dec[TILE_S_MAX] == 0) tile_record(D, 0, ns_single);
+        if (err0 != 0 || ns_single <= 0) return;
+    } else if (!tiled && last_sweep >= 0) {
         __shared__ int sh_ns;
         if (threadIdx.x < WAVE) {
             // a block starting after block 0's record reads that record: the same value
@@ -2130,7 +1941,7 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
             D.ist[0].conv_sweeps = ns_single;
             atomicAdd((unsigned long long*)(D.counters + CNT_CONV), 1ull);
         }
-        if (D.counters[CNT_ERR] != 0 || ns_single == 0) return;
+        if (err0 != 0 || ns_single == 0) return;
     } else if (!step_committed(D, K)) {
         return;
     }
@@ -2163,57 +1974,100 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
             D.counters[CNT_DONE] = n1;
         }
     }
-    // the commit's rho^{n+1} lives in rho_new
-    if (witer && in && s.active && !(ns_guess & 1)) D.rho_new[j] = rho_new;
-    double v[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};   // inflow_eq, exit/c, injection, e0, e1,
-                                                         // inflow_wave (WAVE_ITER), inflow_particles
-    if (in && s.active && (K.t_power != 0.0 || K.stim || K.table) && (bnd[0] || bnd[1] || bnd[2] || bnd[3])) {
-        // temperature-dependent opacity: the boundary faces' coefficients at the
-        // step's final temperature (the iteration has converged on it)
-        const double Tf = D.T_new[cell];
-        const double sk = K.table ? table_group_sigma(D, K, D.tab_mat[cell], I.edge_off + g, Tf)
-                                  : D.kappa[j] * temp_pow(Tf, K.t_power) * group_factor(D, K, I.edge_off, g, Tf);
-#pragma unroll
-        for (int q = 0; q < 2 * DIM; ++q)
-            if (bnd[q]) Df[q] = face_coef(K, sk, (q >> 1) == 0 ? I.fcx : I.fcy);
+    const int ns_tiled = SINGLE ? ns_single : cs_inst;
+    double Tf = 0.0;           // the step's final temperature, in the boundary cells
+    if (tiled && in && s.active && ns_tiled >= 1) {
+        // the iterate lies in place unless the step took another number of sweeps
+        // than its first round; the last sweep's input matters on the boundary and
+        // in pinned cells only
+        const TileOut o = tile_out(K, s0, ns_tiled - 1);
+        if (pin || bnd[0] || bnd[1]) {
+            const TileOut q = tile_out(K, s0, ns_tiled - 2);
+            phi = (ns_tiled == 1 ? D.phi0 : (q.final ? D.phi0n : D.tile_phi + (int64_t)q.at * K.n_cg))[j];
+            Tf = (o.final ? D.T_new : D.tile_T + (int64_t)o.at * K.ncell)[cell];
+            if (witer && (bnd[0] || bnd[1]))
+                winf = tile_inflow(D, K, s.inst, o.final ? 2 * K.tile_cap : o.at)[(bnd[0] ? 0 : MAX_G) + g];
+        }
+        if (!o.final) {
+            const int64_t at = (int64_t)o.at * K.n_cg + j, ac = (int64_t)o.at * K.ncell + cell;
+            rho_new = D.tile_rho[at];
+            D.rho_new[j] = rho_new;
+            D.phi0n[j] = D.tile_phi[at];
+            if (witer) D.Q[j] = D.tile_Q[at];
+            if (g == 0) {
+                T1 = D.tile_T[ac];
+                D.T_new[cell] = T1;
+                if (TDEP && olH > 0.0) uend = D.tile_u[ac];
+            }
+        }
+    } else if (!tiled && in && s.active) {
+        D.phi0n[j] = phi_next;
+        Tf = D.T_new[cell];
     }
-    if (in && s.active) {
-        D.phi0[j] = phi_next;
+    // the commit's rho^{n+1} lives in rho_new
+    if (!tiled && witer && in && s.active && !(ns_guess & 1)) D.rho_new[j] = rho_new;
+    const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
+    double* const dg = D.diag_sub + ((int64_t)s.inst * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8;
+    // the boundary's, the pinned cells' and the source's share of the balance: few
+    // wavefronts have any, and those add theirs by themselves
+    const bool at_wall = bnd[0] || bnd[1] || bnd[2] || bnd[3];
+    if (__ballot(at_wall || pin || src) != 0ull) {
+        if (!faces_early) load_faces();
+        if (TDEP && at_wall && (K.t_power != 0.0 || K.stim || K.table)) {
+            // temperature-dependent opacity: the boundary faces' coefficients at the
+            // step's final temperature (the iteration has converged on it)
+            const TabPtr mt = math_tab();
+            const double sk = K.table ? table_group_sigma(D, K, D.tab_mat[cell], I.edge_off + g, Tf)
+                                      : D.kappa[j] * temp_pow(Tf, K.t_power) * group_factor(D, K, I.edge_off, g, Tf);
+#pragma unroll
+            for (int q = 0; q < 2 * DIM; ++q)
+                if (bnd[q]) Df[q] = face_coef(K, mt, sk, (q >> 1) == 0 ? I.fcx : I.fcy);
+        }
+        // inflow_wave (WAVE_ITER), inflow_eq, exit, injection, inflow_particles
+        constexpr int NB = 5;
+        const int dst[NB] = {0, 1, 2, 3, 6};
+        double v[NB] = {winf, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q < 2 * DIM; ++q) {
             if (!bnd[q]) continue;
             const double S = (q >> 1) == 0 ? I.dy : I.dx;
             const int bc = I.bc[q];
             const double pn = bc == BC_PLANCK ? pb[q] : (bc == BC_REFLECT ? phi : 0.0);
-            v[0] += K.dt * S * Df[q] * (pn - phi) / K.c;
-            v[1] += tal[q] / K.c;
-            v[6] += tal_in[q] / K.c;
+            v[1] += K.dt * S * Df[q] * (pn - phi) / K.c;
+            v[2] += tal[q] / K.c;
+            v[4] += tal_in[q] / K.c;
         }
-        v[5] = winf;
-        if (pin) v[2] = I.V * (K.dt * D.sig[j] / (K.eps * K.eps)) * (phi - rho_new);
-        if (src) v[2] += I.V * K.dt * qs / K.c;
-        v[3] = I.V * rho / K.c;
-        v[4] = I.V * rho_new / K.c;
-        if (g == 0 && olH > 0.0) {
-            // Olson's material energy, and the one the last sweep gave
-            v[3] += I.V * olson_energy(olH, olchi, T0);
-            v[4] += I.V * uend;
-        } else if (g == 0) {
-            v[3] += I.V * cv * T0;
-            v[4] += I.V * cv * T1;
+        if (pin) v[3] = I.V * (K.dt * D.sig[j] / (K.eps * K.eps)) * (phi - rho_new);
+        if (src) v[3] += I.V * K.dt * qs / K.c;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            if (__ballot(v[q] != 0.0) == 0ull) continue;
+            const double t = wave_sum(v[q]);
+            if (lane == 0) atomicAdd(dg + dst[q], t);
         }
     }
-    // the diag entry of each sum: inflow_eq 1, exit 2, injection 3, e_start 4,
-    // e_end 5, inflow_wave 0, inflow_particles 6
-    constexpr int NV = 7;
-    const int dst[NV] = {1, 2, 3, 4, 5, 0, 6};
-#pragma unroll
-    for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
-    __shared__ double wsum[DIAG_THREADS / WAVE][NV];
+    // the energies before and after: per wavefront, then per run of the block's
+    // wavefronts of one instance (e_start 4, e_end 5)
+    double e0 = 0.0, e1 = 0.0;
+    if (in && s.active) {
+        e0 = I.V * rho / K.c;
+        e1 = I.V * rho_new / K.c;
+        if (TDEP && g == 0 && olH > 0.0) {
+            // Olson's material energy, and the one the last sweep gave
+            e0 += I.V * olson_energy(olH, olchi, T0);
+            e1 += I.V * uend;
+        } else if (g == 0) {
+            e0 += I.V * cv * T0;
+            e1 += I.V * cv * T1;
+        }
+    }
+    e0 = wave_sum(e0);
+    e1 = wave_sum(e1);
+    __shared__ double wsum[DIAG_THREADS / WAVE][2];
     __shared__ int winst[DIAG_THREADS / WAVE];
-    const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
     if (lane == 0) {
-        for (int q = 0; q < NV; ++q) wsum[wid][q] = v[q];
+        wsum[wid][0] = e0;
+        wsum[wid][1] = e1;
         winst[wid] = j < K.n_cg ? s.inst : -1;
     }
     __syncthreads();
@@ -2222,15 +2076,16 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
         int w0 = 0;
         while (w0 < nw) {
             int w1 = w0;
-            double acc[NV] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            double a0 = 0.0, a1 = 0.0;
             while (w1 < nw && winst[w1] == winst[w0]) {
-                for (int q = 0; q < NV; ++q) acc[q] += wsum[w1][q];
+                a0 += wsum[w1][0];
+                a1 += wsum[w1][1];
                 ++w1;
             }
             if (winst[w0] >= 0) {
-                double* dg = D.diag_sub + ((int64_t)winst[w0] * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8;
-                for (int q = 0; q < NV; ++q)
-                    if (acc[q] != 0.0) atomicAdd(dg + dst[q], acc[q]);
+                double* dq = D.diag_sub + ((int64_t)winst[w0] * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8;
+                atomicAdd(dq + 4, a0);
+                atomicAdd(dq + 5, a1);
             }
             w0 = w1;
         }
@@ -2262,9 +2117,10 @@ __global__ void k_eval_coef(int n, const double* s, double* c4, double* w, doubl
 {
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
-    c4[j] = coef_c4(s[j]);
-    w[j] = coef_w(s[j]);
-    c2[j] = coef_c2_over_dt(s[j]);
+    const TabPtr t = math_tab();
+    c4[j] = coef_c4(t, s[j]);
+    w[j] = coef_w(t, s[j]);
+    c2[j] = coef_c2_over_dt(t, s[j]);
 }
 
 __global__ void k_eval_uniform(int n, uint64_t seed, const uint64_t* id, uint32_t step, uint32_t purpose,
@@ -2542,13 +2398,10 @@ void launch_sort_scatter(int dim, const Dev& D, const Consts& K, const Pool& In,
 }
 
 template <bool TDEP, bool LIN, bool EXT>
-static auto sweep_kernel_ext(const Consts& K, bool fold, int k)
+static auto sweep_kernel_ext(bool fold, int k)
 {
-    return K.inst0.dim == 1
-               ? (fold ? (k == 0 ? k_si_sweep<true, true, 1, TDEP, LIN, EXT> : k_si_sweep<false, true, 1, TDEP, LIN, false>)
-                       : (k == 0 ? k_si_sweep<true, false, 1, TDEP, LIN, EXT> : k_si_sweep<false, false, 1, TDEP, LIN, false>))
-               : (fold ? (k == 0 ? k_si_sweep<true, true, 2, TDEP, LIN, EXT> : k_si_sweep<false, true, 2, TDEP, LIN, false>)
-                       : (k == 0 ? k_si_sweep<true, false, 2, TDEP, LIN, EXT> : k_si_sweep<false, false, 2, TDEP, LIN, false>));
+    return fold ? (k == 0 ? k_si_sweep<true, true, TDEP, LIN, EXT> : k_si_sweep<false, true, TDEP, LIN, false>)
+                : (k == 0 ? k_si_sweep<true, false, TDEP, LIN, EXT> : k_si_sweep<false, false, TDEP, LIN, false>);
 }
 
 // the first sweep evaluates the wave flux: with slope terms or boundary-source
@@ -2556,8 +2409,8 @@ static auto sweep_kernel_ext(const Consts& K, bool fold, int k)
 template <bool TDEP, bool LIN>
 static auto sweep_kernel(const Consts& K, bool fold, int k)
 {
-    return (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) ? sweep_kernel_ext<TDEP, LIN, true>(K, fold, k)
-                                                                           : sweep_kernel_ext<TDEP, LIN, false>(K, fold, k);
+    return (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) ? sweep_kernel_ext<TDEP, LIN, true>(fold, k)
+                                                                           : sweep_kernel_ext<TDEP, LIN, false>(fold, k);
 }
 
 // rho^m of the source iteration: rho^n for m = 0; from the wave flux of each
@@ -2575,13 +2428,11 @@ void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t
 {
     const bool fold = K.n_inst == 1;
     const bool witer = (K.flags & UGKWP_FLAG_WAVE_ITER) != 0;
-    const int dim = K.inst0.dim;
     for (int k = k0; k < k1; ++k) {
         if (witer && k > 0) {
             // the wave flux of this sweep from its iterate: slopes, then Q
-            if (K.flags & UGKWP_FLAG_SLOPES) launch_slopes(dim, D, K, sweep_rho(D, K, k), true, st);
-            if (dim == 1) k_wave_q<1><<<blocks(K.n_cg, 256), 256, 0, st>>>(D, K, k, sweep_rho(D, K, k));
-            else k_wave_q<2><<<blocks(K.n_cg, 256), 256, 0, st>>>(D, K, k, sweep_rho(D, K, k));
+            if (K.flags & UGKWP_FLAG_SLOPES) launch_slopes(2, D, K, sweep_rho(D, K, k), true, st);
+            k_wave_q<<<blocks(K.n_cg, 256), 256, 0, st>>>(D, K, k, sweep_rho(D, K, k));
         }
         // every instance of a context has the same dimension
         const bool lin = (K.flags & UGKWP_FLAG_SI_LINEARIZED) != 0;
@@ -2598,8 +2449,12 @@ void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t
 
 void launch_finish(const Dev& D, const Consts& K, bool reduce_diag, int last_sweep, int push_blocks, hipStream_t st)
 {
-    auto fin = K.inst0.dim == 1 ? (K.n_inst == 1 ? k_finish<true, 1> : k_finish<false, 1>)
-                                    : (K.n_inst == 1 ? k_finish<true, 2> : k_finish<false, 2>);
+    const bool tdep = K.t_power != 0.0 || K.stim || K.table || K.olson;
+    auto fin = K.inst0.dim == 1
+                   ? (K.n_inst == 1 ? (tdep ? k_finish<true, 1, true> : k_finish<true, 1, false>)
+                                    : (tdep ? k_finish<false, 1, true> : k_finish<false, 1, false>))
+                   : (K.n_inst == 1 ? (tdep ? k_finish<true, 2, true> : k_finish<true, 2, false>)
+                                    : (tdep ? k_finish<false, 2, true> : k_finish<false, 2, false>));
     fin<<<blocks(K.n_cg, DIAG_THREADS), DIAG_THREADS, 0, st>>>(D, K, K.n_inst == 1 ? last_sweep : -1,
                                                                    push_blocks);
     if (reduce_diag) k_diag_reduce<<<blocks(K.n_inst, 64), 64, 0, st>>>(D, K);

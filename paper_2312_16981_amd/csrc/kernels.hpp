@@ -55,8 +55,10 @@ void launch_sort_scatter(int dim, const Dev& D, const Consts& K, const Pool& B, 
 // before the next: for a single instance in the next sweep (the last one's in
 // launch_finish), else by a decide launch after every sweep
 void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t st);
+// rounds r0..r1-1 of the 1-D iteration in tiles (si_tile.hip)
+void launch_si_rounds(const Dev& D, const Consts& K, int r0, int r1, hipStream_t st);
 // commit and energy sums; reduce_diag folds the sums' sub-slots on the device;
-// last_sweep is the last sweep launched (a single instance's convergence
+// last_sweep is the last sweep (in tiles: round) launched (a single instance's convergence
 // after it is decided by the commit launch); the commit also sums the
 // survivor counts of the push's push_blocks blocks
 void launch_finish(const Dev& D, const Consts& K, bool reduce_diag, int last_sweep, int push_blocks,

@@ -127,6 +127,7 @@ struct ugkwp_ctx {
     Consts K{};
     int ncell = 0;
     int64_t n_fx = 0, n_fy = 0, n_edges = 0;
+    size_t n_winflow = 0;
 
     // device state
     std::vector<void*> owned;
@@ -337,6 +338,7 @@ struct ugkwp_ctx {
         K.stim = P.opacity_stim;
         K.nu_power = P.nu_power;
         K.si_tol = P.si_tol;
+        K.si_max = P.si_max_iters;
         K.n_cap = P.n_cap;
         K.pool_cap = P.pool_capacity;
         K.flags = P.flags;
@@ -404,20 +406,29 @@ struct ugkwp_ctx {
         d.rhoh = dalloc<double>(owned, ncg);
         d.Q = dalloc<double>(owned, ncg);
         d.phi0 = dalloc<double>(owned, ncg);
-        d.phi1 = dalloc<double>(owned, ncg);
-        d.phi2 = dalloc<double>(owned, ncg);
+        d.phi0n = dalloc<double>(owned, ncg);
         // slots the sweeps never write (padding groups and cells) stay zero
-        for (double* q : {d.phi0, d.phi1, d.phi2, d.rho, d.rho_new})
-            HIPCHK(hipMemsetAsync(q, 0, sizeof(double) * ncg, st));
+        for (double* q : {d.phi0, d.phi0n, d.rho, d.rho_new}) HIPCHK(hipMemsetAsync(q, 0, sizeof(double) * ncg, st));
+        setup_tiles(d);
+        if (dim == 2) {
+            d.phi1 = dalloc<double>(owned, ncg);
+            d.phi2 = dalloc<double>(owned, ncg);
+            for (double* q : {d.phi1, d.phi2}) HIPCHK(hipMemsetAsync(q, 0, sizeof(double) * ncg, st));
+        }
         d.nb = dalloc<int32_t>(owned, ncg);
         d.boff = dalloc<int64_t>(owned, ncg + 1);
         d.wnew = dalloc<double>(owned, ncg);
         d.wsn = dalloc<double>(owned, ncg);
-        d.sx = dalloc<double>(owned, ncg);
-        d.sy = dalloc<double>(owned, ncg);
-        d.bcoef = dalloc<double>(owned, ncg);
-        d.rho_alt = dalloc<double>(owned, ncg);
-        d.winflow = dalloc<double>(owned, 2 * ncg);
+        if (K.flags & UGKWP_FLAG_SLOPES) {
+            d.sx = dalloc<double>(owned, ncg);
+            d.sy = dalloc<double>(owned, ncg);
+            d.bcoef = dalloc<double>(owned, ncg);
+        }
+        if (K.flags & UGKWP_FLAG_WAVE_ITER) {
+            n_winflow = dim == 2 ? 2 * ncg : (size_t)(2 * K.tile_cap + 1) * n_inst * 2 * MAX_G;
+            d.winflow = dalloc<double>(owned, n_winflow);
+            if (dim == 2) d.rho_alt = dalloc<double>(owned, ncg);
+        }
         d.nbi = dalloc<int32_t>(owned, ncg);
         d.beta = dalloc<double>(owned, ncg);
         d.dep = dalloc<double>(owned, ncg);
@@ -473,10 +484,9 @@ struct ugkwp_ctx {
         HIPCHK(hipMemsetAsync(d.surv, 0, sizeof(double) * ncg, st));
         HIPCHK(hipMemsetAsync(d.nb, 0, sizeof(int32_t) * ncg, st));
         HIPCHK(hipMemsetAsync(d.nbi, 0, sizeof(int32_t) * ncg, st));
-        HIPCHK(hipMemsetAsync(d.sx, 0, sizeof(double) * ncg, st));
-        HIPCHK(hipMemsetAsync(d.sy, 0, sizeof(double) * ncg, st));
-        HIPCHK(hipMemsetAsync(d.bcoef, 0, sizeof(double) * ncg, st));
-        HIPCHK(hipMemsetAsync(d.winflow, 0, sizeof(double) * 2 * ncg, st));
+        if (d.sx)
+            for (double* q : {d.sx, d.sy, d.bcoef}) HIPCHK(hipMemsetAsync(q, 0, sizeof(double) * ncg, st));
+        if (d.winflow) HIPCHK(hipMemsetAsync(d.winflow, 0, sizeof(double) * n_winflow, st));
         HIPCHK(hipMemsetAsync(d.wnew, 0, sizeof(double) * ncg, st));
         HIPCHK(hipMemsetAsync(d.Q, 0, sizeof(double) * ncg, st));
         HIPCHK(hipMemsetAsync(d.rhoh, 0, sizeof(double) * ncg, st));
@@ -503,6 +513,110 @@ struct ugkwp_ctx {
         step_idx = 0;
         HIPCHK(hipStreamSynchronize(st));
         HIPCHK(hipGetLastError());
+    }
+
+    // ---------------------------------------------------------------- 1-D iteration in tiles
+    // (si_tile.hpp)
+    bool tiled() const { return dim == 1; }
+    bool tile_wit() const { return (P.flags & UGKWP_FLAG_WAVE_ITER) != 0; }
+    bool tile_tdep() const { return P.opacity_T_power != 0 || P.opacity_stim || K.table || K.olson; }
+    // cells a tile computes along on either side for S sweeps per round (the wave flux
+    // of an iterate with slopes reaches two cells, and a later round starts one further in)
+    int tile_halo(int S) const { return tile_wit() ? ((P.flags & UGKWP_FLAG_SLOPES) ? 2 : 1) * S : S - 1; }
+
+    void setup_tiles(Dev& d)
+    {
+        K.tile_S = K.tile_H = K.tile_cap = K.tile_extra = K.tile_blocks = K.tile_threads = K.tile_cpt = K.tile_reg = 0;
+        if (!tiled()) return;
+        const size_t ncg = (size_t)K.n_cg;
+        // sweep planes kept: as many as a launch of a small context takes, fewer for
+        // large ones (a plane is 16 bytes per slot)
+        K.tile_cap = K.n_cg <= (1ll << 22) ? TILE_S_MAX : (K.n_cg <= (1ll << 27) ? 4 : 2);
+        if (n_inst > 1) K.tile_cap = std::min(K.tile_cap, tile_wit() ? 2 : 4);
+        const size_t planes = 2 * (size_t)K.tile_cap;
+        d.tile_rho = dalloc<double>(owned, planes * ncg);
+        d.tile_phi = dalloc<double>(owned, planes * ncg);
+        d.tile_T = dalloc<double>(owned, planes * (size_t)ncell);
+        d.tile_u = dalloc<double>(owned, planes * (size_t)ncell);
+        if (tile_wit()) d.tile_Q = dalloc<double>(owned, planes * ncg);
+        K.tile_S = K.tile_cap;
+        int64_t most = 0;       // blocks of any shape: an interior of at least one cell
+        if (n_inst > 1) {
+            batch_tiles(d);
+            most = K.tile_blocks;
+        } else {
+            K.tile_extra = 1;
+            most = ncell;
+        }
+        d.tile_res = dalloc<Resid>(owned, planes * (size_t)most);
+    }
+
+    // A batch's tiles, the same for every step: each block's instance and tile.
+    void batch_tiles(Dev& d)
+    {
+        K.tile_threads = 512;
+        K.tile_cpt = 2;
+        K.tile_H = tile_halo(K.tile_S);
+        std::vector<int2> blk;
+        std::vector<int32_t> start;
+        for (int k = 0; k < n_inst; ++k) {
+            start.push_back((int32_t)blk.size());
+            const int W = K.tile_threads / inst[k].Gp * K.tile_cpt - 2 * K.tile_H;
+            for (int t = 0; t * W < inst[k].nx; ++t) blk.push_back(make_int2(k, t));
+        }
+        start.push_back((int32_t)blk.size());
+        K.tile_blocks = (int)blk.size();
+        int2* db = dalloc<int2>(owned, blk.size());
+        int32_t* ds = dalloc<int32_t>(owned, start.size());
+        HIPCHK(hipMemcpy(db, blk.data(), sizeof(int2) * blk.size(), hipMemcpyHostToDevice));
+        HIPCHK(hipMemcpy(ds, start.data(), sizeof(int32_t) * start.size(), hipMemcpyHostToDevice));
+        d.tile_blk = db;
+        d.tile_start = ds;
+    }
+
+    // The tile shape of a single instance's next steps, for `sweeps` sweeps each: the
+    // block size and sweeps per round with the least estimated time, from a round's
+    // fixed cost (launch, loads, residuals: about 5 us), a sweep's chain (0.8 us) and
+    // its instructions (0.5 us per wavefront and SIMD, 1 us with a T-dependent opacity).
+    void plan_tiles(int sweeps)
+    {
+        if (!tiled() || n_inst > 1) return;
+        const Inst& I = inst[0];
+        double best = 1e300;
+        for (int bt = 128; bt <= tile_max_threads(tile_tdep(), false); bt *= 2)
+            for (int S = 1; S <= K.tile_cap; ++S) {
+                const int C = bt / I.Gp, W = C - 2 * tile_halo(S);
+                if (C < 2 || W < 1) continue;
+                const int64_t nb = (I.nx + W - 1) / W;
+                const double waves = std::max(bt / 256.0, (double)nb * bt / 64.0 / 1024.0);
+                const double sweep = 0.8 + (tile_wit() ? 0.8 : 0.0) + (tile_tdep() ? 1.0 : 0.5) * waves;
+                const int rounds = (sweeps + S - 1) / S;
+                const double t = rounds * (5.0 + std::min(S, sweeps) * sweep);
+                if (t < best) {
+                    best = t;
+                    K.tile_threads = bt;
+                    K.tile_S = S;
+                    K.tile_H = tile_halo(S);
+                    K.tile_cpt = 1;
+                    K.tile_blocks = (int)nb;
+                    K.tile_reg = !tile_wit() && bt <= 512 && nb <= 256;      // one block per CU
+                }
+            }
+    }
+
+    // Launches that take `sweeps` sweeps: sweeps themselves, or rounds of tiles (a
+    // batch's first round takes what each instance needed before: one round more).
+    int sweep_launches(int sweeps) const
+    {
+        if (!tiled()) return std::min(sweeps, P.si_max_iters);
+        if (n_inst == 1) return (sweeps + K.tile_S - 1) / K.tile_S;
+        return 1 + (std::max(sweeps - K.tile_S, 1) + K.tile_S - 1) / K.tile_S;
+    }
+
+    // whether n launches have taken as many sweeps as the iteration may
+    bool sweeps_spent(int n) const
+    {
+        return tiled() ? 1 + (int64_t)(n - 1) * K.tile_S >= P.si_max_iters : n >= P.si_max_iters;
     }
 
     // point D's record entries at record `slot`, the record before it at `prev`
@@ -780,6 +894,8 @@ struct ugkwp_ctx {
         double* rho_new;
         double* T;
         double* T_new;
+        double* phi0;
+        double* phi0n;
         int cur_mv, cur_st;
         uint32_t step;
         int64_t n_slots;       // known after processing; an estimate while planned
@@ -788,13 +904,14 @@ struct ugkwp_ctx {
         int slot;              // record the step writes
         bool do_sort;
         bool push_timed;       // events around the push (a few microseconds each)
-        int sweeps;            // sweeps launched
+        int sweeps;            // sweeps launched (1-D: rounds of them)
     };
 
     Plan state_now() const
     {
         Plan p{};
         p.rho = D.rho; p.rho_new = D.rho_new; p.T = D.T; p.T_new = D.T_new;
+        p.phi0 = D.phi0; p.phi0n = D.phi0n;
         p.cur_mv = cur_mv; p.cur_st = cur_st;
         p.step = step_idx;
         p.n_slots = n_slots;
@@ -807,6 +924,7 @@ struct ugkwp_ctx {
     void set_state(const Plan& p)
     {
         D.rho = p.rho; D.rho_new = p.rho_new; D.T = p.T; D.T_new = p.T_new;
+        D.phi0 = p.phi0; D.phi0n = p.phi0n;
         cur_mv = p.cur_mv; cur_st = p.cur_st;
         step_idx = p.step;
         n_slots = p.n_slots;
@@ -825,6 +943,7 @@ struct ugkwp_ctx {
         Plan q = p;
         std::swap(q.rho, q.rho_new);
         std::swap(q.T, q.T_new);
+        std::swap(q.phi0, q.phi0n);
         if (p.do_sort) q.cur_st = 1 - p.cur_st;    // sorted, compact pool: moving fields in mv[cur_mv]
         else q.cur_mv = 1 - p.cur_mv;              // positions of this step in the other moving buffer
         q.n_slots = n_slots_after;
@@ -904,7 +1023,11 @@ struct ugkwp_ctx {
         launch_sample(dim, D, K, view(cur_mv, cur_st), st);
     }
 
-    void enqueue_sweeps(int k0, int k1) { launch_si_sweeps(D, K, k0, k1, st); }
+    void enqueue_sweeps(int k0, int k1)
+    {
+        if (tiled()) launch_si_rounds(D, K, k0, k1, st);
+        else launch_si_sweeps(D, K, k0, k1, st);
+    }
 
     // Run `enq` on the context stream: replayed from the HIP graph captured for
     // `key` (captured on first use), or launched directly without graphs.
@@ -969,7 +1092,8 @@ struct ugkwp_ctx {
         // the wave flux and Q are evaluated by the first sweep: no launch of their own
         if (phase_times) HIPCHK(hipEventRecord(e[3], st));
         const int first = p.sweeps;
-        launch_group(0x200000u | (uint32_t)first | (parity() << 16) | ((uint32_t)p.slot << 17),
+        launch_group(0x200000u | (uint32_t)first | (parity() << 16) | ((uint32_t)p.slot << 17) |
+                         ((uint32_t)K.tile_S << 22) | ((uint32_t)K.tile_threads / 128u << 26),
                      [&] { enqueue_sweeps(0, first); });
         if (phase_times) HIPCHK(hipEventRecord(e[4], st));
         enqueue_finish(p.do_sort, rec_cap > 0 ? p.nrec : -1, first - 1);
@@ -979,7 +1103,6 @@ struct ugkwp_ctx {
     // Returns the record of the committed step (in h_status).
     StatusView take_up(Plan& p, StatusView s)
     {
-        const int kmax = P.si_max_iters;
         point_record(D, p.slot, p.rec);
         for (;;) {
             const unsigned long long err = s.counters[CNT_ERR];
@@ -993,8 +1116,9 @@ struct ugkwp_ctx {
                 fail(UGKWP_EHIP, "internal error: step %u recorded as step %llu", p.step, s.counters[CNT_DONE]);
             if (s.counters[CNT_CONV] == (unsigned long long)n_inst)
                 fail(UGKWP_EHIP, "internal error: converged step %u not committed", p.step);
-            if (p.sweeps >= kmax) fail(UGKWP_ENOCONV, "source iteration did not converge in %d sweeps", kmax);
-            const int kend = std::min(p.sweeps + 4, kmax);
+            if (sweeps_spent(p.sweeps))
+                fail(UGKWP_ENOCONV, "source iteration did not converge in %d sweeps", P.si_max_iters);
+            const int kend = tiled() ? p.sweeps + 1 : std::min(p.sweeps + 4, P.si_max_iters);
             {
                 GateScope gs(K, use_graph ? GATE_OFF : p.step);
                 enqueue_sweeps(p.sweeps, kend);
@@ -1094,8 +1218,8 @@ struct ugkwp_ctx {
             // number births past 2^ID_BITS (each step births fewer than the capacity)
             if (ids_used + (uint64_t)m * (uint64_t)P.pool_capacity > ID_MASK)
                 fail(UGKWP_EPOOL, "particle ids would pass 2^%d", ID_BITS);
-            const int kmax = P.si_max_iters;
-            const int spec = std::min(kmax, last_sweeps + 1);
+            plan_tiles(last_sweeps + 1);
+            const int spec = sweep_launches(last_sweeps + 1);
             // plan and enqueue
             const Plan start = state_now();
             std::vector<Plan> plan;

@@ -1,0 +1,135 @@
+// The 1-D source iteration in tiles (si_tile.hip): rounds of several sweeps
+// per launch.  Shared with the commit (kernels.hip), which reads the iterate
+// the iteration converged to.
+//
+// A launch ("round") takes up to K.tile_S sweeps.  A block holds a tile of
+// consecutive cells: K.tile_H cells on either side of its interior are
+// computed along (fewer each sweep), so that no block waits for another.  The
+// number of sweeps is known only once the whole instance's residuals are, so
+// every sweep of a round keeps its output; round 0 takes as many sweeps as the
+// step before needed, and writes the last of them where the step's result
+// belongs (rho_new, phi0n, T_new), so that the commit has nothing to copy when
+// that count was right.
+#pragma once
+#include <hip/hip_runtime.h>
+#include "common.hpp"
+#include "device_common.hpp"
+
+namespace ugk {
+
+// Sweeps of round 0 of a step whose predecessor took `prev` (0: none yet).
+__device__ inline int tile_first(const Consts& K, int prev)
+{
+    const int s = prev > 0 ? min(prev + K.tile_extra, K.tile_S) : K.tile_S;
+    return min(s, K.si_max);
+}
+
+// First sweep and number of sweeps of a round, within the iteration's limit.
+struct TileRound {
+    int k0, ns;
+};
+__device__ inline TileRound tile_round(const Consts& K, int s0, int round)
+{
+    TileRound r;
+    r.k0 = round == 0 ? 0 : s0 + (round - 1) * K.tile_S;
+    r.ns = round == 0 ? s0 : max(0, min(K.tile_S, K.si_max - r.k0));
+    return r;
+}
+
+// Where the output of the iteration's sweep k lies: `final` (rho_new, phi0n,
+// T_new, uend) or plane `at` of the sweep arrays.
+struct TileOut {
+    bool final;
+    int at;
+};
+__device__ inline TileOut tile_out(const Consts& K, int s0, int k)
+{
+    TileOut o;
+    o.final = k == s0 - 1;
+    if (k < s0) o.at = k;
+    else {
+        const int q = k - s0, round = 1 + q / K.tile_S;
+        o.at = (round & 1) * K.tile_cap + q % K.tile_S;
+    }
+    return o;
+}
+
+// Boundary wave inflow of a sweep whose wave flux follows the iterate, by plane (the
+// last one: the sweep whose output lies in place): the low cell's groups, then the high cell's.
+__device__ inline double* tile_inflow(const Dev& D, const Consts& K, int inst, int at)
+{
+    return D.winflow + ((int64_t)at * K.n_inst + inst) * 2 * MAX_G;
+}
+
+// Residual entries of a round, one per sweep and block: no atomics, nothing to clear.
+__device__ inline Resid* tile_res(const Dev& D, const Consts& K, int round, int m)
+{
+    return D.tile_res + ((int64_t)(round & 1) * K.tile_cap + m) * K.tile_blocks;
+}
+
+// The stopping test of one sweep from its blocks' entries b0 .. b1-1, by a
+// wavefront: 1 converged, 0 not, -1 a temperature was non-positive or not finite.
+__device__ inline int tile_test(const Dev& D, const Consts& K, int round, int m, int b0, int b1, int lane)
+{
+    const Resid* res = tile_res(D, K, round, m);
+    Resid x = {0ull, 0ull, 0ull, 0ull};
+    for (int b = b0 + lane; b < b1; b += 4 * WAVE) {
+        Resid y[4];            // four entries in flight
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            y[q] = Resid{0ull, 0ull, 0ull, 0ull};
+            if (b + q * WAVE < b1) y[q] = res[b + q * WAVE];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            x.drho = max(x.drho, y[q].drho);
+            x.rho = max(x.rho, y[q].rho);
+            x.dT = max(x.dT, y[q].dT);
+            x.T = max(x.T, y[q].T);
+        }
+    }
+    const double drho = bitsd(wave_max_bits(bitsd(x.drho))), mrho = bitsd(wave_max_bits(bitsd(x.rho)));
+    const double dT = bitsd(wave_max_bits(bitsd(x.dT))), mT = bitsd(wave_max_bits(bitsd(x.T)));
+    if (mT != mT) return -1;
+    return drho <= K.si_tol * mrho && dT <= K.si_tol * mT ? 1 : 0;
+}
+
+// The outcome after a round for the only instance of a context, taken by every
+// thread of a block alike, in two parts: tile_gather tests every plane of the round
+// (a wavefront per plane; without waiting for the number of sweeps it took, so that
+// its loads go out with the kernel's first) and reads the recorded state once per
+// block (block 0 of the launch may record it meanwhile); after a barrier tile_outcome
+// gives the sweeps the iteration took when it converged, -1 when a temperature
+// failed first, 0 to go on.  sh: TILE_S_MAX + 1 words.
+__device__ inline void tile_gather(const Dev& D, const Consts& K, int round, int* sh)
+{
+    if (threadIdx.x == 0) sh[TILE_S_MAX] = D.ist[0].conv_sweeps;
+    const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+    for (int m = wid; m < K.tile_S; m += nw) {
+        const int v = tile_test(D, K, round, m, 0, K.tile_blocks, lane);
+        if (lane == 0) sh[m] = v;
+    }
+}
+
+__device__ inline int tile_outcome(const Consts& K, int round, int s0, const int* sh)
+{
+    int out = sh[TILE_S_MAX];
+    if (out != 0) return out;          // recorded by an earlier launch or just now
+    const TileRound q = tile_round(K, s0, round);
+    for (int m = q.ns - 1; m >= 0; --m) {
+        const int v = sh[m];
+        if (v != 0) out = v > 0 ? q.k0 + m + 1 : -1;
+    }
+    return out;
+}
+
+// Record the outcome of the iteration (block 0 of a single instance's launch, or
+// the decide kernel of a batch): the sweep count, or the failed temperature.
+__device__ inline void tile_record(const Dev& D, int inst, int out)
+{
+    D.ist[inst].conv_sweeps = out;
+    if (out > 0) atomicAdd((unsigned long long*)(D.counters + CNT_CONV), 1ull);
+    else atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_TEMP);
+}
+
+}  // namespace ugk

@@ -532,7 +532,7 @@ struct ugkwp_ctx {
         // sweep planes kept: as many as a launch of a small context takes, fewer for
         // large ones (a plane is 16 bytes per slot)
         K.tile_cap = K.n_cg <= (1ll << 22) ? TILE_S_MAX : (K.n_cg <= (1ll << 27) ? 4 : 2);
-        if (n_inst > 1) K.tile_cap = std::min(K.tile_cap, tile_wit() ? 2 : 4);
+        if (n_inst > 1) K.tile_cap = std::min(K.tile_cap, tile_wit() ? (tile_tdep() ? 1 : 2) : 3);
         const size_t planes = 2 * (size_t)K.tile_cap;
         d.tile_rho = dalloc<double>(owned, planes * ncg);
         d.tile_phi = dalloc<double>(owned, planes * ncg);
@@ -551,10 +551,14 @@ struct ugkwp_ctx {
         d.tile_res = dalloc<Resid>(owned, planes * (size_t)most);
     }
 
-    // A batch's tiles, the same for every step: each block's instance and tile.
+    // A batch's tiles, the same for every step: each block's instance and tile.  (256
+    // slabs, 3 sweeps: 512 threads of two cells took 1.41 ms a step, against 1.49 and
+    // 1.51 for 2 and 4 sweeps, 1.52 for 256 threads, 1.67 for 1024 and 1.74 for one cell a
+    // thread.)  The rows of a T-dependent opacity and those of a wave flux per iterate
+    // together leave room in 64 KiB of LDS for blocks of half the size.
     void batch_tiles(Dev& d)
     {
-        K.tile_threads = 512;
+        K.tile_threads = tile_wit() && tile_tdep() ? 256 : 512;
         K.tile_cpt = 2;
         K.tile_H = tile_halo(K.tile_S);
         std::vector<int2> blk;
@@ -599,7 +603,7 @@ struct ugkwp_ctx {
                     K.tile_H = tile_halo(S);
                     K.tile_cpt = 1;
                     K.tile_blocks = (int)nb;
-                    K.tile_reg = !tile_wit() && bt <= 512 && nb <= 256;      // one block per CU
+                    K.tile_reg = !tile_wit() && !tile_tdep() && bt <= 512 && nb <= 256;      // one block per CU
                 }
             }
     }

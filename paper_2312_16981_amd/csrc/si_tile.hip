@@ -485,7 +485,7 @@ static void tile_launch(const Dev& D, const Consts& K, int round, hipStream_t st
     const size_t rows = 2 + (TDEP ? 2 : 0) + (WIT ? 3 : 0);
     const size_t lds = (size_t)(K.tile_threads * K.tile_cpt + 2 * gmax) * rows * sizeof(double);
     if constexpr (SINGLE) {
-        if constexpr (!WIT) {
+        if constexpr (!WIT && !TDEP) {
             if (K.tile_reg) {
                 k_si_tile<FIRST, true, TDEP, LIN, EXT, false, 1, true><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
                 return;

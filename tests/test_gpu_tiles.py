@@ -79,12 +79,12 @@ def test_iteration_limit_across_rounds(kind):
         assert np.max(np.abs(a - b)) <= 1e-10 * max(np.max(np.abs(b)), 1e-300)
 
 
-@pytest.mark.parametrize("flags", [0, LIN, SL | WI])
-def test_batch_of_different_rounds(flags):
+@pytest.mark.parametrize("flags,T_power", [(0, 0.0), (LIN, 0.0), (SL | WI, 0.0), (LIN | SL | WI, 0.5), (LIN, 0.5)])
+def test_batch_of_different_rounds(flags, T_power):
     probs = []
     for k, (nx, G, kap) in enumerate([(1, 64, 1.0), (57, 32, 2000.0), (300, 16, 0.01), (19, 5, 300.0), (128, 64, 30.0)]):
         probs.append(W.slab(nx, G, lambda x, kap=kap: np.full_like(x, kap), dt=1e-3 if flags & WI else 4e-3,
-                            steps=0, w_ref=4e-5, seed=40 + k, pool_cap=1 << 18, flags=flags, name=f"bt{k}"))
+                            steps=0, w_ref=4e-5, seed=40 + k, pool_cap=1 << 18, flags=flags, T_power=T_power, name=f"bt{k}"))
     ctx = ugkwp.from_batch(probs)
     sims = [oracle.Sim(q) for q in probs]
     ctx.step(10)

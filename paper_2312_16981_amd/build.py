@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libugkwp.so")
-SOURCES = ["kernels.hip", "si_tile.hip", "adjoint.hip", "runtime.hip"]
+SOURCES = ["kernels.hip", "si_tile.hip", "si_grid.hip", "adjoint.hip", "runtime.hip"]
 # The tile sweeps loop over code full of 64-bit constants (exp, the Planck
 # polynomials); hoisted out of the loop they fill the register file (256 VGPRs and
 # spills instead of 76-135), so they are formed where they are used.

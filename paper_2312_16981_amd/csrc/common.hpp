@@ -213,6 +213,7 @@ struct Dev {
     const double* olH;
     const double* olchi;
     double* uend;
+    double* ol_un;              // U(T^n) of those cells, kept by the first of a step's 2-D sweeps
     // volumetric source: rate per (cell, group) slot, and whether the step's source is on
     const double* qsrc;
     int* src_on;

@@ -208,4 +208,13 @@ __device__ inline unsigned long long wave_max_bits(double x)
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// Block b of n works on item xcd_band(b, n): blocks go to the 8 XCDs in turn, and this
+// gives each a contiguous run of items, whose neighbours its L2 then holds (sweeps of
+// 256 x 256 cells of 32 groups: 230 -> 222 us a step; 285 x 285 of 24: 1371 -> 1332).
+__device__ inline uint32_t xcd_band(uint32_t b, uint32_t n)
+{
+    const uint32_t x = b & 7u, q = n >> 3, r = n & 7u;
+    return x * q + min(x, r) + (b >> 3);
+}
+
 }  // namespace ugk

@@ -14,7 +14,8 @@
 //                  collided particles (their slots stay empty until the next sort)
 //   k_sort_scatter counting sort of the survivors by (cell, group) slot, which
 //                  also compacts the pool
-//   k_si_sweep     source iteration (Appendix B, Eq. macroSysAppendixIte, Algorithm 2);
+//   k_si_sweep     2-D source iteration (Appendix B, Eq. macroSysAppendixIte, Algorithm 2;
+//                  si_tile.hip: 1-D; si_grid.hip: an opacity that follows the iterate);
 //                  sweep 0 also evaluates the wave free-transport flux (Sec. 2.2,
 //                  F^{fr,wave}; Remark 3) and the static part Q of the macroscopic
 //                  update (Eq. macroSysFinal)
@@ -124,15 +125,23 @@ __global__ void k_tables(Dev D, Consts K)
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= K.n_cg) return;
     const Slot s = decode_slot(D, K, j);
+    const int mcell = D.inst[s.inst].cell_off + s.lcell;
+    double tsig = 0.0;
+    if (K.table) {
+        // (whole wavefronts: the slots come in multiples of 64)
+        const Inst& I = D.inst[s.inst];
+        TablePlace t = {nullptr, 0.0};
+        if (s.cell_ok) t = table_place(D, K, D.tab_mat[mcell], D.T[mcell]);
+        tsig = table_group_sigma_lanes(D, K, t, I.edge_off, s.g, I.G, I.Gp, s.cell_ok);
+    }
     if (!s.active) {
         D.sig[j] = 0.0; D.sv[j] = 0.0; D.es[j] = 1.0; D.c4[j] = 1.0; D.wc[j] = 0.0; D.inv_kappa[j] = 0.0;
         return;
     }
     const Inst& I = D.inst[s.inst];
-    const double Tc = D.T[I.cell_off + s.lcell];
+    const double Tc = D.T[mcell];
     const double kap = K.t_power != 0.0 ? D.kappa[j] * temp_pow(Tc, K.t_power) : D.kappa[j];
-    const double sg = K.table ? table_group_sigma(D, K, D.tab_mat[I.cell_off + s.lcell], I.edge_off + s.g, Tc)
-                              : kap * group_factor(D, K, I.edge_off, s.g, Tc);
+    const double sg = K.table ? tsig : kap * group_factor(D, K, I.edge_off, s.g, Tc);
     // flights: tau = (eps^2/c) f(nu)^-1 / kappa; with the stimulated-emission
     // factor or a table and group opacities the group opacity's T dependence goes
     // here (the push divides by S_g), per particle the push applies it itself
@@ -151,27 +160,34 @@ __global__ void k_tables(Dev D, Consts K)
 
 // The push's rows of a tabulated opacity: for every cell and nu node, ln sigma of
 // the cell's material interpolated to the cell's T^n (launched with the tables at
-// the start of each step).
-__global__ void k_tab_rows(Dev D, Consts K)
+// the start of each step).  A block's cells are placed in the table once each, by its
+// first threads: with a logarithm per entry, 285 x 285 cells of 136 nodes took 52 us.
+constexpr int ROW_CELLS = 32;
+
+__global__ __launch_bounds__(256) void k_tab_rows(Dev D, Consts K)
 {
     if (!gate_open(D, K, 0)) return;
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= (int64_t)K.ncell * K.tab_nnu) return;
-    const int cell = (int)(j / K.tab_nnu), i = (int)(j % K.tab_nnu);
-    double b;
-    const int jt = table_locate_guess(D.tab_lT, K.tab_nT, log(D.T[cell]), K.tab_lT_inv, &b);
-    const double* L = D.tab_lsig + ((int64_t)D.tab_mat[cell] * K.tab_nT + jt) * K.tab_nnu + i;
-    D.tab_row[j] = (1.0 - b) * L[0] + b * L[K.tab_nnu];
+    __shared__ TablePlace at[ROW_CELLS];
+    const int c0 = blockIdx.x * ROW_CELLS, nc = min(ROW_CELLS, K.ncell - c0);
+    if ((int)threadIdx.x < nc) at[threadIdx.x] = table_place(D, K, D.tab_mat[c0 + threadIdx.x], D.T[c0 + threadIdx.x]);
+    __syncthreads();
+    const uint32_t n = (uint32_t)K.tab_nnu;
+    double* const out = D.tab_row + (int64_t)c0 * n;
+    for (uint32_t q = threadIdx.x; q < (uint32_t)nc * n; q += 256) {
+        const uint32_t c = q / n, i = q - c * n;
+        const TablePlace t = at[c];
+        out[q] = (1.0 - t.b) * t.row[i] + t.b * t.row[i + n];
+    }
 }
 
 // The nu intervals and upper-node weights of the three Simpson points (lower
-// edge, midpoint, upper edge) of the group starting at every edge e < n_edges - 1,
-// once at set-up (after the logs of the nodes).
+// edge, midpoint, upper edge) of the group starting at every edge (of the last edge the
+// first), once at set-up (after the logs of the nodes).
 __global__ void k_tab_groups(Dev D, Consts K, int64_t n_edges)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e + 1 >= n_edges) return;
-    const double nl = D.nu[e], nh = D.nu[e + 1], nm = 0.5 * (nl + nh);
+    if (e >= n_edges) return;
+    const double nl = D.nu[e], nh = D.nu[e + 1 < n_edges ? e + 1 : e], nm = 0.5 * (nl + nh);
     const double pts[3] = {nl, nm, nh};
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
@@ -217,7 +233,7 @@ __global__ void k_face_D(Dev D, Consts K, int inst, int axis)
     if (cl >= 0 && cr >= 0) {
         const double a = D.sig[I.cg_off + ((int64_t)cl << I.lgGp) + g];
         const double b = D.sig[I.cg_off + ((int64_t)cr << I.lgGp) + g];
-        sf = (a + b > 0.0) ? 2.0 * (a * b) / (a + b) : 0.0;
+        sf = face_sigma(a, b);
     } else {
         sf = D.sig[I.cg_off + ((int64_t)(cl >= 0 ? cl : cr) << I.lgGp) + g];
     }
@@ -1446,23 +1462,6 @@ __host__ __device__ inline const double* sweep_in(const Dev& D, int k)
 }
 __host__ __device__ inline double* sweep_out(const Dev& D, int k) { return (k & 1) ? D.phi2 : D.phi1; }
 
-// Residual sub-slots of sweep k for instance inst: [RES_SLOTS][n_inst][RES_SUB],
-// so that the slots of sweep 0 form one range cleared at the start of a step.
-__device__ inline Resid* res_slot(const Dev& D, const Consts& K, int inst, int k)
-{
-    return D.res + ((int64_t)(k % RES_SLOTS) * K.n_inst + inst) * RES_SUB;
-}
-
-// The stopping test after sweep k for instance inst, taken by one wavefront
-// from the instance's 64 residual sub-slots (lane l reads sub-slot l).
-__device__ inline bool si_converged(const Dev& D, const Consts& K, int inst, int k, int lane)
-{
-    const Resid r = res_slot(D, K, inst, k)[lane];
-    const double drho = bitsd(wave_max_bits(bitsd(r.drho))), mrho = bitsd(wave_max_bits(bitsd(r.rho)));
-    const double dT = bitsd(wave_max_bits(bitsd(r.dT))), mT = bitsd(wave_max_bits(bitsd(r.T)));
-    return drho <= K.si_tol * mrho && dT <= K.si_tol * mT;
-}
-
 // Sweep k: rho^{k+1}, T^{k+1} and phi^{k+1} from phi^k for every instance whose
 // iteration is still running.  The residual maxima of the sweep go to sub-slots
 // of the instance (spread over 64 addresses by block); k_si_decide reads them.
@@ -1483,7 +1482,8 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
 {
     constexpr int DIM = 2;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
-    const int64_t j = (int64_t)blockIdx.x * SI_THREADS + threadIdx.x;
+    const uint32_t blk = SINGLE ? xcd_band(blockIdx.x, gridDim.x) : blockIdx.x;
+    const int64_t j = (int64_t)blk * SI_THREADS + threadIdx.x;
     // The gate (step count), for batches the flags of the block's wavefronts
     // (a block whose four wavefronts all belong to converged instances returns
     // after them) and for one instance the state and residuals of the sweep
@@ -1508,14 +1508,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         // little
         __shared__ int stop;
         if (wid == 0) {
-            bool conv = false;
-            if (cs_prev == 0) {
-                const double drho = bitsd(wave_max_bits(bitsd(res_prev.drho)));
-                const double mrho = bitsd(wave_max_bits(bitsd(res_prev.rho)));
-                const double dTm = bitsd(wave_max_bits(bitsd(res_prev.dT)));
-                const double mTm = bitsd(wave_max_bits(bitsd(res_prev.T)));
-                conv = drho <= K.si_tol * mrho && dTm <= K.si_tol * mTm;
-            }
+            const bool conv = cs_prev == 0 && resid_converged(K, res_prev);
             if (lane == 0) {
                 stop = (conv || cs_prev != 0) ? 1 : 0;
                 if (conv && blockIdx.x == 0) {
@@ -1636,7 +1629,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
                 double sf = sk;
                 if (F.inside[q]) {
                     const double sn = K.table ? tsig_n[q] : kap_n[q] * temp_pow(T_nb[q], K.t_power) * Sn[q];
-                    sf = (sk + sn > 0.0) ? 2.0 * (sk * sn) / (sk + sn) : 0.0;
+                    sf = face_sigma(sk, sn);
                 }
                 Df[q] = face_coef(K, mt, sf, q < 2 ? I.fcx : I.fcy);
             }
@@ -1667,26 +1660,8 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     double Tnew = 1.0, uend = 0.0;
     bool bad = false;
     if (work) {
-        if (TDEP && olH > 0.0) {
-            // Olson's heat capacity: the energy equation in the material energy U,
-            // U(T^{n+1}) = U(T^n) + exchange.  Literal: U(T^{k+1}) = U(T^n) +
-            // exchange(phi^k), solved for T^{k+1}; linearized: one Newton step at
-            // T^k with U and the emission linearized, whose material energy is
-            // U(T^k) + C_v(T^k)(T^{k+1} - T^k).
-            const double un = olson_energy(olH, olchi, Tn);
-            if (pinned) {
-                Tnew = Tn;
-                uend = un;
-            } else if (LIN) {
-                const double uk = olson_energy(olH, olchi, Tk), ck = olson_cv(olH, olchi, Tk);
-                Tnew = Tk + (un - uk + K.dt / (K.eps * K.eps) * contrib) / (ck + K.dt / (K.eps * K.eps) * dcon);
-                uend = uk + ck * (Tnew - Tk);
-            } else {
-                uend = un + K.dt / (K.eps * K.eps) * contrib;
-                Tnew = olson_temperature(olH, olchi, uend, Tk);
-            }
-        } else if (LIN) Tnew = pinned ? Tn : Tk + (Tn - Tk + dtcv * contrib) / (1.0 + dtcv * dcon);
-        else Tnew = pinned ? Tn : Tn + dtcv * contrib;
+        const double un = TDEP && olH > 0.0 ? olson_energy(olH, olchi, Tn) : 0.0;
+        Tnew = cell_temperature<TDEP, LIN>(K, {Tn, Tk, dtcv, olH, olchi, un, pinned != 0}, contrib, dcon, &uend);
         if (LIN && s.active) {
             // rho^{k+1} with the linearized emission of T^{k+1}
             const double pe = pinned ? phi : phi + dph * (Tnew - Tk);
@@ -1794,7 +1769,7 @@ __global__ void k_si_decide(Dev D, Consts K, int k)
     const int inst = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const int lane = threadIdx.x & (WAVE - 1);
     if (inst >= K.n_inst || D.ist[inst].conv_sweeps != 0) return;
-    const bool conv = si_converged(D, K, inst, k, lane);
+    const bool conv = resid_converged(K, res_slot(D, K, inst, k)[lane]);
     if (conv) {
         // the instance's wavefronts stop running in the following sweeps
         for (int64_t w = D.inst_cg[inst] / WAVE + lane; w < D.inst_cg[inst + 1] / WAVE; w += WAVE) D.wave_run[w] = 0;
@@ -2156,7 +2131,7 @@ static inline unsigned blocks(int64_t n, int t) { return (unsigned)((n + t - 1) 
 void launch_tables(const Dev& D, const Consts& K, hipStream_t st)
 {
     k_tables<<<blocks(K.n_cg, 256), 256, 0, st>>>(D, K);
-    if (K.table) k_tab_rows<<<blocks((int64_t)K.ncell * K.tab_nnu, 256), 256, 0, st>>>(D, K);
+    if (K.table) k_tab_rows<<<blocks(K.ncell, ROW_CELLS), 256, 0, st>>>(D, K);
 }
 
 void launch_tab_logs(double* v, int64_t n, hipStream_t st)
@@ -2397,20 +2372,14 @@ void launch_sort_scatter(int dim, const Dev& D, const Consts& K, const Pool& In,
     }
 }
 
-template <bool TDEP, bool LIN, bool EXT>
-static auto sweep_kernel_ext(bool fold, int k)
-{
-    return fold ? (k == 0 ? k_si_sweep<true, true, TDEP, LIN, EXT> : k_si_sweep<false, true, TDEP, LIN, false>)
-                : (k == 0 ? k_si_sweep<true, false, TDEP, LIN, EXT> : k_si_sweep<false, false, TDEP, LIN, false>);
-}
-
 // the first sweep evaluates the wave flux: with slope terms or boundary-source
 // ghosts, its extended instantiation
-template <bool TDEP, bool LIN>
-static auto sweep_kernel(const Consts& K, bool fold, int k)
+template <bool SINGLE, bool TDEP, bool LIN>
+static auto sweep_kernel(const Consts& K, int k)
 {
-    return (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) ? sweep_kernel_ext<TDEP, LIN, true>(fold, k)
-                                                                           : sweep_kernel_ext<TDEP, LIN, false>(fold, k);
+    if (k > 0) return k_si_sweep<false, SINGLE, TDEP, LIN, false>;
+    return (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) ? k_si_sweep<true, SINGLE, TDEP, LIN, true>
+                                                                           : k_si_sweep<true, SINGLE, TDEP, LIN, false>;
 }
 
 // rho^m of the source iteration: rho^n for m = 0; from the wave flux of each
@@ -2434,22 +2403,29 @@ void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t
             if (K.flags & UGKWP_FLAG_SLOPES) launch_slopes(2, D, K, sweep_rho(D, K, k), true, st);
             k_wave_q<<<blocks(K.n_cg, 256), 256, 0, st>>>(D, K, k, sweep_rho(D, K, k));
         }
-        // every instance of a context has the same dimension
         const bool lin = (K.flags & UGKWP_FLAG_SI_LINEARIZED) != 0;
+        const double* rho_in = sweep_rho(D, K, k);
+        double* rho_out = const_cast<double*>(sweep_rho(D, K, k + 1));
+        const int decide_prev = fold && k > k0 ? 1 : 0;
         // a temperature-dependent or tabulated opacity and Olson's heat capacity take
         // the sweeps that re-evaluate the material from the iterate
-        auto kern = (K.t_power != 0.0 || K.stim || K.table || K.olson) ? (lin ? sweep_kernel<true, true>(K, fold, k) : sweep_kernel<true, false>(K, fold, k))
-                                     : (lin ? sweep_kernel<false, true>(K, fold, k) : sweep_kernel<false, false>(K, fold, k));
-        kern<<<blocks(K.n_cg, SI_THREADS), SI_THREADS, 0, st>>>(D, K, k, sweep_in(D, k), sweep_out(D, k),
-                                                                    fold && k > k0 ? 1 : 0, sweep_rho(D, K, k),
-                                                                    const_cast<double*>(sweep_rho(D, K, k + 1)));
+        const bool tdep = opacity_form(K) != OP_FIXED;
+        if (fold && tdep) {
+            launch_si_grid(D, K, k, sweep_in(D, k), sweep_out(D, k), decide_prev, rho_in, rho_out, st);
+            continue;
+        }
+        auto kern = fold ? (lin ? sweep_kernel<true, false, true>(K, k) : sweep_kernel<true, false, false>(K, k))
+                  : tdep ? (lin ? sweep_kernel<false, true, true>(K, k) : sweep_kernel<false, true, false>(K, k))
+                         : (lin ? sweep_kernel<false, false, true>(K, k) : sweep_kernel<false, false, false>(K, k));
+        kern<<<blocks(K.n_cg, SI_THREADS), SI_THREADS, 0, st>>>(D, K, k, sweep_in(D, k), sweep_out(D, k), decide_prev,
+                                                                rho_in, rho_out);
         if (!fold) k_si_decide<<<blocks((int64_t)K.n_inst * WAVE, 256), 256, 0, st>>>(D, K, k);
     }
 }
 
 void launch_finish(const Dev& D, const Consts& K, bool reduce_diag, int last_sweep, int push_blocks, hipStream_t st)
 {
-    const bool tdep = K.t_power != 0.0 || K.stim || K.table || K.olson;
+    const bool tdep = opacity_form(K) != OP_FIXED;
     auto fin = K.inst0.dim == 1
                    ? (K.n_inst == 1 ? (tdep ? k_finish<true, 1, true> : k_finish<true, 1, false>)
                                     : (tdep ? k_finish<false, 1, true> : k_finish<false, 1, false>))

@@ -55,6 +55,9 @@ void launch_sort_scatter(int dim, const Dev& D, const Consts& K, const Pool& B, 
 // before the next: for a single instance in the next sweep (the last one's in
 // launch_finish), else by a decide launch after every sweep
 void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t st);
+// one sweep of a single instance whose opacity follows the iterate (si_grid.hip)
+void launch_si_grid(const Dev& D, const Consts& K, int k, const double* phi_in, double* phi_out, int decide_prev,
+                    const double* rho_in, double* rho_out, hipStream_t st);
 // rounds r0..r1-1 of the 1-D iteration in tiles (si_tile.hip)
 void launch_si_rounds(const Dev& D, const Consts& K, int r0, int r1, hipStream_t st);
 // commit and energy sums; reduce_diag folds the sums' sub-slots on the device;

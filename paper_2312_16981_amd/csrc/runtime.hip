@@ -144,6 +144,7 @@ struct ugkwp_ctx {
     double* d_phib = nullptr;
     // Olson's material models (allocated on first use)
     double* olH_buf = nullptr;
+    double* olun_buf = nullptr;
     double* olchi_buf = nullptr;
     double* uend_buf = nullptr;
     double* qsrc_buf = nullptr;
@@ -245,7 +246,7 @@ struct ugkwp_ctx {
         D = Dev{};
         mv[0] = mv[1] = stb[0] = stb[1] = Pool{};
         have_opacity = have_material = false;
-        olH_buf = olchi_buf = uend_buf = qsrc_buf = nullptr;
+        olH_buf = olchi_buf = uend_buf = olun_buf = qsrc_buf = nullptr;
         src_on_buf = nullptr;
         tab_mat_buf = nullptr;
         tab_sig_buf = nullptr;
@@ -736,6 +737,7 @@ struct ugkwp_ctx {
         double* dH = model_array(olH_buf, (size_t)ncell);
         double* dchi = model_array(olchi_buf, (size_t)ncell);
         model_array(uend_buf, (size_t)ncell);
+        if (!tiled()) D.ol_un = model_array(olun_buf, (size_t)ncell);
         HIPCHK(hipMemcpyAsync(dH, H, sizeof(double) * ncell, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemcpyAsync(dchi, chi, sizeof(double) * ncell, hipMemcpyHostToDevice, st));
         HIPCHK(hipMemsetAsync(uend_buf, 0, sizeof(double) * ncell, st));

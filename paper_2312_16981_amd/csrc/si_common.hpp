@@ -18,7 +18,7 @@ __device__ inline double stim_factor(const Consts& K, double nu, double T)
 
 // Frequency factor of group g at temperature T: Simpson's mean of nu^-p over
 // the group, times the stimulated-emission factor when that is on.
-__device__ inline double group_factor(const Dev& D, const Consts& K, int edge_off, int g, double T)
+__device__ __forceinline__ double group_factor(const Dev& D, const Consts& K, int edge_off, int g, double T)
 {
     if (!K.stim) return D.simpson[edge_off + g];
     const double nl = D.nu[edge_off + g], nh = D.nu[edge_off + g + 1], nm = 0.5 * (nl + nh);
@@ -26,29 +26,60 @@ __device__ inline double group_factor(const Dev& D, const Consts& K, int edge_of
             + nu_pow(nh, K.nu_power) * stim_factor(K, nh, T)) * (1.0 / 6.0);
 }
 
-// Group opacity of material m at T from the table (Sec. 3.4-3.5's printed
-// opacities, tabulated by the caller): sigma is bilinear in (ln nu, ln T) on
-// ln sigma, constant beyond the end nodes, and the group value is Simpson's rule
-// over the group (edge index e = edge_off + g).  The nu intervals and weights of the group's
-// three Simpson points are fixed by the edges and read from tab_gi / tab_ga
+// Group opacity from the table (Sec. 3.4-3.5's printed opacities, tabulated by the
+// caller): sigma is bilinear in (ln nu, ln T) on ln sigma, constant beyond the end
+// nodes, and the group value is Simpson's rule over the group.  The nu intervals and
+// weights of the Simpson points are fixed by the edges and read from tab_gi / tab_ga
 // (k_tab_groups at set-up); only T is located here.
+struct TablePlace {
+    const double* row;     // ln sigma of the material at the T node below
+    double b;              // weight of the node above
+};
+
+__device__ inline TablePlace table_place(const Dev& D, const Consts& K, int m, double T)
+{
+    TablePlace p;
+    const int jt = table_locate_guess(D.tab_lT, K.tab_nT, log(T), K.tab_lT_inv, &p.b);
+    p.row = D.tab_lsig + ((int64_t)m * K.tab_nT + jt) * K.tab_nnu;
+    return p;
+}
+
+// sigma at Simpson point p (0 lower edge, 1 midpoint, 2 upper edge) of the group at edge e
+__device__ inline double table_point(const Dev& D, const Consts& K, TabPtr mt, const TablePlace& t, int e, int p)
+{
+    const double a = D.tab_ga[3 * e + p];
+    const double* L = t.row + D.tab_gi[3 * e + p];
+    const int n = K.tab_nnu;
+    const double lo = (1.0 - a) * L[0] + a * L[1], hi = (1.0 - a) * L[n] + a * L[n + 1];
+    return exp_neg(mt, -((1.0 - t.b) * lo + t.b * hi));
+}
+
+// of material m at T, the group at edge e = edge_off + g
 __device__ inline double table_group_sigma(const Dev& D, const Consts& K, int m, int e, double T)
 {
     const TabPtr mt = math_tab();
-    double b;
-    const int jt = table_locate_guess(D.tab_lT, K.tab_nT, log(T), K.tab_lT_inv, &b);
-    const int n = K.tab_nnu;
-    const double* L0 = D.tab_lsig + ((int64_t)m * K.tab_nT + jt) * n;
-    double v[3];
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-        const int i = D.tab_gi[3 * e + p];
-        const double a = D.tab_ga[3 * e + p];
-        const double* L = L0 + i;
-        const double lo = (1.0 - a) * L[0] + a * L[1], hi = (1.0 - a) * L[n] + a * L[n + 1];
-        v[p] = exp_neg(mt, -((1.0 - b) * lo + b * hi));
+    const TablePlace t = table_place(D, K, m, T);
+    const double v0 = table_point(D, K, mt, t, e, 0), v1 = table_point(D, K, mt, t, e, 1);
+    return (v0 + 4.0 * v1 + table_point(D, K, mt, t, e, 2)) * (1.0 / 6.0);
+}
+
+// The same for the groups of a cell in consecutive lanes (g of Gp, edges g <= G, `on` for
+// the whole cell), t the place of the cell's T: the upper edge is the next lane's lower
+// one.  Called by whole wavefronts; two exponentials and eight table loads a lane instead
+// of three and twelve.
+__device__ inline double table_group_sigma_lanes(const Dev& D, const Consts& K, const TablePlace& t, int edge_off,
+                                                 int g, int G, int Gp, bool on)
+{
+    const TabPtr mt = math_tab();
+    const int e = edge_off + g;
+    double v0 = 0.0, v1 = 0.0;
+    if (on && g <= G) {
+        v0 = table_point(D, K, mt, t, e, 0);
+        if (g < G) v1 = table_point(D, K, mt, t, e, 1);
     }
-    return (v[0] + 4.0 * v[1] + v[2]) * (1.0 / 6.0);
+    double v2 = next_lane(v0);
+    if (on && g == G - 1 && G == Gp) v2 = table_point(D, K, mt, t, e, 2);
+    return (v0 + 4.0 * v1 + v2) * (1.0 / 6.0);
 }
 
 // T^-q; the paper's q = 1/2 without pow().
@@ -65,6 +96,97 @@ __device__ inline bool source_on(const Consts& K, uint32_t step)
 __device__ inline double face_coef(const Consts& K, TabPtr t, double sf, double fc)
 {
     return fc * coef_c2_over_dt(t, s_of_sigma(K, sf));
+}
+
+// What a sweep forms the opacity from: fixed tables, a power of the iterate's
+// temperature with the stimulated-emission factor, or the opacity table.  OP_POWER also
+// stands for Olson's heat capacity alone.  (Kept apart at compile time: pow() and the
+// table's look-up together cost a sweep 64 to 140 spilled scalar registers.)
+enum { OP_FIXED, OP_POWER, OP_TABLE };
+
+__host__ inline int opacity_form(const Consts& K)
+{
+    return K.table ? OP_TABLE : (K.t_power != 0.0 || K.stim || K.olson) ? OP_POWER : OP_FIXED;
+}
+
+// What a slot's opacity is formed from.
+struct SlotMat {
+    double kap;
+    int mat;
+};
+
+// sigma of the group at edge + g, at T (group_factor's frequency part included)
+template <int OP>
+__device__ __forceinline__ double slot_sigma(const Dev& D, const Consts& K, const SlotMat& s, int edge, int g, double T)
+{
+    if (OP == OP_TABLE) return table_group_sigma(D, K, s.mat, edge + g, T);
+    return s.kap * temp_pow(T, K.t_power) * group_factor(D, K, edge, g, T);
+}
+
+// Opacity of a face between cells of opacity a and b.
+__device__ inline double face_sigma(double a, double b) { return (a + b > 0.0) ? 2.0 * (a * b) / (a + b) : 0.0; }
+
+// What a cell's energy equation is solved from: T^n, the iterate T^k, dt / C_v (or
+// Olson's H and chi and the material energy U(T^n)).
+struct CellHeat {
+    double Tn, Tk, dtcv, H, chi, un;
+    bool pinned;
+};
+
+// T^{k+1} of a cell from the exchange summed over its groups and (LIN) its derivative;
+// *uend gets Olson's material energy.  Olson's heat capacity: the energy equation in the
+// material energy U, U(T^{n+1}) = U(T^n) + exchange.  Literal: U(T^{k+1}) = U(T^n) +
+// exchange(phi^k), solved for T^{k+1}; linearized: one Newton step at T^k with U and the
+// emission linearized, whose material energy is U(T^k) + C_v(T^k)(T^{k+1} - T^k).
+// uk, ck: U and C_v at T^k (linearized, with Olson's heat capacity).
+template <bool TDEP, bool LIN>
+__device__ inline double cell_temperature(const Consts& K, const CellHeat& c, double uk, double ck, double contrib,
+                                          double dcon, double* uend)
+{
+    if (TDEP && c.H > 0.0) {
+        if (c.pinned) {
+            *uend = c.un;
+            return c.Tn;
+        }
+        const double wdt = K.dt / (K.eps * K.eps);
+        if (LIN) {
+            const double T = c.Tk + (c.un - uk + wdt * contrib) / (ck + wdt * dcon);
+            *uend = uk + ck * (T - c.Tk);
+            return T;
+        }
+        *uend = c.un + wdt * contrib;
+        return olson_temperature(c.H, c.chi, *uend, c.Tk);
+    }
+    if (c.pinned) return c.Tn;
+    return LIN ? c.Tk + (c.Tn - c.Tk + c.dtcv * contrib) / (1.0 + c.dtcv * dcon) : c.Tn + c.dtcv * contrib;
+}
+
+// The same with U(T^k) and C_v(T^k) evaluated here.
+template <bool TDEP, bool LIN>
+__device__ inline double cell_temperature(const Consts& K, const CellHeat& c, double contrib, double dcon, double* uend)
+{
+    double uk = 0.0, ck = 0.0;
+    if (TDEP && LIN && c.H > 0.0) {
+        uk = olson_energy(c.H, c.chi, c.Tk);
+        ck = olson_cv(c.H, c.chi, c.Tk);
+    }
+    return cell_temperature<TDEP, LIN>(K, c, uk, ck, contrib, dcon, uend);
+}
+
+// Residual sub-slots of a 2-D sweep k for instance inst: [RES_SLOTS][n_inst][RES_SUB],
+// so that the slots of sweep 0 form one range cleared at the start of a step.
+__device__ inline Resid* res_slot(const Dev& D, const Consts& K, int inst, int k)
+{
+    return D.res + ((int64_t)(k % RES_SLOTS) * K.n_inst + inst) * RES_SUB;
+}
+
+// The stopping test by one wavefront, r the sub-slot of each lane: max|rho^{k+1} - rho^k|
+// <= si_tol max|rho^{k+1}| and max|T^{k+1} - T^k| <= si_tol max T^{k+1} (Algorithm 2).
+__device__ inline bool resid_converged(const Consts& K, const Resid& r)
+{
+    const double drho = bitsd(wave_max_bits(bitsd(r.drho))), mrho = bitsd(wave_max_bits(bitsd(r.rho)));
+    const double dT = bitsd(wave_max_bits(bitsd(r.dT))), mT = bitsd(wave_max_bits(bitsd(r.T)));
+    return drho <= K.si_tol * mrho && dT <= K.si_tol * mT;
 }
 
 __device__ inline double minmod_diff(double a, double b)

@@ -17,28 +17,6 @@
 
 namespace ugk {
 
-// What the temperature-dependent opacity of a slot is formed from.
-struct SlotMat {
-    double kap;
-    int mat;
-};
-
-__device__ inline SlotMat slot_mat(const Dev& D, const Consts& K, int64_t j, int cell)
-{
-    SlotMat s = {0.0, 0};
-    if (K.table) s.mat = D.tab_mat[cell];
-    else s.kap = D.kappa[j];
-    return s;
-}
-
-__device__ inline double slot_sigma(const Dev& D, const Consts& K, const SlotMat& s, int edge, int g, double T)
-{
-    if (K.table) return table_group_sigma(D, K, s.mat, edge + g, T);
-    return s.kap * temp_pow(T, K.t_power) * group_factor(D, K, edge, g, T);
-}
-
-__device__ inline double face_sigma(double a, double b) { return (a + b > 0.0) ? 2.0 * (a * b) / (a + b) : 0.0; }
-
 template <bool LIN, bool REG>
 struct TileTab {
     RegTab r;
@@ -83,15 +61,16 @@ __device__ inline WaveStatic wave_static(const Dev& D, const Consts& K, const In
     return w;
 }
 
-// FIRST: round 0, which also evaluates the wave flux and Q; TDEP: the opacity
-// (and Olson's heat capacity) follow the iterate; LIN: the linearized sweep;
+// FIRST: round 0, which also evaluates the wave flux and Q; OP: how the opacity
+// (and Olson's heat capacity) follows the iterate; LIN: the linearized sweep;
 // EXT: slope terms and boundary-source ghosts in the wave flux; WIT: the wave flux of
 // every sweep k >= 1 from its iterate (its cells reach two further with slopes, and the
 // rounds after the first one more, K.tile_H in all); CPT cells per thread; REG: the
 // Planck coefficients in registers (TileTab).
-template <bool FIRST, bool SINGLE, bool TDEP, bool LIN, bool EXT, bool WIT, int CPT, bool REG>
-__global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, Consts K, int round)
+template <bool FIRST, bool SINGLE, int OP, bool LIN, bool EXT, bool WIT, int CPT, bool REG>
+__global__ __launch_bounds__(tile_max_threads(OP != OP_FIXED, REG)) void k_si_tile(Dev D, Consts K, int round)
 {
+    constexpr bool TDEP = OP != OP_FIXED, TABLE = OP == OP_TABLE;
     extern __shared__ double lds[];
     __shared__ unsigned long long lres[TILE_S_MAX][4][WAVE];    // residual maxima per sweep and lane
     __shared__ int dec[TILE_S_MAX + 1];
@@ -165,10 +144,10 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
     const double pbh = active && I.bc[XHI] == BC_PLANCK ? D.phib[((int64_t)inst * 4 + XHI) * MAX_G + g] : 0.0;
 
     double phi[CPT], rho[CPT], Q[CPT], lam[CPT], rl[CPT], sig[CPT], Dl[CPT], Dh[CPT];
-    double Tn[CPT], Tk[CPT], dtcv[CPT], olH[CPT], olchi[CPT], dph[CPT], infl[CPT];
+    double dph[CPT], infl[CPT];
+    CellHeat ht[CPT];
     WaveStatic ws[CPT];
     SlotMat mat[CPT];
-    bool pin[CPT];
     int mlim[CPT];
     // every load first
 #pragma unroll
@@ -177,26 +156,27 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
         const bool ok = ix >= 0 && ix < nx, act = ok && active;
         const int64_t j = I.cg_off + ((int64_t)ix << I.lgGp) + g;
         const int cell = I.cell_off + ix;
-        phi[r] = rho[r] = Q[r] = lam[r] = sig[r] = Dl[r] = Dh[r] = dtcv[r] = olH[r] = olchi[r] = dph[r] = 0.0;
+        phi[r] = rho[r] = Q[r] = lam[r] = sig[r] = Dl[r] = Dh[r] = dph[r] = 0.0;
         infl[r] = 0.0;
-        rl[r] = Tn[r] = Tk[r] = 1.0;
+        rl[r] = 1.0;
+        ht[r] = {1.0, 1.0, 0.0, 0.0, 0.0, 0.0, false};
         mat[r].kap = 0.0;
         mat[r].mat = 0;
-        pin[r] = false;
         ws[r] = WaveStatic{};
         mlim[r] = ok ? TILE_S_MAX : -1;
         if (ok && c0 > 0) mlim[r] = min(mlim[r], ci / reach - behind);
         if (ok && c0 + C < nx) mlim[r] = min(mlim[r], (C - 1 - ci) / reach - behind);
         double beyond = 0.0, sbeyond = 0.0;      // phi and sigma of the cell beyond the tile's end
         if (ok) {
-            Tn[r] = D.T[cell];
-            Tk[r] = FIRST ? Tn[r] : T_in[cell];
-            pin[r] = D.pinned[cell] != 0;
-            dtcv[r] = D.dtcv[cell];
+            ht[r].Tn = D.T[cell];
+            ht[r].Tk = FIRST ? ht[r].Tn : T_in[cell];
+            ht[r].pinned = D.pinned[cell] != 0;
+            ht[r].dtcv = D.dtcv[cell];
             if (TDEP && K.olson) {
-                olH[r] = D.olH[cell];
-                olchi[r] = D.olchi[cell];
+                ht[r].H = D.olH[cell];
+                ht[r].chi = D.olchi[cell];
             }
+            if (TABLE) mat[r].mat = D.tab_mat[cell];
         }
         if (act) {
             phi[r] = phi_in[j];
@@ -204,7 +184,7 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
             if (!FIRST && !WIT) Q[r] = D.Q[j];
             if (WIT) ws[r] = wave_static(D, K, I, j, ix, g, ix == 0 ? pbl : 0.0, ix == nx - 1 ? pbh : 0.0);
             if (TDEP) {
-                mat[r] = slot_mat(D, K, j, cell);
+                if (!TABLE) mat[r].kap = D.kappa[j];
             } else {
                 lam[r] = D.sv[j];
                 sig[r] = D.sig[j];
@@ -217,9 +197,12 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
                 const int64_t jb = j + (el ? -Gp : Gp);
                 const int cb = cell + (el ? -1 : 1);
                 beyond = phi_in[jb];
-                if (TDEP) sbeyond = FIRST ? D.sig[jb] : slot_sigma(D, K, slot_mat(D, K, jb, cb), I.edge_off, g, T_in[cb]);
+                SlotMat nb = {0.0, 0};
+                if (TABLE) nb.mat = D.tab_mat[cb];
+                else if (TDEP) nb.kap = D.kappa[jb];
+                if (TDEP) sbeyond = FIRST ? D.sig[jb] : slot_sigma<OP>(D, K, nb, I.edge_off, g, T_in[cb]);
             }
-            if (TDEP) sig[r] = FIRST ? D.sig[j] : slot_sigma(D, K, mat[r], I.edge_off, g, Tk[r]);
+            if (TDEP) sig[r] = FIRST ? D.sig[j] : slot_sigma<OP>(D, K, mat[r], I.edge_off, g, ht[r].Tk);
         }
         // the ghosts' values stay in both rows (no cell's update writes there)
         const int l = ((ci + 1) << I.lgGp) + g;
@@ -251,16 +234,18 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
         }
         if (LIN) {
             const TabPtr mt = math_tab();
-            const double we = ok && g <= G ? planck_edge_weight(mt, nu_lo / Tk[r]) : 0.0;
+            const double we = ok && g <= G ? planck_edge_weight(mt, nu_lo / ht[r].Tk) : 0.0;
             double wh = next_lane(we);
-            if (ok && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / Tk[r]);
-            if (act) dph[r] = 4.0 * phi[r] / Tk[r] + K.a * K.c * (Tk[r] * Tk[r] * Tk[r]) * (we - wh) * UGK_15_PI4;
+            if (ok && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / ht[r].Tk);
+            if (act) dph[r] = 4.0 * phi[r] / ht[r].Tk + K.a * K.c * (ht[r].Tk * ht[r].Tk * ht[r].Tk) * (we - wh) * UGK_15_PI4;
         }
     }
     __syncthreads();
 
     const TileTab<LIN, REG> tab;
-    const double wdt = K.dt / (K.eps * K.eps);
+    if (TDEP && K.olson)
+#pragma unroll
+        for (int r = 0; r < CPT; ++r) ht[r].un = olson_energy(ht[r].H, ht[r].chi, ht[r].Tn);
     int cur = 0;
     for (int m = 0; m < rd.ns; ++m) {
         const double* Pc = Lphi + cur * row;
@@ -365,25 +350,9 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
             double Tnew = 1.0, uend = 0.0;
             bool bad = false;
             if (work) {
-                if (TDEP && olH[r] > 0.0) {
-                    // Olson's heat capacity: U(T^{n+1}) = U(T^n) + exchange; linearized, one
-                    // Newton step at T^k with U and the emission linearized
-                    const double un = olson_energy(olH[r], olchi[r], Tn[r]);
-                    if (pin[r]) {
-                        Tnew = Tn[r];
-                        uend = un;
-                    } else if (LIN) {
-                        const double uk = olson_energy(olH[r], olchi[r], Tk[r]), ck = olson_cv(olH[r], olchi[r], Tk[r]);
-                        Tnew = Tk[r] + (un - uk + wdt * contrib) / (ck + wdt * dcon);
-                        uend = uk + ck * (Tnew - Tk[r]);
-                    } else {
-                        uend = un + wdt * contrib;
-                        Tnew = olson_temperature(olH[r], olchi[r], uend, Tk[r]);
-                    }
-                } else if (LIN) Tnew = pin[r] ? Tn[r] : Tk[r] + (Tn[r] - Tk[r] + dtcv[r] * contrib) / (1.0 + dtcv[r] * dcon);
-                else Tnew = pin[r] ? Tn[r] : Tn[r] + dtcv[r] * contrib;
+                Tnew = cell_temperature<TDEP, LIN>(K, ht[r], contrib, dcon, &uend);
                 if (LIN && active) {
-                    const double pe = pin[r] ? phi[r] : phi[r] + dph[r] * (Tnew - Tk[r]);
+                    const double pe = ht[r].pinned ? phi[r] : phi[r] + dph[r] * (Tnew - ht[r].Tk);
                     rr = quotient(b + lam[r] * pe, 1.0 + lam[r], rl[r]);
                 }
                 if (!(Tnew > 0.0) || !isfinite(Tnew)) {
@@ -424,19 +393,23 @@ __global__ __launch_bounds__(tile_max_threads(TDEP, REG)) void k_si_tile(Dev D, 
                 phi[r] = pn;
                 Pn[l] = pn;
                 if (LIN) dph[r] = 4.0 * pn / Tnew + K.a * K.c * (Tnew * Tnew * Tnew) * (we - wh) * UGK_15_PI4;
-                if (TDEP && m + 1 < rd.ns) {
-                    sig[r] = slot_sigma(D, K, mat[r], I.edge_off, g, Tnew);
-                    Sn[l] = sig[r];
-                }
+            }
+            if (TDEP && m + 1 < rd.ns) {
+                if (TABLE) {
+                    TablePlace t = {nullptr, 0.0};
+                    if (work) t = table_place(D, K, mat[r].mat, Tnew);
+                    sig[r] = table_group_sigma_lanes(D, K, t, I.edge_off, g, G, Gp, work);
+                } else if (act) sig[r] = slot_sigma<OP>(D, K, mat[r], I.edge_off, g, Tnew);
+                if (act) Sn[l] = sig[r];
             }
             if (inner && g == 0) {
                 const int cell = I.cell_off + ix;
                 T_out[cell] = Tnew;
-                if (TDEP && olH[r] > 0.0) (final ? D.uend : D.tile_u + (int64_t)at * K.ncell)[cell] = uend;
-                dT = nan_max(dT, fabs(Tnew - Tk[r]));
+                if (TDEP && ht[r].H > 0.0) (final ? D.uend : D.tile_u + (int64_t)at * K.ncell)[cell] = uend;
+                dT = nan_max(dT, fabs(Tnew - ht[r].Tk));
                 mT = nan_max(mT, bad ? __builtin_nan("") : Tnew);
             }
-            if (work) Tk[r] = Tnew;
+            if (work) ht[r].Tk = Tnew;
         }
         // the sweep's residual maxima per lane (non-negative or NaN, ordered by their
         // bits) over the block's wavefronts; a reduction over the lanes in every
@@ -478,55 +451,56 @@ __global__ void k_tile_decide(Dev D, Consts K, int round)
 // ---------------------------------------------------------------------------
 // launchers
 
-template <bool FIRST, bool SINGLE, bool TDEP, bool LIN, bool EXT, bool WIT>
+template <bool FIRST, bool SINGLE, int OP, bool LIN, bool EXT, bool WIT>
 static void tile_launch(const Dev& D, const Consts& K, int round, hipStream_t st)
 {
     const int gmax = SINGLE ? K.inst0.Gp : MAX_G;
-    const size_t rows = 2 + (TDEP ? 2 : 0) + (WIT ? 3 : 0);
+    const size_t rows = 2 + (OP != OP_FIXED ? 2 : 0) + (WIT ? 3 : 0);
     const size_t lds = (size_t)(K.tile_threads * K.tile_cpt + 2 * gmax) * rows * sizeof(double);
     if constexpr (SINGLE) {
-        if constexpr (!WIT && !TDEP) {
+        if constexpr (!WIT && OP == OP_FIXED) {
             if (K.tile_reg) {
-                k_si_tile<FIRST, true, TDEP, LIN, EXT, false, 1, true><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
+                k_si_tile<FIRST, true, OP, LIN, EXT, false, 1, true><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
                 return;
             }
         }
-        k_si_tile<FIRST, true, TDEP, LIN, EXT, WIT, 1, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
+        k_si_tile<FIRST, true, OP, LIN, EXT, WIT, 1, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
     } else {
-        k_si_tile<FIRST, false, TDEP, LIN, EXT, WIT, 2, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
+        k_si_tile<FIRST, false, OP, LIN, EXT, WIT, 2, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
     }
 }
 
-template <bool SINGLE, bool TDEP, bool LIN>
+template <bool SINGLE, int OP, bool LIN>
 static void tile_mode(const Dev& D, const Consts& K, int round, hipStream_t st)
 {
     const bool ext = (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) != 0;
     if (K.flags & UGKWP_FLAG_WAVE_ITER) {
-        if (round == 0) tile_launch<true, SINGLE, TDEP, LIN, true, true>(D, K, round, st);
-        else tile_launch<false, SINGLE, TDEP, LIN, true, true>(D, K, round, st);
+        if (round == 0) tile_launch<true, SINGLE, OP, LIN, true, true>(D, K, round, st);
+        else tile_launch<false, SINGLE, OP, LIN, true, true>(D, K, round, st);
     } else if (round > 0) {
-        tile_launch<false, SINGLE, TDEP, LIN, false, false>(D, K, round, st);
+        tile_launch<false, SINGLE, OP, LIN, false, false>(D, K, round, st);
     } else if (ext) {
-        tile_launch<true, SINGLE, TDEP, LIN, true, false>(D, K, round, st);
+        tile_launch<true, SINGLE, OP, LIN, true, false>(D, K, round, st);
     } else {
-        tile_launch<true, SINGLE, TDEP, LIN, false, false>(D, K, round, st);
+        tile_launch<true, SINGLE, OP, LIN, false, false>(D, K, round, st);
     }
 }
 
 void launch_si_rounds(const Dev& D, const Consts& K, int r0, int r1, hipStream_t st)
 {
     const bool lin = (K.flags & UGKWP_FLAG_SI_LINEARIZED) != 0;
-    const bool tdep = K.t_power != 0.0 || K.stim || K.table || K.olson;
+    const int op = opacity_form(K);
     for (int r = r0; r < r1; ++r) {
         if (K.n_inst == 1) {
-            if (tdep) lin ? tile_mode<true, true, true>(D, K, r, st) : tile_mode<true, true, false>(D, K, r, st);
-            else lin ? tile_mode<true, false, true>(D, K, r, st) : tile_mode<true, false, false>(D, K, r, st);
+            if (op == OP_TABLE) lin ? tile_mode<true, OP_TABLE, true>(D, K, r, st) : tile_mode<true, OP_TABLE, false>(D, K, r, st);
+            else if (op == OP_POWER) lin ? tile_mode<true, OP_POWER, true>(D, K, r, st) : tile_mode<true, OP_POWER, false>(D, K, r, st);
+            else lin ? tile_mode<true, OP_FIXED, true>(D, K, r, st) : tile_mode<true, OP_FIXED, false>(D, K, r, st);
         } else {
-            if (tdep) lin ? tile_mode<false, true, true>(D, K, r, st) : tile_mode<false, true, false>(D, K, r, st);
-            else lin ? tile_mode<false, false, true>(D, K, r, st) : tile_mode<false, false, false>(D, K, r, st);
-        }
-        if (K.n_inst > 1)
+            if (op == OP_TABLE) lin ? tile_mode<false, OP_TABLE, true>(D, K, r, st) : tile_mode<false, OP_TABLE, false>(D, K, r, st);
+            else if (op == OP_POWER) lin ? tile_mode<false, OP_POWER, true>(D, K, r, st) : tile_mode<false, OP_POWER, false>(D, K, r, st);
+            else lin ? tile_mode<false, OP_FIXED, true>(D, K, r, st) : tile_mode<false, OP_FIXED, false>(D, K, r, st);
             k_tile_decide<<<(unsigned)((K.n_inst * WAVE + 255) / 256), 256, 0, st>>>(D, K, r);
+        }
     }
 }
 

@@ -898,10 +898,11 @@ __device__ inline double cell_tau(const Dev& D, const Consts& K, const Geo& I, d
     return t;
 }
 
+template <int DIM>
 __device__ inline void draw_flight(const Consts& K, const Geo& I, uint64_t id, uint32_t step, Flight& f)
 {
     double u;
-    if ((f.d & 1u) == 0) keyed_uniform_pair(I.seed, id, step, PURPOSE_FLIGHT, f.d, u, f.u_odd);
+    if ((f.d & 1u) == 0) keyed_uniform_pair<DIM == 1>(I.seed, id, step, PURPOSE_FLIGHT, f.d, u, f.u_odd);
     else u = f.u_odd;                  // the first crossing's draw: no second Philox evaluation
     f.d++;
     const double room = K.dt - f.t;
@@ -912,7 +913,7 @@ __device__ inline void draw_flight(const Consts& K, const Geo& I, uint64_t id, u
         f.t_rem = room;
         return;
     }
-    const double a = f.tau * neg_log_unit(u);
+    const double a = f.tau * neg_log_unit<DIM == 2>(u);
     f.coll = a < room;
     f.t_rem = f.coll ? a : room;
 }
@@ -996,7 +997,7 @@ __device__ inline int fly(const Dev& D, const Consts& K, const Geo& I, TallyTabl
         lds_tally(T, D, type, index, w);
         if (xaxis) f.ix += pos ? 1 : -1; else f.iy += pos ? 1 : -1;
         f.tau = cell_tau<SM>(D, K, I, tfac, f.iy * I.nx + f.ix, g, nu, f);
-        draw_flight(K, I, id, step, f);
+        draw_flight<DIM>(K, I, id, step, f);
     }
 }
 
@@ -1055,7 +1056,7 @@ __device__ inline bool enter_from_ghost(const Dev& D, const Consts& K, const Geo
     lds_tally(T, D, type, index, w);
     f.t = te;
     f.tau = cell_tau<SM>(D, K, I, tfac, f.iy * I.nx + f.ix, g, nu, f);
-    draw_flight(K, I, id, step, f);
+    draw_flight<DIM>(K, I, id, step, f);
     return true;
 }
 
@@ -1124,13 +1125,9 @@ constexpr int push_min_waves()
 #ifndef UGK_PUSH_ATTR
 #define UGK_PUSH_ATTR __attribute__((amdgpu_waves_per_eu(push_min_waves<DIM, SINGLE, SM>())))
 #endif
-#ifndef UGK_PUSH_PREFETCH_2D
-#define UGK_PUSH_PREFETCH_2D 1
-#endif
 template <int DIM, bool SINGLE, int SM, int BS>
 __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool In, Pool Out, int ppt)
 {
-    constexpr bool PUSH_PREFETCH = DIM == 2 && UGK_PUSH_PREFETCH_2D;
     if (!gate_open(D, K, 0)) return;
     const uint32_t step = *D.step;
     __shared__ TallyTable T;
@@ -1158,14 +1155,12 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
             T.val[h] = 0.0;
         }
         __syncthreads();
-        // 2-D: the records of the next round are read while this round's flights
-        // run (1-D: the registers this takes would cost a wavefront per SIMD)
+        // the records of the next round are read while this round's flights run (1.3
+        // million particles of a slab: 32.0 us with the records read at their round's
+        // start, 30.5 so; 256 slabs: 56 and 51 us)
         const int64_t cend = min(c0 + chunk, n_total);
         PoolRec<DIM> nxt;
-        if (PUSH_PREFETCH) {
-            const int64_t i0 = c0 + threadIdx.x;
-            if (i0 < cend) nxt.load(In, (uint32_t)i0);
-        }
+        if (c0 + threadIdx.x < cend) nxt.load(In, (uint32_t)(c0 + threadIdx.x));
 #pragma unroll 1
         for (int r = 0; r < nloop; ++r) {
             const int64_t i = c0 + (int64_t)r * BS + threadIdx.x;
@@ -1174,13 +1169,8 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
             bool has = false;
             uint32_t tkey = 0u;
             double tw = 0.0;
-            PoolRec<DIM> cur;
-            if (PUSH_PREFETCH) {
-                cur = nxt;
-                if (r + 1 < nloop && i + BS < cend) nxt.load(In, iu + BS);
-            } else if (i < cend) {
-                cur.word = ldnt(In.cell, iu);      // the rest only for a live slot
-            }
+            const PoolRec<DIM> cur = nxt;
+            if (r + 1 < nloop && i + BS < cend) nxt.load(In, iu + BS);
             const int32_t word = cur.word;
             const int cell = word & CELL_MASK;
             if (i >= cend) {
@@ -1191,17 +1181,6 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
                 atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_RECORD);
                 stnt(Out.cell, iu, DEAD);
             } else {
-                if (!PUSH_PREFETCH) {
-                    cur.idw = ldnt(In.id, iu);
-                    cur.x = ldnt(In.x, iu);
-                    cur.ox = ldnt(In.ox, iu);
-                    if (DIM == 2) {
-                        cur.y = ldnt(In.y, iu);
-                        cur.oy = ldnt(In.oy, iu);
-                    }
-                    cur.nu = ldnt(In.nu, iu);
-                    cur.w = ldnt(In.w, iu);
-                }
                 const int32_t gword = (int32_t)(cur.idw >> ID_BITS);
                 const int g = gword & GROUP_MASK;
                 const int gside = gword >> GHOST_SHIFT;    // boundary-source particle: 1 + ghost side
@@ -1244,7 +1223,7 @@ __global__ __launch_bounds__(BS) UGK_PUSH_ATTR void k_push(Dev D, Consts K, Pool
                         // entered: its flight is drawn; the group word loses the ghost mark
                         at(In.id, iu) = id | ((uint64_t)g << ID_BITS);
                     } else if (i < n_slots) {
-                        draw_flight(K, I, id, step, f);             // old particle: t_f = min(-tau ln eta, dt)
+                        draw_flight<DIM>(K, I, id, step, f);             // old particle: t_f = min(-tau ln eta, dt)
                     } else {
                         f.coll = false;                             // new collisionless particle: t_f = dt
                         f.t_rem = K.dt;

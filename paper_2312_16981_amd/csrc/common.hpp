@@ -21,6 +21,7 @@ constexpr int TILE_S_MAX = 8;    // most source-iteration sweeps per launch (1-D
 
 // Threads per tile block: the sweeps that follow the opacity and those that keep the
 // Planck coefficients in registers hold too many for 16 wavefronts per CU.
+constexpr int TILE_BATCH_THREADS = 512;     // a batch's tiles
 constexpr int tile_max_threads(bool tdep, bool reg) { return tdep || reg ? 512 : 1024; }
 
 enum { BC_VACUUM = 0, BC_PLANCK = 1, BC_REFLECT = 2 };

@@ -1852,7 +1852,7 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     if (faces_early) load_faces();
     __shared__ int dec[TILE_S_MAX + 1];
     if (tiled && SINGLE) tile_gather(D, K, last_sweep, dec);
-    const int s0 = tiled ? __builtin_amdgcn_readfirstlane(tile_first(K, prev_sweeps)) : 0;
+    const TilePlan plan = tile_plan(K, __builtin_amdgcn_readfirstlane(prev_sweeps));
     // the commit below advances *D.step while other blocks may still start:
     // both the step's own value and the next one open this launch
     if (!(K.gate == GATE_OFF || now == K.gate || now == K.gate + 1)) return;
@@ -1874,7 +1874,7 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     int ns_single = 0;
     if (tiled && SINGLE) {
         __syncthreads();
-        ns_single = tile_outcome(K, last_sweep, s0, dec);
+        ns_single = tile_outcome(K, last_sweep, plan, dec);
         if (blockIdx.x == 0 && threadIdx.x == 0 && ns_single != 0 && dec[TILE_S_MAX] == 0) tile_record(D, 0, ns_single);
         if (err0 != 0 || ns_single <= 0) return;
     } else if (!tiled && last_sweep >= 0) {
@@ -1934,9 +1934,9 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
         // the iterate lies in place unless the step took another number of sweeps
         // than its first round; the last sweep's input matters on the boundary and
         // in pinned cells only
-        const TileOut o = tile_out(K, s0, ns_tiled - 1);
+        const TileOut o = tile_out(K, plan, ns_tiled - 1);
         if (pin || bnd[0] || bnd[1]) {
-            const TileOut q = tile_out(K, s0, ns_tiled - 2);
+            const TileOut q = tile_out(K, plan, ns_tiled - 2);
             phi = (ns_tiled == 1 ? D.phi0 : (q.final ? D.phi0n : D.tile_phi + (int64_t)q.at * K.n_cg))[j];
             Tf = (o.final ? D.T_new : D.tile_T + (int64_t)o.at * K.ncell)[cell];
             if (witer && (bnd[0] || bnd[1]))

@@ -559,7 +559,7 @@ struct ugkwp_ctx {
     // together leave room in 64 KiB of LDS for blocks of half the size.
     void batch_tiles(Dev& d)
     {
-        K.tile_threads = tile_wit() && tile_tdep() ? 256 : 512;
+        K.tile_threads = tile_wit() && tile_tdep() ? TILE_BATCH_THREADS / 2 : TILE_BATCH_THREADS;
         K.tile_cpt = 2;
         K.tile_H = tile_halo(K.tile_S);
         std::vector<int2> blk;
@@ -609,19 +609,22 @@ struct ugkwp_ctx {
             }
     }
 
-    // Launches that take `sweeps` sweeps: sweeps themselves, or rounds of tiles (a
-    // batch's first round takes what each instance needed before: one round more).
-    int sweep_launches(int sweeps) const
+    // Launches that take one sweep more than `last`: sweeps themselves, or rounds of tiles
+    // (a batch's first two rounds end where each instance's iteration ended before).
+    int sweep_launches(int last) const
     {
-        if (!tiled()) return std::min(sweeps, P.si_max_iters);
-        if (n_inst == 1) return (sweeps + K.tile_S - 1) / K.tile_S;
-        return 1 + (std::max(sweeps - K.tile_S, 1) + K.tile_S - 1) / K.tile_S;
+        const int S = K.tile_S;
+        if (!tiled()) return std::min(last + 1, P.si_max_iters);
+        if (n_inst == 1) return (last + S) / S;
+        return last <= S ? 2 : 3 + std::max(last - 2 * S, 0) / S;
     }
 
     // whether n launches have taken as many sweeps as the iteration may
     bool sweeps_spent(int n) const
     {
-        return tiled() ? 1 + (int64_t)(n - 1) * K.tile_S >= P.si_max_iters : n >= P.si_max_iters;
+        if (!tiled()) return n >= P.si_max_iters;
+        const int few = n_inst > 1 ? 2 : 1;      // rounds that may be of a single sweep
+        return std::min(n, few) + (int64_t)std::max(n - few, 0) * K.tile_S >= P.si_max_iters;
     }
 
     // point D's record entries at record `slot`, the record before it at `prev`
@@ -1225,7 +1228,7 @@ struct ugkwp_ctx {
             if (ids_used + (uint64_t)m * (uint64_t)P.pool_capacity > ID_MASK)
                 fail(UGKWP_EPOOL, "particle ids would pass 2^%d", ID_BITS);
             plan_tiles(last_sweeps + 1);
-            const int spec = sweep_launches(last_sweeps + 1);
+            const int spec = sweep_launches(last_sweeps);
             // plan and enqueue
             const Plan start = state_now();
             std::vector<Plan> plan;

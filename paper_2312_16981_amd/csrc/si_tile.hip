@@ -68,7 +68,7 @@ __device__ inline WaveStatic wave_static(const Dev& D, const Consts& K, const In
 // rounds after the first one more, K.tile_H in all); CPT cells per thread; REG: the
 // Planck coefficients in registers (TileTab).
 template <bool FIRST, bool SINGLE, int OP, bool LIN, bool EXT, bool WIT, int CPT, bool REG>
-__global__ __launch_bounds__(tile_max_threads(OP != OP_FIXED, REG)) void k_si_tile(Dev D, Consts K, int round)
+__global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TILE_BATCH_THREADS) void k_si_tile(Dev D, Consts K, int round)
 {
     constexpr bool TDEP = OP != OP_FIXED, TABLE = OP == OP_TABLE;
     extern __shared__ double lds[];
@@ -90,11 +90,11 @@ __global__ __launch_bounds__(tile_max_threads(OP != OP_FIXED, REG)) void k_si_ti
         tile = __builtin_amdgcn_readfirstlane(bt.y);
         I = D.inst[inst];
     }
-    const int s0 = tile_first(K, D.prev_ist[inst].conv_sweeps);
+    const TilePlan plan = tile_plan(K, D.prev_ist[inst].conv_sweeps);
     if (!FIRST) {
         if (SINGLE) {
             __syncthreads();
-            const int out = tile_outcome(K, round - 1, s0, dec);
+            const int out = tile_outcome(K, round - 1, plan, dec);
             if (out != 0) {
                 if (blockIdx.x == 0 && threadIdx.x == 0 && dec[TILE_S_MAX] == 0) tile_record(D, 0, out);
                 return;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(tile_max_threads(OP != OP_FIXED, REG)) void k_si_ti
             return;
         }
     }
-    const TileRound rd = tile_round(K, s0, round);
+    const TileRound rd = tile_round(K, plan, round);
     if (rd.ns == 0) return;
     if (FIRST && blockIdx.x == 0 && threadIdx.x == 0 && K.has_src) *D.src_on = source_on(K, now) ? 1 : 0;
     for (int q = threadIdx.x; q < rd.ns * 4 * WAVE; q += blockDim.x) lres[0][0][q] = 0ull;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(tile_max_threads(OP != OP_FIXED, REG)) void k_si_ti
     const double* rho_in = D.rho;
     const double* T_in = D.T;
     if (!FIRST) {
-        const TileOut o = tile_out(K, s0, rd.k0 - 1);
+        const TileOut o = tile_out(K, plan, rd.k0 - 1);
         phi_in = o.final ? D.phi0n : D.tile_phi + o.at * ncg;
         rho_in = o.final ? D.rho_new : D.tile_rho + o.at * ncg;
         T_in = o.final ? D.T_new : D.tile_T + (int64_t)o.at * K.ncell;
@@ -252,8 +252,8 @@ __global__ __launch_bounds__(tile_max_threads(OP != OP_FIXED, REG)) void k_si_ti
         const double* Sc = Lsig + cur * row;
         double* Pn = Lphi + (cur ^ 1) * row;
         double* Sn = Lsig + (cur ^ 1) * row;
-        // the sweep's output: in place for the last of round 0, else its plane
-        const bool final = round == 0 && m == rd.ns - 1;
+        // the sweep's output: in place, or its plane
+        const bool final = rd.k0 + m == plan.fin;
         const int at = (round & 1) * K.tile_cap + m;
         double* const rho_out = final ? D.rho_new : D.tile_rho + at * ncg;
         double* const phi_out = final ? D.phi0n : D.tile_phi + at * ncg;
@@ -438,7 +438,7 @@ __global__ void k_tile_decide(Dev D, Consts K, int round)
     const int inst = blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE;
     const int lane = threadIdx.x & (WAVE - 1);
     if (inst >= K.n_inst || D.ist[inst].conv_sweeps != 0) return;
-    const TileRound q = tile_round(K, tile_first(K, D.prev_ist[inst].conv_sweeps), round);
+    const TileRound q = tile_round(K, tile_plan(K, D.prev_ist[inst].conv_sweeps), round);
     const int b0 = D.tile_start[inst], b1 = D.tile_start[inst + 1];
     for (int m = 0; m < q.ns; ++m) {
         const int v = tile_test(D, K, round, m, b0, b1, lane);

@@ -6,10 +6,9 @@
 // consecutive cells: K.tile_H cells on either side of its interior are
 // computed along (fewer each sweep), so that no block waits for another.  The
 // number of sweeps is known only once the whole instance's residuals are, so
-// every sweep of a round keeps its output; round 0 takes as many sweeps as the
-// step before needed, and writes the last of them where the step's result
-// belongs (rho_new, phi0n, T_new), so that the commit has nothing to copy when
-// that count was right.
+// every sweep of a round keeps its output; the sweep at which the step before
+// converged writes where the step's result belongs (rho_new, phi0n, T_new), so
+// that the commit has nothing to copy when this step takes as many.
 #pragma once
 #include <hip/hip_runtime.h>
 #include "common.hpp"
@@ -17,22 +16,32 @@
 
 namespace ugk {
 
-// Sweeps of round 0 of a step whose predecessor took `prev` (0: none yet).
-__device__ inline int tile_first(const Consts& K, int prev)
+// The rounds of a step whose predecessor took `prev` sweeps (0: none yet): sweeps of
+// round 0 and of round 1 (a batch's ends where its instance's iteration ended before, a
+// single instance's rounds are planned so by the host), S after; and the sweep whose
+// output is written in place.
+struct TilePlan {
+    int s0, s1, fin;
+};
+__device__ inline TilePlan tile_plan(const Consts& K, int prev)
 {
-    const int s = prev > 0 ? min(prev + K.tile_extra, K.tile_S) : K.tile_S;
-    return min(s, K.si_max);
+    TilePlan p;
+    p.s0 = min(prev > 0 ? min(prev + K.tile_extra, K.tile_S) : K.tile_S, K.si_max);
+    p.s1 = K.n_inst > 1 && prev > p.s0 ? min(prev - p.s0, K.tile_S) : K.tile_S;
+    p.fin = (prev > 0 ? prev : p.s0) - 1;
+    return p;
 }
 
 // First sweep and number of sweeps of a round, within the iteration's limit.
 struct TileRound {
     int k0, ns;
 };
-__device__ inline TileRound tile_round(const Consts& K, int s0, int round)
+__device__ inline TileRound tile_round(const Consts& K, const TilePlan& p, int round)
 {
     TileRound r;
-    r.k0 = round == 0 ? 0 : s0 + (round - 1) * K.tile_S;
-    r.ns = round == 0 ? s0 : max(0, min(K.tile_S, K.si_max - r.k0));
+    r.k0 = round == 0 ? 0 : p.s0 + (round == 1 ? 0 : p.s1 + (round - 2) * K.tile_S);
+    const int most = round == 0 ? p.s0 : (round == 1 ? p.s1 : K.tile_S);
+    r.ns = max(0, min(most, K.si_max - r.k0));
     return r;
 }
 
@@ -42,13 +51,14 @@ struct TileOut {
     bool final;
     int at;
 };
-__device__ inline TileOut tile_out(const Consts& K, int s0, int k)
+__device__ inline TileOut tile_out(const Consts& K, const TilePlan& p, int k)
 {
     TileOut o;
-    o.final = k == s0 - 1;
-    if (k < s0) o.at = k;
+    o.final = k == p.fin;
+    if (k < p.s0) o.at = k;
+    else if (k < p.s0 + p.s1) o.at = K.tile_cap + k - p.s0;
     else {
-        const int q = k - s0, round = 1 + q / K.tile_S;
+        const int q = k - p.s0 - p.s1, round = 2 + q / K.tile_S;
         o.at = (round & 1) * K.tile_cap + q % K.tile_S;
     }
     return o;
@@ -111,11 +121,11 @@ __device__ inline void tile_gather(const Dev& D, const Consts& K, int round, int
     }
 }
 
-__device__ inline int tile_outcome(const Consts& K, int round, int s0, const int* sh)
+__device__ inline int tile_outcome(const Consts& K, int round, const TilePlan& p, const int* sh)
 {
     int out = sh[TILE_S_MAX];
     if (out != 0) return out;          // recorded by an earlier launch or just now
-    const TileRound q = tile_round(K, s0, round);
+    const TileRound q = tile_round(K, p, round);
     for (int m = q.ns - 1; m >= 0; --m) {
         const int v = sh[m];
         if (v != 0) out = v > 0 ? q.k0 + m + 1 : -1;

@@ -28,6 +28,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
                                                           double* phi_out, int decide_prev, const double* rho_in,
                                                           double* rho_out)
 {
+    constexpr bool TDEP = OP != OP_FIXED;
     extern __shared__ double lds[];
     __shared__ unsigned long long lres[4][WAVE];     // residual maxima per lane
     __shared__ int stop;
@@ -52,13 +53,13 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
     const int lcell = iy * nx + ix, cell = I.cell_off + lcell;
     const int64_t j = I.cg_off + ((int64_t)lcell << lg) + g;
     const int row = (TX + 2) << lg;                 // of the maps
-    double* const Lsig = lds;
-    double* const Lphi = Lsig + (TY + 2) * row;
-    double* const Lfx = Lphi + (TY + 2) * row;      // [TY][TX + 1] faces along x
+    double* const Lphi = lds;
+    double* const Lwav = Lphi + (TY + 2) * row;     // FIRST: the map of A rho^h
+    double* const Lsig = Lwav + (FIRST ? (TY + 2) * row : 0);
+    double* const Lfx = Lsig + (TY + 2) * row;      // [TY][TX + 1] faces along x
     double* const Lfy = Lfx + ((TY * (TX + 1)) << lg);      // [TY + 1][TX] along y
     double* const cell_a = Lfy + (((TY + 1) * TX) << lg);   // two values per cell, see below
     double* const cell_b = cell_a + (GRID_THREADS >> lg);
-    double* const Lwav = cell_b + (GRID_THREADS >> lg);     // FIRST: the map of A rho^h
     // What is needed once a cell and takes long (Olson's energy and heat capacity, the
     // place of T in the table) is evaluated by the block's last threads, one a cell,
     // beside the other wavefronts' work, and passed on through LDS (every lane of a cell
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
     // sigma of the sweeps' input iterate: the step's tables at T^n, the table's values
     // written by the sweep before, or formed here from T^k
     auto sigma_in = [&](int64_t slot, int cl) __attribute__((always_inline)) -> double {
-        if (FIRST) return D.sig[slot];
+        if (FIRST || OP == OP_FIXED) return D.sig[slot];
         if (OP == OP_TABLE) return D.tab_sig[(int64_t)(k & 1) * K.n_cg + slot];
         return slot_sigma<OP>(D, K, {D.kappa[slot], 0}, I.edge_off, g, D.T_new[cl]);
     };
@@ -89,14 +90,14 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         ht.Tk = FIRST ? ht.Tn : D.T_new[cell];
         ht.pinned = D.pinned[cell] != 0;
         ht.dtcv = D.dtcv[cell];
-        if (K.olson) {
+        if (TDEP && K.olson) {
             ht.H = D.olH[cell];
             ht.chi = D.olchi[cell];
             if (!FIRST) ht.un = D.ol_un[cell];
         }
     }
     double wT = 1.0, wH = 0.0, wchi = 0.0;
-    if (cell_lane) {
+    if (TDEP && cell_lane) {
         if (OP == OP_TABLE) mat = D.tab_mat[wcell];
         if (K.olson) {
             wT = FIRST ? D.T[wcell] : D.T_new[wcell];
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         const double w = wsamp[slot], c4 = D.c4[slot];
         return (D.nbi[slot] > 0 ? w : c4) * D.rhoh[slot];
     };
-    double here = 0.0, c4 = 0.0;
+    double here = 0.0, c4 = 0.0, lam = 0.0, Df[4] = {0.0, 0.0, 0.0, 0.0};
     if (act) {
         phi = phi_in[j];
         if (!FIRST) Qj = D.Q[j];
@@ -122,6 +123,15 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         }
         rho_prev = rho_in[j];
         sig = sigma_in(j, cell);
+        if (!TDEP) {
+            lam = D.sv[j];
+            const int64_t fl = I.fx_off + (((int64_t)iy * (nx + 1) + ix) << lg) + g;
+            const int64_t fb = I.fy_off + ((int64_t)lcell << lg) + g;
+            Df[0] = D.Dx[fl];
+            Df[1] = D.Dx[fl + Gp];
+            Df[2] = D.Dy[fb];
+            Df[3] = D.Dy[fb + ((int64_t)nx << lg)];
+        }
     }
     // a cell around the patch, h = 0 .. 2 (TX + TY) - 1 (below, above, left, right): its
     // place in the maps, sigma (< 0 beyond the boundary), phi (or the ghost's) and A rho^h
@@ -141,7 +151,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
             a.s = 0.0;
             if (g < G) {
                 a.p = phi_in[hj];
-                a.s = sigma_in(hj, I.cell_off + hc);
+                if (TDEP) a.s = sigma_in(hj, I.cell_off + hc);
                 if (FLUX) a.w = wave_up(hj);
             }
         } else {
@@ -191,14 +201,14 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
     if (threadIdx.x < 4 * WAVE) lres[wid][lane] = 0ull;
     const int l = (cy + 1) * row + ((cx + 1) << lg) + g;
     // (a slot of the patch beyond the boundary is a ghost where it touches the mesh)
-    Lsig[l] = ok ? sig : -1.0;
+    if (TDEP) Lsig[l] = ok ? sig : -1.0;
     Lphi[l] = phi;
     if (FLUX) Lwav[l] = here;
     if (!ok && ix == nx && iy < ny && I.bc[XHI] == BC_PLANCK) Lphi[l] = phib[XHI * MAX_G + g];
     if (!ok && iy == ny && ix < nx && I.bc[YHI] == BC_PLANCK) Lphi[l] = phib[YHI * MAX_G + g];
     for (int h = c; h < n_around; h += GRID_THREADS >> lg) {
         if (h > c) ar = around(h);
-        Lsig[ar.l] = ar.s;
+        if (TDEP) Lsig[ar.l] = ar.s;
         Lphi[ar.l] = ar.p;
         if (FLUX) Lwav[ar.l] = ar.w;
     }
@@ -209,18 +219,19 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         const double sa = Lsig[a], sb = Lsig[b];
         return face_coef(K, mt, sa < 0.0 ? fmax(sb, 0.0) : (sb < 0.0 ? sa : face_sigma(sa, sb)), fc);
     };
-    const double Dxl = face(l - Gp, l, I.fcx), Dyl = face(l - row, l, I.fcy);
     const int lfx = ((cy * (TX + 1) + cx) << lg) + g, lfy = ((cy * TX + cx) << lg) + g;
-    Lfx[lfx] = Dxl;
-    Lfy[lfy] = Dyl;
-    if (c < TX + TY) {
+    if (TDEP) {
+        Lfx[lfx] = Df[0] = face(l - Gp, l, I.fcx);
+        Lfy[lfy] = Df[2] = face(l - row, l, I.fcy);
+    }
+    if (TDEP && c < TX + TY) {
         if (c < TX) Lfy[((TY * TX + c) << lg) + g] = face(TY * row + ((c + 1) << lg) + g, (TY + 1) * row + ((c + 1) << lg) + g, I.fcy);
         else {
             const int r = c - TX;
             Lfx[((r * (TX + 1) + TX) << lg) + g] = face((r + 1) * row + (TX << lg) + g, (r + 1) * row + ((TX + 1) << lg) + g, I.fcx);
         }
     }
-    if (K.olson && (LIN || FIRST) && cell_lane) {
+    if (TDEP && K.olson && (LIN || FIRST) && cell_lane) {
         cell_a[cw] = olson_energy(wH, wchi, wT);
         if (LIN) cell_b[cw] = olson_cv(wH, wchi, wT);
     }
@@ -232,8 +243,8 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         if (ok && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / ht.Tk);
         if (act) dph = 4.0 * phi / ht.Tk + K.a * K.c * (ht.Tk * ht.Tk * ht.Tk) * (we - wh) * UGK_15_PI4;
     }
-    __syncthreads();
-    double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0, lam = 0.0, rl = 1.0;    // rl = 1 / (1 + lambda)
+    if (TDEP) __syncthreads();
+    double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0, rl = 1.0;    // rl = 1 / (1 + lambda)
     double dr = 0.0, mr = 0.0, dT = 0.0, mT = 0.0;
     if (FLUX && act) {
         // the flux through each face along +axis is cq (A_low rho^h_low - A_high rho^h_high)
@@ -252,16 +263,20 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         if (source_on(K, now)) Qj = Qj + src;
     }
     if (act) {
-        lam = s_of_sigma(K, sig);
+        if (TDEP) {
+            lam = s_of_sigma(K, sig);
+            Df[1] = Lfx[lfx + Gp];
+            Df[3] = Lfy[lfy + (TX << lg)];
+        }
         double pl = Lphi[l - Gp], ph = Lphi[l + Gp], pb = Lphi[l - row], pt = Lphi[l + row];
         if (ix == 0 && I.bc[XLO] == BC_REFLECT) pl = phi;
         if (ix == nx - 1 && I.bc[XHI] == BC_REFLECT) ph = phi;
         if (iy == 0 && I.bc[YLO] == BC_REFLECT) pb = phi;
         if (iy == ny - 1 && I.bc[YHI] == BC_REFLECT) pt = phi;
-        double lap = I.dy * Dxl * (pl - phi);
-        lap += I.dy * Lfx[lfx + Gp] * (ph - phi);
-        lap += I.dx * Dyl * (pb - phi);
-        lap += I.dx * Lfy[lfy + (TX << lg)] * (pt - phi);
+        double lap = I.dy * Df[0] * (pl - phi);
+        lap += I.dy * Df[1] * (ph - phi);
+        lap += I.dx * Df[2] * (pb - phi);
+        lap += I.dx * Df[3] * (pt - phi);
         b = Qj + I.dt_V * lap;
         rl = 1.0 / (1.0 + lam);
         const double em = quotient(b - phi, 1.0 + lam, rl);
@@ -276,12 +291,12 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
     bool bad = false;
     if (ok) {
         double uk = 0.0, ck = 0.0;
-        if (K.olson && (LIN || FIRST)) {
+        if (TDEP && K.olson && (LIN || FIRST)) {
             uk = cell_a[c];
             if (LIN) ck = cell_b[c];
         }
         if (FIRST) ht.un = uk;
-        Tnew = cell_temperature<true, LIN>(K, ht, uk, ck, contrib, dcon, &uend);
+        Tnew = cell_temperature<TDEP, LIN>(K, ht, uk, ck, contrib, dcon, &uend);
         if (act) {
             if (LIN) {
                 // rho^{k+1} with the linearized emission of T^{k+1}
@@ -346,8 +361,8 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
             atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_TEMP);
         }
         D.T_new[cell] = Tnew;
-        if (ht.H > 0.0) D.uend[cell] = uend;
-        if (FIRST && K.olson) D.ol_un[cell] = ht.un;
+        if (TDEP && ht.H > 0.0) D.uend[cell] = uend;
+        if (TDEP && FIRST && K.olson) D.ol_un[cell] = ht.un;
     }
     // residual maxima (non-negative or NaN: as bit patterns): per lane over the block's
     // wavefronts in LDS, then over the lanes by one wavefront each (a reduction over the
@@ -380,14 +395,16 @@ void launch_si_grid(const Dev& D, const Consts& K, int k, const double* phi_in, 
                     const double* rho_in, double* rho_out, hipStream_t st)
 {
     const bool lin = (K.flags & UGKWP_FLAG_SI_LINEARIZED) != 0;
-    auto kern = K.table ? (lin ? grid_kernel<OP_TABLE, true>(K, k) : grid_kernel<OP_TABLE, false>(K, k))
-                        : (lin ? grid_kernel<OP_POWER, true>(K, k) : grid_kernel<OP_POWER, false>(K, k));
+    const int op = opacity_form(K);
+    auto kern = op == OP_TABLE   ? (lin ? grid_kernel<OP_TABLE, true>(K, k) : grid_kernel<OP_TABLE, false>(K, k))
+                : op == OP_POWER ? (lin ? grid_kernel<OP_POWER, true>(K, k) : grid_kernel<OP_POWER, false>(K, k))
+                                 : (lin ? grid_kernel<OP_FIXED, true>(K, k) : grid_kernel<OP_FIXED, false>(K, k));
     const Inst& I = K.inst0;
     const int lx = grid_lx(I.lgGp), ly = grid_ly(I.lgGp), TX = 1 << lx, TY = 1 << ly;
     const unsigned nb = (unsigned)(((I.nx + TX - 1) >> lx) * ((I.ny + TY - 1) >> ly));
     // maps, faces and the values per cell: 29 to 40 KB (the most with 64 lanes a cell: 48)
     const size_t map = (size_t)(TX + 2) * (TY + 2) * I.Gp, faces = (size_t)((TX + 1) * TY + TX * (TY + 1)) * I.Gp;
-    const size_t lds = ((k == 0 ? 3 : 2) * map + faces + 2 * TX * TY) * sizeof(double);
+    const size_t lds = ((k == 0 ? 2 : 1) * map + (op == OP_FIXED ? 0 : map + faces + 2 * TX * TY)) * sizeof(double);
     kern<<<nb, GRID_THREADS, lds, st>>>(D, K, k, phi_in, phi_out, decide_prev, rho_in, rho_out);
 }
 

@@ -133,6 +133,7 @@ struct ugkwp_ctx {
     std::vector<void*> owned;
     Dev D{};
     Pool mv[2]{};          // moving fields (x, y, cell word), alternate every step
+    void* pool_mem = nullptr;
     Pool stb[2]{};         // stable fields (direction, nu, w, id, g), switch on sorts
     int cur_mv = 0, cur_st = 0;
     int64_t n_alive = 0;   // live particles
@@ -219,6 +220,7 @@ struct ugkwp_ctx {
         if (cap_st) (void)hipStreamDestroy(cap_st);
         cap_st = nullptr;
         free_record();
+        free_pool();
         if (h_adj) (void)hipHostFree(h_adj);
         h_adj = nullptr;
         for (void* p : owned) (void)hipFree(p);
@@ -244,7 +246,7 @@ struct ugkwp_ctx {
         for (void* p : owned) (void)hipFree(p);
         owned.clear();
         D = Dev{};
-        mv[0] = mv[1] = stb[0] = stb[1] = Pool{};
+        free_pool();
         have_opacity = have_material = false;
         olH_buf = olchi_buf = uend_buf = olun_buf = qsrc_buf = nullptr;
         src_on_buf = nullptr;
@@ -341,7 +343,6 @@ struct ugkwp_ctx {
         K.si_tol = P.si_tol;
         K.si_max = P.si_max_iters;
         K.n_cap = P.n_cap;
-        K.pool_cap = P.pool_capacity;
         K.flags = P.flags;
         K.gate = GATE_OFF;
         K.n_inst = n_inst;
@@ -493,19 +494,7 @@ struct ugkwp_ctx {
         HIPCHK(hipMemsetAsync(d.rhoh, 0, sizeof(double) * ncg, st));
         launch_ghost_phi(D, K, d_phib, st);
 
-        const int64_t cap = std::max<int64_t>(P.pool_capacity, 1);
-        for (int b = 0; b < 2; ++b) {
-            mv[b].x = dalloc<double>(owned, cap);
-            mv[b].cell = dalloc<int32_t>(owned, cap);
-            stb[b].ox = dalloc<double>(owned, cap);
-            if (dim == 2) {
-                mv[b].y = dalloc<double>(owned, cap);
-                stb[b].oy = dalloc<double>(owned, cap);
-            }
-            stb[b].nu = dalloc<double>(owned, cap);
-            stb[b].w = dalloc<double>(owned, cap);
-            stb[b].id = dalloc<uint64_t>(owned, cap);
-        }
+        open_pool();
         d.blk_surv = dalloc<unsigned long long>(owned, MAX_PUSH_BLOCKS);
         push_shape = push_default_shape(dim, K);
         push_shape.blocks = std::min(push_shape.blocks, MAX_PUSH_BLOCKS);
@@ -514,6 +503,104 @@ struct ugkwp_ctx {
         step_idx = 0;
         HIPCHK(hipStreamSynchronize(st));
         HIPCHK(hipGetLastError());
+    }
+
+    // ---------------------------------------------------------------- particle pool
+    // The pool holds up to P.pool_capacity slots but starts smaller and grows when a step
+    // needs it: that step finds no room, changes nothing and is taken again.  Its arrays
+    // lie in one allocation: hipFree takes about 0.25 ms for each of more than a few
+    // megabytes, and more the larger it is, so that closing a context of 18432 slots of the
+    // mesh with a capacity of 2^24 particles took 4.3 to 50 ms (now 0.4).
+    // The first size is what a run seldom outgrows, and growing by four keeps the copies
+    // few; where the device's free memory would not hold the pool twice, all of it is
+    // allocated (or refused) at once.
+    static constexpr int64_t POOL_FIRST = 1 << 21, POOL_PER_SLOT = 64;
+
+    // `at(array, bytes per slot, moving, buffer)` for every array of the pool
+    template <class F>
+    void pool_arrays(F&& at)
+    {
+        for (int b = 0; b < 2; ++b) {
+            at((void**)&mv[b].x, 8, true, b);
+            at((void**)&stb[b].ox, 8, false, b);
+            if (dim == 2) {
+                at((void**)&mv[b].y, 8, true, b);
+                at((void**)&stb[b].oy, 8, false, b);
+            }
+            at((void**)&stb[b].nu, 8, false, b);
+            at((void**)&stb[b].w, 8, false, b);
+            at((void**)&stb[b].id, 8, false, b);
+            at((void**)&mv[b].cell, 4, true, b);
+        }
+    }
+
+    static size_t pool_bytes(int64_t cap, int per) { return ((size_t)cap * per + 255) / 256 * 256; }
+
+    size_t pool_total(int64_t cap)
+    {
+        size_t t = 0;
+        pool_arrays([&](void**, int per, bool, int) { t += pool_bytes(cap, per); });
+        return t;
+    }
+
+    void open_pool()
+    {
+        const int64_t cap = std::max<int64_t>(P.pool_capacity, 1);
+        int64_t first = std::min(cap, std::max(POOL_FIRST, POOL_PER_SLOT * K.n_cg));
+        if (first < cap) {
+            size_t free_b = 0, total_b = 0;
+            HIPCHK(hipMemGetInfo(&free_b, &total_b));
+            if (2 * pool_total(cap) > free_b) first = cap;
+        }
+        n_slots = 0;
+        resize_pool(first);
+    }
+
+    // The pool's arrays moved to an allocation for `cap` slots, with the committed particles.
+    void resize_pool(int64_t cap)
+    {
+        drop_graphs();
+        void* p = nullptr;
+        const size_t bytes = pool_total(cap);
+        if (hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            fail(UGKWP_ENOMEM, "hipMalloc of %zu bytes for the particle pool failed", bytes);
+        }
+        if (n_slots > 0) {
+            char* to = (char*)p;
+            hipError_t e = hipSuccess;
+            pool_arrays([&](void** a, int per, bool moving, int b) {
+                if (b == (moving ? cur_mv : cur_st) && e == hipSuccess)
+                    e = hipMemcpyAsync(to, *a, (size_t)n_slots * per, hipMemcpyDeviceToDevice, st);
+                to += pool_bytes(cap, per);
+            });
+            const hipError_t es = hipStreamSynchronize(st);
+            if (e != hipSuccess || es != hipSuccess) {
+                (void)hipFree(p);
+                HIPCHK(e != hipSuccess ? e : es);
+            }
+        }
+        free_pool();
+        pool_mem = p;
+        char* to = (char*)p;
+        pool_arrays([&](void** a, int per, bool, int) {
+            *a = to;
+            to += pool_bytes(cap, per);
+        });
+        K.pool_cap = std::min(cap, P.pool_capacity);
+    }
+
+    // room for n slots (n <= P.pool_capacity)
+    void reserve_pool(int64_t n)
+    {
+        if (n > K.pool_cap) resize_pool(std::min(std::max(n + n / 4, 4 * K.pool_cap), P.pool_capacity));
+    }
+
+    void free_pool()
+    {
+        if (pool_mem) (void)hipFree(pool_mem);
+        pool_mem = nullptr;
+        mv[0] = mv[1] = stb[0] = stb[1] = Pool{};
     }
 
     // ---------------------------------------------------------------- 1-D iteration in tiles
@@ -1262,6 +1349,12 @@ struct ugkwp_ctx {
                 StatusView s = status_at(h_ring + (size_t)q.slot * ring_stride);
                 const bool committed =
                     s.counters[CNT_DONE] == (unsigned long long)q.step + 1 && s.counters[CNT_ERR] == 0;
+                if (!committed && s.counters[CNT_ERR] == ERR_POOL && K.pool_cap < P.pool_capacity &&
+                    (int64_t)s.counters[CNT_SLOTS] + s.total[0] <= P.pool_capacity) {
+                    // the step needs more room than the pool has so far: taken again
+                    reserve_pool((int64_t)s.counters[CNT_SLOTS] + s.total[0]);
+                    break;
+                }
                 if (!committed) {
                     const Plan before = state_now();
                     try {
@@ -1276,7 +1369,7 @@ struct ugkwp_ctx {
                 done++;
                 if (!committed) break;      // later steps of the batch did not run: plan again
             }
-            last_sweeps = batch_max;
+            if (batch_max > 0) last_sweeps = batch_max;
         }
     }
 
@@ -2130,6 +2223,7 @@ int ugkwp_set_pool(ugkwp_ctx* ctx, int64_t n, const double* x, const double* y, 
                 id[q] > ID_MASK)
                 fail(UGKWP_EINVAL, "particle %lld: cell, group, weight, frequency or id out of range", (long long)q);
         if (birth_counter > ID_MASK) fail(UGKWP_EINVAL, "birth counter beyond the id range");
+        ctx->reserve_pool(n);
         const Pool p = ctx->view(ctx->cur_mv, ctx->cur_st);
         hipStream_t st = ctx->st;
         auto cp = [&](void* dst, const void* src, size_t bytes) {
@@ -2265,6 +2359,7 @@ int ugkwp_set_state(ugkwp_ctx* ctx, const void* buf, int64_t bytes)
             if (nb > ID_MASK) fail(UGKWP_EINVAL, "saved birth counter beyond the id range");
         }
 
+        ctx->reserve_pool(h.n_slots);
         hipStream_t st = ctx->st;
         auto cp = [&](void* dst, size_t off, size_t n) {
             if (n) HIPCHK(hipMemcpyAsync(dst, b + off, n, hipMemcpyHostToDevice, st));

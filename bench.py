@@ -49,10 +49,10 @@ SI_SWEEP_BYTES = 64        # Q, lambda, sigma, phi^k, rho^k, one face D read; rh
 # x 1.0), over the windows of the profiles under profiles/.  They hold only for
 # the push kernel sources they were taken with (SHA-256 prefix below); any change
 # to those sources makes bench.py report the traffic as unknown.
-PUSH_SOURCES = ("kernels.hip", "device_math.hpp", "device_common.hpp", "common.hpp")
+PUSH_SOURCES = ("kernels.hip", "device_math.hpp", "device_common.hpp", "si_common.hpp", "common.hpp")
 PUSH_TRAFFIC = {
-    "slab": {"sources": "130a38c77fd81f1c", "read_per_push": 45.04, "write_per_push": 12.89},
-    "lattice": {"sources": "130a38c77fd81f1c", "read_per_push": 62.23, "write_per_push": 21.64},
+    "slab": {"sources": "48372a5027541f9d", "read_per_push": 45.04, "write_per_push": 12.90},
+    "lattice": {"sources": "48372a5027541f9d", "read_per_push": 62.25, "write_per_push": 21.62},
 }
 
 
@@ -586,8 +586,9 @@ def main():
         # the source-iteration phase as a second roofline object (every sweep and decide
         # launch between two events, from the phase-timed steps)
         si_ach = SI_SWEEP_BYTES * ph_cgu / (ms_si_ph * 1e-3) / 1e9
+        si_kern = "k_si_tile" if probs[0].dim == 1 else "k_si_grid and k_si_sweep"
         out["roofline_si"] = {"bound": "hbm", "achieved": si_ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                              "frac": si_ach / HBM_PEAK_GBS, "kernel": "k_si_sweep (the source-iteration phase)",
+                              "frac": si_ach / HBM_PEAK_GBS, "kernel": f"{si_kern} (the source-iteration phase)",
                               "algorithmic_bytes_per_update": SI_SWEEP_BYTES,
                               "from": f"{nph} further steps with every phase timed"}
     if wl == "batch" and ms_si_ph > 0:
@@ -597,7 +598,7 @@ def main():
         out["roofline_push"] = out["roofline"]
         out["roofline"] = {"bound": "hbm", "achieved": si_ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": si_ach / HBM_PEAK_GBS, "traffic": None,
-                           "kernel": "k_si_sweep (the source-iteration phase: sweeps and decides)",
+                           "kernel": "k_si_tile (the source-iteration phase: rounds of sweeps and decides)",
                            "algorithmic_bytes_per_update": SI_SWEEP_BYTES,
                            "from": f"{nph} further steps with every phase timed"}
     if wl == "batch" and not args.per_instance and not args.no_compare:

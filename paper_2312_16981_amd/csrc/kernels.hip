@@ -1433,8 +1433,8 @@ __global__ __launch_bounds__(256) void k_wave_q(Dev D, Consts K, int k, const do
 
 constexpr int SI_THREADS = 256;
 
-// phi^k buffers: sweep 0 reads phi0 = phi(T^n), sweep k writes phi1 (k even)
-// or phi2 (k odd) and sweep k + 1 reads it; phi0 is only rewritten by the commit.
+// phi^k buffers of the 2-D sweeps: sweep 0 reads phi0 = phi(T^n), sweep k writes phi1
+// (k even) or phi2 (k odd) and sweep k + 1 reads it; the commit fills phi0n.
 __host__ __device__ inline const double* sweep_in(const Dev& D, int k)
 {
     return k == 0 ? D.phi0 : (((k - 1) & 1) ? D.phi2 : D.phi1);
@@ -1763,9 +1763,9 @@ __global__ void k_si_decide(Dev D, Consts K, int k)
 // commit and diagnostics
 
 // Energy bookkeeping of the step per instance: diag[inst*8 + q],
-// q = 0 inflow_wave (written by k_wave_source), 1 inflow_eq, 2 exit, 3 injection,
+// q = 0 inflow_wave (added by the first sweep), 1 inflow_eq, 2 exit, 3 injection,
 // 4 e_start, 5 e_end.  Uses the final source-iteration input phi^k; the
-// commit also keeps the last sweep's phi(T^{n+1}) in phi0 for the next step.  Sums are
+// commit also keeps the last sweep's phi(T^{n+1}) in phi0n for the next step.  Sums are
 // reduced per wavefront and per run of same-instance wavefronts of the block
 // before one atomic per quantity.
 constexpr int DIAG_THREADS = 256;

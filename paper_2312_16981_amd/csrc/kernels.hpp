@@ -51,7 +51,7 @@ int push_num_cus();
 void launch_push(int dim, const Dev& D, const Consts& K, const Pool& A, const Pool& B, const PushShape& sh,
                  hipStream_t st);
 void launch_sort_scatter(int dim, const Dev& D, const Consts& K, const Pool& B, const Pool& A, hipStream_t st);
-// sweeps k0..k1-1 of the source iteration, each sweep's convergence decided
+// sweeps k0..k1-1 of the 2-D source iteration, each sweep's convergence decided
 // before the next: for a single instance in the next sweep (the last one's in
 // launch_finish), else by a decide launch after every sweep
 void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t st);

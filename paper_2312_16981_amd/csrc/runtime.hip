@@ -640,10 +640,11 @@ struct ugkwp_ctx {
     }
 
     // A batch's tiles, the same for every step: each block's instance and tile.  (256
-    // slabs, 3 sweeps: 512 threads of two cells took 1.41 ms a step, against 1.49 and
-    // 1.51 for 2 and 4 sweeps, 1.52 for 256 threads, 1.67 for 1024 and 1.74 for one cell a
-    // thread.)  The rows of a T-dependent opacity and those of a wave flux per iterate
-    // together leave room in 64 KiB of LDS for blocks of half the size.
+    // slabs: 3 sweeps a round took 1.25 ms a step, 2 and 4 1.40 and 1.31; before round 1
+    // ended where the instance had converged, 512 threads of two cells took 1.41, 256
+    // threads 1.52, 1024 1.67 and one cell a thread 1.74.)  The rows of a T-dependent opacity
+    // and those of a wave flux per iterate together leave room in 64 KiB of LDS for blocks
+    // of half the size.
     void batch_tiles(Dev& d)
     {
         K.tile_threads = tile_wit() && tile_tdep() ? TILE_BATCH_THREADS / 2 : TILE_BATCH_THREADS;

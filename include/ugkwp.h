@@ -102,7 +102,9 @@ typedef struct {
     double dt;           /* time step                                              */
     double nu_power;     /* p in sigma(nu) = kappa * nu^-p (3 for the paper's tests) */
     int64_t n_cap;       /* max particles sampled per (cell, group) and step       */
-    int64_t pool_capacity; /* particle slots of the context (all instances), at most 2^29 */
+    int64_t pool_capacity; /* particle slots of the context (all instances), at most 2^29;
+                              allocated as a run needs them (UGKWP_ENOMEM from the step that
+                              finds no device memory for more: its state stays as it was) */
     int si_max_iters;    /* source-iteration limit (Algorithm 2)                   */
     double si_tol;       /* relative max-norm tolerance on rho and on T            */
     uint32_t flags;      /* UGKWP_FLAG_*                                           */

@@ -692,7 +692,10 @@ struct ugkwp_ctx {
                     K.tile_H = tile_halo(S);
                     K.tile_cpt = 1;
                     K.tile_blocks = (int)nb;
-                    K.tile_reg = !tile_wit() && !tile_tdep() && bt <= 512 && nb <= 256;      // one block per CU
+                    // the Planck coefficients in registers where a CU has one block and the
+                    // sweep leaves room for them: a round of 300 x 24 slots 14.7 -> 13.7 us; with
+                    // a T-dependent opacity they spill (Larsen's 27.5 -> 29.5, Olson's 19.2 -> 20.3)
+                    K.tile_reg = !tile_wit() && !tile_tdep() && bt <= 512 && nb <= 256;
                 }
             }
     }

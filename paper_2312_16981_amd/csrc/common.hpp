@@ -182,6 +182,8 @@ struct Dev {
     double* phi0n;              // phi(T^{n+1}) (the two swap when the step commits)
     double* phi1;               // phi^{k+1} of the even sweeps
     double* phi2;               // phi^{k+1} of the odd sweeps
+    double* T_it;               // [2][cell] T^k read by the 2-D sweep k across its cells' faces: a block
+                                // may run after the blocks of those cells have written T_new
     int32_t* nb;                // births per slot
     int64_t* boff;              // exclusive scan of nb
     double* wnew;

@@ -1542,6 +1542,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     int mat_j = 0;
     if (TDEP && act) {
         const double* tsig = FIRST ? D.sig : D.tab_sig + (int64_t)(k & 1) * K.n_cg;
+        const double* T_it = D.T_it + (int64_t)(k & 1) * K.ncell;
         if (K.table) {
             mat_j = D.tab_mat[cell];
             tsig_j = tsig[j];
@@ -1558,7 +1559,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
             }
             const bool lo = (q & 1) == 0;
             const int nbc = cell + (q < 2 ? (lo ? -1 : 1) : (lo ? -nx : nx));
-            T_nb[q] = FIRST ? D.T[nbc] : D.T_new[nbc];
+            T_nb[q] = FIRST ? D.T[nbc] : T_it[nbc];
             kap_n[q] = D.kappa[F.nbj[q]];
             Sn[q] = K.stim ? group_factor(D, K, I.edge_off, g, T_nb[q]) : Sg;
         }
@@ -1698,6 +1699,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
             atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_TEMP);
         }
         D.T_new[cell] = Tnew;
+        if (TDEP && !K.table) D.T_it[(int64_t)((k + 1) & 1) * K.ncell + cell] = Tnew;
         if (TDEP && olH > 0.0) D.uend[cell] = uend;
     }
     // residual maxima: wavefront, then runs of wavefronts of one instance in the block

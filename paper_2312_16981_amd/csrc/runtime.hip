@@ -415,6 +415,7 @@ struct ugkwp_ctx {
         if (dim == 2) {
             d.phi1 = dalloc<double>(owned, ncg);
             d.phi2 = dalloc<double>(owned, ncg);
+            d.T_it = dalloc<double>(owned, 2 * (size_t)ncell);
             for (double* q : {d.phi1, d.phi2}) HIPCHK(hipMemsetAsync(q, 0, sizeof(double) * ncg, st));
         }
         d.nb = dalloc<int32_t>(owned, ncg);

@@ -70,11 +70,12 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
     const int wcell = I.cell_off + wy * nx + wx;
     const double* phib = D.phib;
     // sigma of the sweeps' input iterate: the step's tables at T^n, the table's values
-    // written by the sweep before, or formed here from T^k
+    // written by the sweep before, or formed here from T^k (both of buffers that no block
+    // of this launch writes)
     auto sigma_in = [&](int64_t slot, int cl) __attribute__((always_inline)) -> double {
         if (FIRST || OP == OP_FIXED) return D.sig[slot];
         if (OP == OP_TABLE) return D.tab_sig[(int64_t)(k & 1) * K.n_cg + slot];
-        return slot_sigma<OP>(D, K, {D.kappa[slot], 0}, I.edge_off, g, D.T_new[cl]);
+        return slot_sigma<OP>(D, K, {D.kappa[slot], 0}, I.edge_off, g, D.T_it[(int64_t)(k & 1) * K.ncell + cl]);
     };
 
     // every load first: the slot, the cell, and of the cells around the patch the
@@ -361,6 +362,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
             atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_TEMP);
         }
         D.T_new[cell] = Tnew;
+        if (OP == OP_POWER) D.T_it[(int64_t)((k + 1) & 1) * K.ncell + cell] = Tnew;
         if (TDEP && ht.H > 0.0) D.uend[cell] = uend;
         if (TDEP && FIRST && K.olson) D.ol_un[cell] = ht.un;
     }

@@ -21,8 +21,25 @@ constexpr int TILE_S_MAX = 8;    // most source-iteration sweeps per launch (1-D
 
 // Threads per tile block: the sweeps that follow the opacity and those that keep the
 // Planck coefficients in registers hold too many for 16 wavefronts per CU.
-constexpr int TILE_BATCH_THREADS = 512;     // a batch's tiles
+constexpr int TILE_BATCH_THREADS = 512, TILE_BATCH_CPT = 2;     // a batch's tiles, and their cells per thread
 constexpr int tile_max_threads(bool tdep, bool reg) { return tdep || reg ? 512 : 1024; }
+
+// LDS of a block's rows, of its cells and one beyond on either side: phi and with an opacity that
+// follows the iterate (tdep) sigma, twice, and three of the wave flux of every iterate (wit).
+constexpr size_t tile_rows_lds(int threads, int cpt, int gp, bool wit, bool tdep)
+{
+    return (size_t)(threads * cpt + 2 * gp) * (2 + (tdep ? 2 : 0) + (wit ? 3 : 0)) * sizeof(double);
+}
+
+// A block may take up to 160 KiB of LDS.  A batch's tile with all seven rows takes 81 KB (one
+// block per CU); halved, with one sweep a round, it takes 52 KB and is slower: 200 slabs of
+// up to 439 cells, 33 sweeps with slopes and Olson's heat capacity, 7.1 ms a step against 6.2.
+// So every batch has one shape, whichever model is set later.
+constexpr size_t LDS_PER_BLOCK = 160 * 1024;
+constexpr size_t TILE_RES_LDS = TILE_S_MAX * 4 * 64 * sizeof(unsigned long long) + (TILE_S_MAX + 1) * sizeof(int);
+static_assert(tile_rows_lds(TILE_BATCH_THREADS, TILE_BATCH_CPT, MAX_G, true, true) + TILE_RES_LDS <= LDS_PER_BLOCK &&
+              tile_rows_lds(tile_max_threads(true, false), 1, MAX_G, true, true) + TILE_RES_LDS <= LDS_PER_BLOCK &&
+              tile_rows_lds(tile_max_threads(false, false), 1, MAX_G, true, false) + TILE_RES_LDS <= LDS_PER_BLOCK, "");
 
 enum { BC_VACUUM = 0, BC_PLANCK = 1, BC_REFLECT = 2 };
 enum { XLO = 0, XHI = 1, YLO = 2, YHI = 3 };

@@ -621,7 +621,7 @@ struct ugkwp_ctx {
         // sweep planes kept: as many as a launch of a small context takes, fewer for
         // large ones (a plane is 16 bytes per slot)
         K.tile_cap = K.n_cg <= (1ll << 22) ? TILE_S_MAX : (K.n_cg <= (1ll << 27) ? 4 : 2);
-        if (n_inst > 1) K.tile_cap = std::min(K.tile_cap, tile_wit() ? (tile_tdep() ? 1 : 2) : 3);
+        if (n_inst > 1) K.tile_cap = std::min(K.tile_cap, tile_wit() ? 2 : 3);
         const size_t planes = 2 * (size_t)K.tile_cap;
         d.tile_rho = dalloc<double>(owned, planes * ncg);
         d.tile_phi = dalloc<double>(owned, planes * ncg);
@@ -643,13 +643,12 @@ struct ugkwp_ctx {
     // A batch's tiles, the same for every step: each block's instance and tile.  (256
     // slabs: 3 sweeps a round took 1.25 ms a step, 2 and 4 1.40 and 1.31; before round 1
     // ended where the instance had converged, 512 threads of two cells took 1.41, 256
-    // threads 1.52, 1024 1.67 and one cell a thread 1.74.)  The rows of a T-dependent opacity
-    // and those of a wave flux per iterate together leave room in 64 KiB of LDS for blocks
-    // of half the size.
+    // threads 1.52, 1024 1.67 and one cell a thread 1.74.)  The shape does not ask for the
+    // model: Olson's heat capacity or a table may be set after it.
     void batch_tiles(Dev& d)
     {
-        K.tile_threads = tile_wit() && tile_tdep() ? TILE_BATCH_THREADS / 2 : TILE_BATCH_THREADS;
-        K.tile_cpt = 2;
+        K.tile_threads = TILE_BATCH_THREADS;
+        K.tile_cpt = TILE_BATCH_CPT;
         K.tile_H = tile_halo(K.tile_S);
         std::vector<int2> blk;
         std::vector<int32_t> start;

@@ -77,6 +77,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
     extern __shared__ double lds[];
     __shared__ unsigned long long lres[TILE_S_MAX][4][WAVE];    // residual maxima per sweep and lane
     __shared__ int dec[TILE_S_MAX + 1];
+    static_assert(sizeof(lres) + sizeof(dec) == TILE_RES_LDS, "");
     const int lane = threadIdx.x & (WAVE - 1);
     warm_args<sizeof(Dev) + sizeof(Consts)>();
     const uint32_t now = *D.step;
@@ -458,8 +459,7 @@ template <bool FIRST, bool SINGLE, int OP, bool LIN, bool EXT, bool WIT>
 static void tile_launch(const Dev& D, const Consts& K, int round, hipStream_t st)
 {
     const int gmax = SINGLE ? K.inst0.Gp : MAX_G;
-    const size_t rows = 2 + (OP != OP_FIXED ? 2 : 0) + (WIT ? 3 : 0);
-    const size_t lds = (size_t)(K.tile_threads * K.tile_cpt + 2 * gmax) * rows * sizeof(double);
+    const size_t lds = tile_rows_lds(K.tile_threads, K.tile_cpt, gmax, WIT, OP != OP_FIXED);
     if constexpr (SINGLE) {
         if constexpr (!WIT && OP == OP_FIXED) {
             if (K.tile_reg) {
@@ -469,7 +469,7 @@ static void tile_launch(const Dev& D, const Consts& K, int round, hipStream_t st
         }
         k_si_tile<FIRST, true, OP, LIN, EXT, WIT, 1, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
     } else {
-        k_si_tile<FIRST, false, OP, LIN, EXT, WIT, 2, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
+        k_si_tile<FIRST, false, OP, LIN, EXT, WIT, TILE_BATCH_CPT, false><<<K.tile_blocks, K.tile_threads, lds, st>>>(D, K, round);
     }
 }
 

@@ -9,6 +9,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "pool.hpp"
 
 namespace ugk {
 
@@ -131,7 +132,7 @@ enum {
     N_COUNTERS = 8
 };
 enum : unsigned long long {
-    ERR_POOL = 1,      // pool capacity would be exceeded: nothing sampled, step not committed
+    ERR_POOL = POOL_REFUSED,      // pool capacity would be exceeded: nothing sampled, step not committed
     ERR_RECORD = 2,    // a particle record with an out-of-range cell or group
     ERR_COUNT = 4,     // survivor counts disagree with the pool
     ERR_TEMP = 8       // non-positive or non-finite temperature in the source iteration

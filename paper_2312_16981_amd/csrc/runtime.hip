@@ -1353,10 +1353,11 @@ struct ugkwp_ctx {
                 StatusView s = status_at(h_ring + (size_t)q.slot * ring_stride);
                 const bool committed =
                     s.counters[CNT_DONE] == (unsigned long long)q.step + 1 && s.counters[CNT_ERR] == 0;
-                if (!committed && s.counters[CNT_ERR] == ERR_POOL && K.pool_cap < P.pool_capacity &&
-                    (int64_t)s.counters[CNT_SLOTS] + s.total[0] <= P.pool_capacity) {
+                const int64_t need = pool_need(s.counters[CNT_ERR], K.pool_cap, P.pool_capacity,
+                                               (int64_t)s.counters[CNT_SLOTS], s.total[0]);
+                if (!committed && need > 0) {
                     // the step needs more room than the pool has so far: taken again
-                    reserve_pool((int64_t)s.counters[CNT_SLOTS] + s.total[0]);
+                    reserve_pool(need);
                     break;
                 }
                 if (!committed) {

@@ -134,6 +134,7 @@ struct ugkwp_ctx {
     Dev D{};
     Pool mv[2]{};          // moving fields (x, y, cell word), alternate every step
     void* pool_mem = nullptr;
+    int64_t pool_slots = 0;    // slots of pool_mem
     Pool stb[2]{};         // stable fields (direction, nu, w, id, g), switch on sorts
     int cur_mv = 0, cur_st = 0;
     int64_t n_alive = 0;   // live particles
@@ -508,13 +509,12 @@ struct ugkwp_ctx {
 
     // ---------------------------------------------------------------- particle pool
     // The pool holds up to P.pool_capacity slots but starts smaller and grows when a step
-    // needs it: that step finds no room, changes nothing and is taken again.  Its arrays
-    // lie in one allocation: hipFree takes about 0.25 ms for each of more than a few
+    // needs it: that step finds no room, changes nothing and is taken again (pool.hpp).  Its
+    // arrays lie in one allocation: hipFree takes about 0.25 ms for each of more than a few
     // megabytes, and more the larger it is, so that closing a context of 18432 slots of the
     // mesh with a capacity of 2^24 particles took 4.3 to 50 ms (now 0.4).
-    // The first size is what a run seldom outgrows, and growing by four keeps the copies
-    // few; where the device's free memory would not hold the pool twice, all of it is
-    // allocated (or refused) at once.
+    // The first size is what a run seldom outgrows; where the device's free memory would not
+    // hold the pool twice, all of it is allocated (or refused) at once.
     static constexpr int64_t POOL_FIRST = 1 << 21, POOL_PER_SLOT = 64;
 
     // `at(array, bytes per slot, moving, buffer)` for every array of the pool
@@ -535,72 +535,93 @@ struct ugkwp_ctx {
         }
     }
 
-    static size_t pool_bytes(int64_t cap, int per) { return ((size_t)cap * per + 255) / 256 * 256; }
-
-    size_t pool_total(int64_t cap)
+    std::vector<PoolArray> pool_layout()
     {
-        size_t t = 0;
-        pool_arrays([&](void**, int per, bool, int) { t += pool_bytes(cap, per); });
-        return t;
+        std::vector<PoolArray> a;
+        pool_arrays([&](void**, int per, bool moving, int b) { a.push_back({per, b == (moving ? cur_mv : cur_st)}); });
+        return a;
     }
+
+    // device memory and copies of the pool's move
+    struct PoolMem {
+        hipStream_t st;
+        hipError_t err = hipSuccess;
+        void* alloc(size_t bytes)
+        {
+            void* p = nullptr;
+            if (hipMalloc(&p, bytes) == hipSuccess) return p;
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        void release(void* p) { (void)hipFree(p); }
+        size_t room()
+        {
+            size_t free_b = 0, total_b = 0;
+            return hipMemGetInfo(&free_b, &total_b) == hipSuccess ? free_b : 0;
+        }
+        void copy(void* to, const void* from, size_t bytes, hipMemcpyKind kind)
+        {
+            if (err == hipSuccess) err = hipMemcpyAsync(to, from, bytes, kind, st);
+        }
+        void within(void* to, const void* from, size_t bytes) { copy(to, from, bytes, hipMemcpyDeviceToDevice); }
+        void down(void* to, const void* from, size_t bytes) { copy(to, from, bytes, hipMemcpyDeviceToHost); }
+        void up(void* to, const void* from, size_t bytes) { copy(to, from, bytes, hipMemcpyHostToDevice); }
+        bool wait()
+        {
+            const hipError_t e = hipStreamSynchronize(st);
+            if (err == hipSuccess) err = e;
+            return err == hipSuccess;
+        }
+    };
 
     void open_pool()
     {
         const int64_t cap = std::max<int64_t>(P.pool_capacity, 1);
         int64_t first = std::min(cap, std::max(POOL_FIRST, POOL_PER_SLOT * K.n_cg));
-        if (first < cap) {
-            size_t free_b = 0, total_b = 0;
-            HIPCHK(hipMemGetInfo(&free_b, &total_b));
-            if (2 * pool_total(cap) > free_b) first = cap;
-        }
+        if (first < cap && 2 * pool_total(pool_layout(), cap) > PoolMem{st}.room()) first = cap;
         n_slots = 0;
-        resize_pool(first);
+        pool_slots = 0;
+        move_pool({first, first, first});
     }
 
-    // The pool's arrays moved to an allocation for `cap` slots, with the committed particles.
-    void resize_pool(int64_t cap)
+    // The pool's arrays moved to an allocation for one of `sizes`, with the committed particles.
+    void move_pool(const std::array<int64_t, 3>& sizes)
     {
         drop_graphs();
-        void* p = nullptr;
-        const size_t bytes = pool_total(cap);
-        if (hipMalloc(&p, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            fail(UGKWP_ENOMEM, "hipMalloc of %zu bytes for the particle pool failed", bytes);
+        PoolMem m{st};
+        const std::vector<PoolArray> layout = pool_layout();
+        const PoolMove r = pool_move(m, layout, &pool_mem, &pool_slots, n_slots, sizes);
+        if (r == PoolMove::lost) {
+            // nothing is left to step from until set_material puts a state back
+            free_pool();
+            n_slots = n_alive = 0;
+            have_material = false;
+            fail(UGKWP_ENOMEM, "the particles were lost while the pool grew: its memory was taken by others");
         }
-        if (n_slots > 0) {
-            char* to = (char*)p;
-            hipError_t e = hipSuccess;
-            pool_arrays([&](void** a, int per, bool moving, int b) {
-                if (b == (moving ? cur_mv : cur_st) && e == hipSuccess)
-                    e = hipMemcpyAsync(to, *a, (size_t)n_slots * per, hipMemcpyDeviceToDevice, st);
-                to += pool_bytes(cap, per);
-            });
-            const hipError_t es = hipStreamSynchronize(st);
-            if (e != hipSuccess || es != hipSuccess) {
-                (void)hipFree(p);
-                HIPCHK(e != hipSuccess ? e : es);
-            }
-        }
-        free_pool();
-        pool_mem = p;
-        char* to = (char*)p;
+        // (also where the pool is as large as it was: its address may have changed)
+        char* to = (char*)pool_mem;
         pool_arrays([&](void** a, int per, bool, int) {
             *a = to;
-            to += pool_bytes(cap, per);
+            to += pool_bytes(pool_slots, per);
         });
-        K.pool_cap = std::min(cap, P.pool_capacity);
+        K.pool_cap = std::min(pool_slots, P.pool_capacity);
+        if (r == PoolMove::failed) HIPCHK(m.err);
+        if (r == PoolMove::no_memory)
+            fail(UGKWP_ENOMEM, "no %zu bytes of device memory for the particle pool", pool_total(layout, sizes.back()));
     }
 
     // room for n slots (n <= P.pool_capacity)
     void reserve_pool(int64_t n)
     {
-        if (n > K.pool_cap) resize_pool(std::min(std::max(n + n / 4, 4 * K.pool_cap), P.pool_capacity));
+        if (n > K.pool_cap) move_pool(pool_sizes(n, K.pool_cap, P.pool_capacity));
     }
 
     void free_pool()
     {
         if (pool_mem) (void)hipFree(pool_mem);
         pool_mem = nullptr;
+        pool_slots = 0;
+        K.pool_cap = 0;
         mv[0] = mv[1] = stb[0] = stb[1] = Pool{};
     }
 

@@ -480,12 +480,13 @@ __host__ __device__ inline double quotient(double n, double d, double r)
 
 // C2/dt = [2 C4 - 1 - e^{-s}] / s from s = 2 on; below, where that cancels, s times the
 // polynomial of the series sum_{n>=2} (-1)^{n+1} (n-1) s^{n-1}/(n+1)! (within 1e-18).
+// (1/s is 0 for an infinite s alone, whose quotients would be NaN.)
 __device__ inline double coef_c2_over_dt(TabPtr t, double s)
 {
     if (s < 2.0) return s * poly<15>(t->c2, s);
     const double e = exp_neg(t, s), r = 1.0 / s;
     const double c4 = quotient(1.0 - e, s, r);
-    return quotient(2.0 * c4 - 1.0 - e, s, r);
+    return r > 0.0 ? quotient(2.0 * c4 - 1.0 - e, s, r) : -r;
 }
 
 // C5/dt of the slope term of the UGKS free-transport flux (Sec. 2.2):

@@ -2074,9 +2074,17 @@ __global__ void k_eval_coef(int n, const double* s, double* c4, double* w, doubl
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= n) return;
     const TabPtr t = math_tab();
-    c4[j] = coef_c4(t, s[j]);
-    w[j] = coef_w(t, s[j]);
-    c2[j] = coef_c2_over_dt(t, s[j]);
+    const double a = fabs(s[j]), f4 = coef_c4(t, a), fw = coef_w(t, a), f2 = coef_c2_over_dt(t, a);
+    c4[j] = f4;
+    w[j] = fw;
+    c2[j] = f2;
+    if (s[j] < 0.0) {
+        // by C4(-a) = e^a C4(a) and 1 - C4(a) = W(a) - a C2(a)/dt (the polynomials hold for s >= 0)
+        const double e = exp(a);
+        c4[j] = e * f4;
+        w[j] = -e * (fw - a * f2);
+        c2[j] = -e * f2;
+    }
 }
 
 __global__ void k_eval_uniform(int n, uint64_t seed, const uint64_t* id, uint32_t step, uint32_t purpose,

@@ -1777,15 +1777,28 @@ constexpr int DIAG_THREADS = 256;
 // takes it from the same residual sub-slots, and block 0 records it.
 // TDEP: a temperature-dependent opacity or Olson's heat capacity (kept apart for their
 // registers).
+// What bounds it: the chain of waits of a block, some 5 us, and the blocks in flight.
+// The walls' terms, which few wavefronts have, are formed last, when the energies no longer
+// hold registers (44 instead of 62 in 2-D, 64 instead of 104 with TDEP, which spills in
+// those terms alone), and 8 wavefronts a SIMD fit everywhere but in a single 1-D
+// instance, whose few blocks are all in flight and only get longer by spilling (128 x 24
+// slots: 9.6 us, 12 with the floor).  285 x 285 cells of 24 groups: 69 -> 42 us (11 of them by
+// the source's share in the block's sum instead of an atomic per wavefront), 256 x 256 of
+// 32: 37 -> 33, 256 slabs: 228 -> 158.
+template <int DIM, bool TDEP>
+constexpr int finish_min_waves() { return DIM == 2 && TDEP ? 8 : 1; }
+
 template <bool SINGLE, int DIM, bool TDEP>
-__global__ __launch_bounds__(DIAG_THREADS)
+__global__ __launch_bounds__(DIAG_THREADS) __attribute__((amdgpu_waves_per_eu(finish_min_waves<DIM, TDEP>())))
 void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
 {
     const int64_t j = (int64_t)blockIdx.x * DIAG_THREADS + threadIdx.x;
     // the loads come first (nothing is stored before the gate): step count,
     // the stopping state of the last sweep (one instance), the slot's data
-    warm_args<sizeof(Dev) + sizeof(Consts)>();
-    const int z = lane_zero();
+    // (a batch fills the chip many times over: there both only stand in the way of its other
+    // loads, 238 against 158 us)
+    if (SINGLE) warm_args<sizeof(Dev) + sizeof(Consts)>();
+    const int z = SINGLE ? lane_zero() : 0;
     const uint32_t now = D.step[z];
     Inst I;
     const Slot s = decode_slot_rec<SINGLE>(D, K, j, I);
@@ -1864,14 +1877,15 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     const int ns_guess = last_sweep >= 0 ? (cs0 != 0 ? cs0 : last_sweep + 1) : cs_inst;
     double winf = 0.0;
     if (!tiled && in && s.active && ns_guess >= 1) {
-        // phi^k of the last sweep, which matters on the boundary and in pinned cells only
-        if (pin || bnd[0] || bnd[1] || bnd[2] || bnd[3]) phi = sweep_in(D, ns_guess - 1)[j];
         phi_next = sweep_out(D, ns_guess - 1)[j];    // phi(T^{n+1}): the next step's phi^0
         if (witer) {
             // the last sweep's output and the boundary wave inflow of its wave flux
             rho_new = ((ns_guess & 1) ? D.rho_new : D.rho_alt)[j];
             winf = D.winflow[(int64_t)((ns_guess - 1) & 1) * K.n_cg + j];
         }
+        // phi^k of the last sweep, which matters on the boundary and in pinned cells only
+        // (after the others: the test waits for `pin`)
+        if (pin || bnd[0] || bnd[1] || bnd[2] || bnd[3]) phi = sweep_in(D, ns_guess - 1)[j];
     }
     int ns_single = 0;
     if (tiled && SINGLE) {
@@ -1958,53 +1972,14 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
         }
     } else if (!tiled && in && s.active) {
         D.phi0n[j] = phi_next;
-        Tf = D.T_new[cell];
     }
     // the commit's rho^{n+1} lives in rho_new
     if (!tiled && witer && in && s.active && !(ns_guess & 1)) D.rho_new[j] = rho_new;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
-    double* const dg = D.diag_sub + ((int64_t)s.inst * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8;
-    // the boundary's, the pinned cells' and the source's share of the balance: few
-    // wavefronts have any, and those add theirs by themselves
-    const bool at_wall = bnd[0] || bnd[1] || bnd[2] || bnd[3];
-    if (__ballot(at_wall || pin || src) != 0ull) {
-        if (!faces_early) load_faces();
-        if (TDEP && at_wall && (K.t_power != 0.0 || K.stim || K.table)) {
-            // temperature-dependent opacity: the boundary faces' coefficients at the
-            // step's final temperature (the iteration has converged on it)
-            const TabPtr mt = math_tab();
-            const double sk = K.table ? table_group_sigma(D, K, D.tab_mat[cell], I.edge_off + g, Tf)
-                                      : D.kappa[j] * temp_pow(Tf, K.t_power) * group_factor(D, K, I.edge_off, g, Tf);
-#pragma unroll
-            for (int q = 0; q < 2 * DIM; ++q)
-                if (bnd[q]) Df[q] = face_coef(K, mt, sk, (q >> 1) == 0 ? I.fcx : I.fcy);
-        }
-        // inflow_wave (WAVE_ITER), inflow_eq, exit, injection, inflow_particles
-        constexpr int NB = 5;
-        const int dst[NB] = {0, 1, 2, 3, 6};
-        double v[NB] = {winf, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < 2 * DIM; ++q) {
-            if (!bnd[q]) continue;
-            const double S = (q >> 1) == 0 ? I.dy : I.dx;
-            const int bc = I.bc[q];
-            const double pn = bc == BC_PLANCK ? pb[q] : (bc == BC_REFLECT ? phi : 0.0);
-            v[1] += K.dt * S * Df[q] * (pn - phi) / K.c;
-            v[2] += tal[q] / K.c;
-            v[4] += tal_in[q] / K.c;
-        }
-        if (pin) v[3] = I.V * (K.dt * D.sig[j] / (K.eps * K.eps)) * (phi - rho_new);
-        if (src) v[3] += I.V * K.dt * qs / K.c;
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            if (__ballot(v[q] != 0.0) == 0ull) continue;
-            const double t = wave_sum(v[q]);
-            if (lane == 0) atomicAdd(dg + dst[q], t);
-        }
-    }
-    // the energies before and after: per wavefront, then per run of the block's
-    // wavefronts of one instance (e_start 4, e_end 5)
-    double e0 = 0.0, e1 = 0.0;
+    // the energies before and after and the pinned cells' and the source's share of the
+    // balance: per wavefront, then per run of the block's wavefronts of one instance
+    // (e_start 4, e_end 5, injection 3)
+    double e0 = 0.0, e1 = 0.0, inj = 0.0;
     if (in && s.active) {
         e0 = I.V * rho / K.c;
         e1 = I.V * rho_new / K.c;
@@ -2017,34 +1992,74 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
             e1 += I.V * cv * T1;
         }
     }
+    if (__ballot(pin || src) != 0ull) {
+        if (pin) inj = I.V * (K.dt * D.sig[j] / (K.eps * K.eps)) * (phi - rho_new);
+        if (src) inj += I.V * K.dt * qs / K.c;
+        inj = wave_sum(inj);
+    }
     e0 = wave_sum(e0);
     e1 = wave_sum(e1);
-    __shared__ double wsum[DIAG_THREADS / WAVE][2];
-    __shared__ int winst[DIAG_THREADS / WAVE];
+    constexpr int NW = DIAG_THREADS / WAVE, NE = 3;
+    const int dst[NE] = {4, 5, 3};
+    __shared__ double wsum[NW][NE];
+    __shared__ int winst[NW];
     if (lane == 0) {
         wsum[wid][0] = e0;
         wsum[wid][1] = e1;
+        wsum[wid][2] = inj;
         winst[wid] = j < K.n_cg ? s.inst : -1;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int nw = DIAG_THREADS / WAVE;
-        int w0 = 0;
-        while (w0 < nw) {
-            int w1 = w0;
-            double a0 = 0.0, a1 = 0.0;
-            while (w1 < nw && winst[w1] == winst[w0]) {
-                a0 += wsum[w1][0];
-                a1 += wsum[w1][1];
-                ++w1;
-            }
-            if (winst[w0] >= 0) {
-                double* dq = D.diag_sub + ((int64_t)winst[w0] * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8;
-                atomicAdd(dq + 4, a0);
-                atomicAdd(dq + 5, a1);
-            }
-            w0 = w1;
+    if (threadIdx.x < NW * NE) {
+        // thread (w, q): quantity q of the run that starts at wavefront w
+        const int w = threadIdx.x / NE, q = threadIdx.x - NE * w, mine = winst[w];
+        const bool lead = mine >= 0 && (w == 0 || winst[w - 1] != mine);
+        bool same = lead;
+        double a = wsum[w][q];
+#pragma unroll
+        for (int d = 1; d < NW; ++d) {
+            const int o = min(w + d, NW - 1);
+            same = same && w + d < NW && winst[o] == mine;
+            a += same ? wsum[o][q] : 0.0;
         }
+        if (lead && a != 0.0)
+            atomicAdd(D.diag_sub + ((int64_t)mine * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8 + dst[q], a);
+    }
+    // the walls' share: few wavefronts have any, and those add theirs by themselves
+    const bool at_wall = bnd[0] || bnd[1] || bnd[2] || bnd[3];
+    if (__ballot(at_wall) == 0ull) return;
+    if (!faces_early) load_faces();
+    if (TDEP && at_wall && (K.t_power != 0.0 || K.stim || K.table)) {
+        // temperature-dependent opacity: the boundary faces' coefficients at the
+        // step's final temperature (the iteration has converged on it)
+        if (!tiled) Tf = D.T_new[cell];
+        const TabPtr mt = math_tab();
+        const double sk = K.table ? table_group_sigma(D, K, D.tab_mat[cell], I.edge_off + g, Tf)
+                                  : D.kappa[j] * temp_pow(Tf, K.t_power) * group_factor(D, K, I.edge_off, g, Tf);
+#pragma unroll
+        for (int q = 0; q < 2 * DIM; ++q)
+            if (bnd[q]) Df[q] = face_coef(K, mt, sk, (q >> 1) == 0 ? I.fcx : I.fcy);
+    }
+    // inflow_wave (WAVE_ITER), inflow_eq, exit, inflow_particles
+    constexpr int NB = 4;
+    const int to[NB] = {0, 1, 2, 6};
+    double v[NB] = {winf, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 2 * DIM; ++q) {
+        if (!bnd[q]) continue;
+        const double S = (q >> 1) == 0 ? I.dy : I.dx;
+        const int bc = I.bc[q];
+        const double pn = bc == BC_PLANCK ? pb[q] : (bc == BC_REFLECT ? phi : 0.0);
+        v[1] += K.dt * S * Df[q] * (pn - phi) / K.c;
+        v[2] += tal[q] / K.c;
+        v[3] += tal_in[q] / K.c;
+    }
+    double* const dg = D.diag_sub + ((int64_t)s.inst * DIAG_SUB + (blockIdx.x & (DIAG_SUB - 1))) * 8;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        if (__ballot(v[q] != 0.0) == 0ull) continue;
+        const double t = wave_sum(v[q]);
+        if (lane == 0) atomicAdd(dg + to[q], t);
     }
 }
 

@@ -112,7 +112,6 @@ struct Resid {
 struct InstState {
     int conv_sweeps;       // sweeps used by the converged source iteration, 0 = running (-1: a
                            // temperature failed, 1-D)
-    int bad;               // non-finite / non-positive temperature seen
     uint64_t births;       // birth counter B_n (carried from step to step)
 };
 

@@ -383,7 +383,6 @@ __global__ __launch_bounds__(COUNT_THREADS) void k_count(Dev D, Consts K, ZeroLi
         for (int q = threadIdx.x; q < K.n_inst; q += COUNT_THREADS) {
             InstState st;
             st.conv_sweeps = 0;
-            st.bad = 0;
             st.births = D.prev_ist[q].births;
             D.ist[q] = st;
         }
@@ -1449,7 +1448,8 @@ __host__ __device__ inline double* sweep_out(const Dev& D, int k) { return (k & 
 // decide launch sits between sweeps; block 0 records it.
 // FIRST: sweep 0 (its own instantiation, so that the wave-flux code does not
 // weigh on the registers of the later sweeps); SINGLE: a context of one
-// instance.  (1-D contexts take several sweeps per launch: si_tile.hip.)
+// instance, in the sweeps after the first of a fixed opacity (its others run by
+// patches: si_grid.hip).  (1-D contexts take several sweeps per launch: si_tile.hip.)
 // LIN: the linearized iteration. A sweep takes the new temperature's emission
 // as phi^k + phi'(T^k) (T^{k+1} - T^k) and solves each cell's energy balance
 // for T^{k+1}, a local Newton step with the literal iteration's fixed point
@@ -1459,7 +1459,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
                                                           double* phi_out, int decide_prev, const double* rho_in,
                                                           double* rho_out)
 {
-    constexpr int DIM = 2;
+    static_assert(!(FIRST && SINGLE), "a single instance's first sweep runs by patches");
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
     const uint32_t blk = SINGLE ? xcd_band(blockIdx.x, gridDim.x) : blockIdx.x;
     const int64_t j = (int64_t)blk * SI_THREADS + threadIdx.x;
@@ -1470,7 +1470,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     // once the block is known to run.
     const uint32_t now = *D.step;
     uint32_t flags = 0xFFFFFFFFu;
-    if (K.n_inst > 1 && !FIRST) flags = ((const uint32_t*)D.wave_run)[blockIdx.x];
+    if (!SINGLE && !FIRST) flags = ((const uint32_t*)D.wave_run)[blockIdx.x];
     int cs_prev = 0;
     Resid res_prev = {0ull, 0ull, 0ull, 0ull};
     if (decide_prev) {
@@ -1507,10 +1507,9 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
 
     // every load of the sweep is issued here, before the first wait
     const int nx = I.nx;
-    const int ix = DIM == 1 ? s.lcell : s.lcell % nx, iy = DIM == 1 ? 0 : s.lcell / nx;
+    const int ix = s.lcell % nx, iy = s.lcell / nx;
     const int cell = I.cell_off + s.lcell;
-    const CellFaces F = cell_faces<DIM>(I, j, ix, iy, g);
-    constexpr int nf = 2 * DIM;
+    const CellFaces F = cell_faces<2>(I, j, ix, iy, g);
     const double* phib = D.phib + (int64_t)s.inst * 4 * MAX_G;
     double phi = 0.0, Qj = 0.0, lam = 0.0, sig = 0.0, rho_prev = 0.0;
     double Df[4] = {0.0, 0.0, 0.0, 0.0}, pn[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1526,7 +1525,6 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         rho_prev = rho_in[j];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (q >= nf) continue;
             if (!TDEP) Df[q] = q < 2 ? D.Dx[F.fslot[q]] : D.Dy[F.fslot[q]];
             if (F.inside[q]) pn[q] = phi_in[F.nbj[q]];
             else if (I.bc[q] == BC_PLANCK) pn[q] = phib[q * MAX_G + g];
@@ -1552,7 +1550,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (q >= nf || !F.inside[q]) continue;
+            if (!F.inside[q]) continue;
             if (K.table) {
                 tsig_n[q] = tsig[F.nbj[q]];
                 continue;
@@ -1580,7 +1578,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         if (g == G - 1 && G == Gp) nu_top = D.nu[I.edge_off + G];
     }
     double inflow = 0.0;
-    if (FIRST && act) Qj = wave_source<DIM, EXT>(D, K, I, j, s, F, &inflow, D.rhoh, false);
+    if (FIRST && act) Qj = wave_source<2, EXT>(D, K, I, j, s, F, &inflow, D.rhoh, false);
 
     const bool run = wave_on && cs_inst == 0 && j < K.n_cg;
     double dr = 0.0, mr = 0.0, dT = 0.0, mT = 0.0;
@@ -1605,7 +1603,6 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
             lam = s_of_sigma(K, sk);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (q >= nf) continue;
                 double sf = sk;
                 if (F.inside[q]) {
                     const double sn = K.table ? tsig_n[q] : kap_n[q] * temp_pow(T_nb[q], K.t_power) * Sn[q];
@@ -1617,7 +1614,6 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         double lap = 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (q >= nf) continue;
             const double p = F.inside[q] ? pn[q] : (I.bc[q] == BC_REFLECT ? phi : pn[q]);
             lap += F.S[q] * Df[q] * (p - phi);
         }
@@ -1674,7 +1670,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         if (work && s.active) phi_new = phi_from_band(K.a, K.c, Tnew, planck_band_from_edges(xe, ve, xh, vh));
     }
     // stores
-    if (FIRST && K.n_inst > 1 && lane == 0) D.wave_run[(int64_t)blockIdx.x * (SI_THREADS / WAVE) + wid] = 1;
+    if (FIRST && lane == 0) D.wave_run[(int64_t)blockIdx.x * (SI_THREADS / WAVE) + wid] = 1;
     const int64_t rel = j - I.cg_off;
     if (run && rel >= 0 && rel < RES_SUB) {
         Resid z = {0ull, 0ull, 0ull, 0ull};
@@ -1695,7 +1691,6 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
     }
     if (work && g == 0) {
         if (bad) {
-            atomicOr(&D.ist[s.inst].bad, 1);
             atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_TEMP);
         }
         D.T_new[cell] = Tnew;
@@ -2376,14 +2371,14 @@ void launch_sort_scatter(int dim, const Dev& D, const Consts& K, const Pool& In,
     }
 }
 
-// the first sweep evaluates the wave flux: with slope terms or boundary-source
-// ghosts, its extended instantiation
-template <bool SINGLE, bool TDEP, bool LIN>
+// A batch's sweep; the first evaluates the wave flux: with slope terms or boundary-source
+// ghosts, its extended instantiation.
+template <bool TDEP, bool LIN>
 static auto sweep_kernel(const Consts& K, int k)
 {
-    if (k > 0) return k_si_sweep<false, SINGLE, TDEP, LIN, false>;
-    return (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) ? k_si_sweep<true, SINGLE, TDEP, LIN, true>
-                                                                           : k_si_sweep<true, SINGLE, TDEP, LIN, false>;
+    if (k > 0) return k_si_sweep<false, false, TDEP, LIN, false>;
+    return (K.flags & (UGKWP_FLAG_SLOPES | UGKWP_FLAG_BOUNDARY_PARTICLES)) ? k_si_sweep<true, false, TDEP, LIN, true>
+                                                                           : k_si_sweep<true, false, TDEP, LIN, false>;
 }
 
 // rho^m of the source iteration: rho^n for m = 0; from the wave flux of each
@@ -2424,9 +2419,9 @@ void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t
             launch_si_grid(D, K, k, sweep_in(D, k), sweep_out(D, k), decide_prev, rho_in, rho_out, st);
             continue;
         }
-        auto kern = fold ? (lin ? sweep_kernel<true, false, true>(K, k) : sweep_kernel<true, false, false>(K, k))
-                  : tdep ? (lin ? sweep_kernel<false, true, true>(K, k) : sweep_kernel<false, true, false>(K, k))
-                         : (lin ? sweep_kernel<false, false, true>(K, k) : sweep_kernel<false, false, false>(K, k));
+        auto kern = fold ? (lin ? k_si_sweep<false, true, false, true, false> : k_si_sweep<false, true, false, false, false>)
+                  : tdep ? (lin ? sweep_kernel<true, true>(K, k) : sweep_kernel<true, false>(K, k))
+                         : (lin ? sweep_kernel<false, true>(K, k) : sweep_kernel<false, false>(K, k));
         kern<<<blocks(K.n_cg, SI_THREADS), SI_THREADS, 0, st>>>(D, K, k, sweep_in(D, k), sweep_out(D, k), decide_prev,
                                                                 rho_in, rho_out);
         if (!fold) k_si_decide<<<blocks((int64_t)K.n_inst * WAVE, 256), 256, 0, st>>>(D, K, k);

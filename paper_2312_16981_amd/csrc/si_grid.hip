@@ -358,7 +358,6 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
     }
     if (ok && g == 0) {
         if (bad) {
-            atomicOr(&D.ist[0].bad, 1);
             atomicOr((unsigned long long*)(D.counters + CNT_ERR), ERR_TEMP);
         }
         D.T_new[cell] = Tnew;

@@ -42,7 +42,10 @@ PUSH_BYTES_DEAD = 4        # empty-slot mark of a particle absorbed or gone
 SPINUP = {"slab": 500, "lattice": 300, "batch": 100, "adjoint": 0, "thickthin": 200, "marshak": 100, "larsen": 100,
           "olson1d": 0, "olson2d": 0}
 ADJ_SWEEP_BYTES = 40       # rbar, sigma, phi' and two face coefficients per (cell, group) update (lambda is formed from sigma)
-SI_SWEEP_BYTES = 64        # Q, lambda, sigma, phi^k, rho^k, one face D read; rho^{k+1}, phi^{k+1} written
+SI_SWEEP_BYTES = 64        # 2-D: Q, lambda, sigma, phi^k, rho^k, one face D read; rho^{k+1}, phi^{k+1} written
+# 1-D: several sweeps per launch keep a slot's inputs in registers.  Read once a step: lambda, sigma, phi, rho, one face D,
+# and for Q the two wave coefficients, rho^h, the birth count and a face's crossings; per sweep rho, phi written
+SI_STEP_BYTES_1D, SI_SWEEP_BYTES_1D = 88, 16
 
 # HBM bytes per push of k_push measured with rocprofv3 FETCH_SIZE / WRITE_SIZE,
 # each scaled by its reading for a plain 1 GiB copy (FETCH_SIZE x 2.0, WRITE_SIZE
@@ -531,6 +534,10 @@ def main():
     cgu = sum(t["cg_updates"] for t in tots)
     ph_cgu = sum(t["cg_updates"] for t in ptot)
     ms_si_ph = sum(t["ms_si"] for t in ptot)
+    if probs[0].dim == 1:
+        si_bytes = SI_STEP_BYTES_1D * nph * sum(p.ncell * p.G for p in probs) + SI_SWEEP_BYTES_1D * ph_cgu
+    else:
+        si_bytes = SI_SWEEP_BYTES * ph_cgu
 
     value = pushes / elapsed
     br, bw, bd = (PUSH_BYTES_READ, PUSH_BYTES_WRITE, PUSH_BYTES_DEAD) if probs[0].dim == 1 else BYTES_2D
@@ -585,21 +592,20 @@ def main():
     if ms_si_ph > 0:
         # the source-iteration phase as a second roofline object (every sweep and decide
         # launch between two events, from the phase-timed steps)
-        si_ach = SI_SWEEP_BYTES * ph_cgu / (ms_si_ph * 1e-3) / 1e9
+        si_ach = si_bytes / (ms_si_ph * 1e-3) / 1e9
         si_kern = "k_si_tile" if probs[0].dim == 1 else "k_si_grid and k_si_sweep"
         out["roofline_si"] = {"bound": "hbm", "achieved": si_ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": si_ach / HBM_PEAK_GBS, "kernel": f"{si_kern} (the source-iteration phase)",
-                              "algorithmic_bytes_per_update": SI_SWEEP_BYTES,
+                              "algorithmic_bytes_per_update": si_bytes / ph_cgu,
                               "from": f"{nph} further steps with every phase timed"}
     if wl == "batch" and ms_si_ph > 0:
         # the source iteration dominates the batched step: its phase (every sweep and
         # decide launch between two events) is the roofline kernel, the push is kept
-        si_ach = SI_SWEEP_BYTES * ph_cgu / (ms_si_ph * 1e-3) / 1e9
         out["roofline_push"] = out["roofline"]
         out["roofline"] = {"bound": "hbm", "achieved": si_ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": si_ach / HBM_PEAK_GBS, "traffic": None,
                            "kernel": "k_si_tile (the source-iteration phase: rounds of sweeps and decides)",
-                           "algorithmic_bytes_per_update": SI_SWEEP_BYTES,
+                           "algorithmic_bytes_per_update": si_bytes / ph_cgu,
                            "from": f"{nph} further steps with every phase timed"}
     if wl == "batch" and not args.per_instance and not args.no_compare:
         del ctxs

@@ -93,8 +93,8 @@ __host__ __device__ inline void keyed_uniform_pair(uint64_t seed, uint64_t id, u
 
 // ---------------------------------------------------------------------------
 // Polynomial coefficients of the functions below, interpolated in 60-digit
-// arithmetic at the Chebyshev nodes of each interval, in ascending order.  They
-// are read from constant memory with scalar loads (math_tab) and enter each
+// arithmetic at the Chebyshev nodes of each interval (gen_math_tab.py), in ascending
+// order.  They are read from constant memory with scalar loads (math_tab) and enter each
 // multiply-add as a scalar operand (horner): as literals every one of them cost two
 // vector moves beside its multiply-add, 40% of a source-iteration sweep's vector
 // instructions.

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_prep(Dev D, Consts K, Adj A
             const double phi = phi_from_band(K.a, K.c, T, planck_band_from_edges(xe, ve, xh, vh));
             const double T3 = T * T * T;
             A.phi[j] = phi;
-            A.dphi[j] = 4.0 * phi / T + K.a * K.c * T3 * (we - wh) * UGK_15_PI4;
+            A.dphi[j] = 4.0 * phi / T + K.a * K.c * T3 * over_pi4_15(we - wh);
         } else {
             A.phi[j] = 0.0;
             A.dphi[j] = 0.0;

@@ -101,6 +101,7 @@ __host__ __device__ inline void keyed_uniform_pair(uint64_t seed, uint64_t id, u
 struct MathTab {
     double head[11], weight[11], L1[11], L2[10], L3[10], L4[9];   // Planck edge integrals
     double ex[10];        // (e^{-r} - 1 + r) / r^2 on |r| <= ln 2 / 2
+    double exf[11];       // the same within 5e-18
     double one_ex[15];    // (1 - e^{-x}) / x on [0, 2]
     double w[12];         // (C4 - e^{-s}) / s on [0, 1]
     double c2[15];        // (C2/dt) / s on [0, 2]
@@ -145,6 +146,11 @@ static __device__ __constant__ MathTab g_math_tab = {
         0x1.0000000000001p-1, -0x1.5555555555556p-3, 0x1.5555555553d63p-5, -0x1.11111111109b3p-7, 0x1.6c16c1788bd90p-10,
         -0x1.a01a01a7c41d5p-13, 0x1.a019b90d2ae7ap-16, -0x1.71de0dae63bb3p-19, 0x1.289185613a3d6p-22,
         -0x1.af38a9b0ec855p-26},
+    // exf
+    {
+        0x1.0000000000000p-1, -0x1.5555555555557p-3, 0x1.5555555555556p-5, -0x1.11111111100dcp-7, 0x1.6c16c16c162d4p-10,
+        -0x1.a01a01abe7fe1p-13, 0x1.a01a01a6d889cp-16, -0x1.71de0231960ebp-19, 0x1.27e4db646b17ep-22,
+        -0x1.af4de97ca4194p-26, 0x1.1f730349868cep-29},
     // one_ex
     {
         0x1.0000000000000p+0, -0x1.ffffffffffffbp-2, 0x1.55555555553e2p-3, -0x1.555555554ff99p-5, 0x1.111111106b15bp-7,
@@ -334,11 +340,48 @@ __device__ inline double exp_neg(const Tab& t, double x)
     return ldexp(p, -(int)k);
 }
 
-// 1 - e^{-x} for x >= 0, without cancellation below 2.
+// e^{-x} in two parts, 2^-k (hi + lo): with the rounding errors of r and of 1 - r, and q of
+// degree 10 (within 5e-18).
+struct ExpParts {
+    double hi, lo;
+    int k;
+};
+
+__device__ inline ExpParts exp_parts(TabPtr t, double x)
+{
+    x = fmin(fmax(x, -800.0), 800.0);
+    const double k = rint(x * 0x1.71547652b82fep+0), a = fma(-k, 0x1.62e42fef00000p-1, x);
+    const double r = fma(-k, 0x1.473de6af278edp-34, a), dr = fma(-k, 0x1.473de6af278edp-34, a - r);
+    const double h = 1.0 - r, l = fma(r * r, poly<11>(t->exf, r), ((1.0 - h) - r) - dr), hi = h + l;
+    return {hi, l - (hi - h), (int)k};
+}
+
+// e^{-x} where its own rounding is the result's: 1.11e-16 at most, as libm's (exp_neg: 1.43e-16).
+__device__ inline double exp_neg_fine(TabPtr t, double x)
+{
+    const ExpParts e = exp_parts(t, x);
+    return ldexp(e.hi, -e.k);
+}
+
+// 1 - e^{-x} for x >= 0: within 1.41e-16, as expm1.
 __device__ inline double one_less_exp_neg(TabPtr t, double x)
 {
-    return x < 2.0 ? x * poly<15>(t->one_ex, x) : 1.0 - exp_neg(t, x);
+    const ExpParts e = exp_parts(t, x);
+    const double hi = ldexp(e.hi, -e.k), w = 1.0 - hi;
+    return w + (((1.0 - w) - hi) - ldexp(e.lo, -e.k));
 }
+
+// n / d with r = 1/d at hand: one correction of n r (the quotient to the last
+// bit but for rare half-way cases), 3 instructions instead of a division's 11.
+__host__ __device__ inline double quotient(double n, double d, double r)
+{
+    const double q = n * r;
+    return fma(fma(-d, q, n), r, q);
+}
+
+// v / 6 (Simpson's rule) and v / (pi^4 / 15)
+__host__ __device__ inline double sixth(double v) { return quotient(v, 6.0, 1.0 / 6.0); }
+__host__ __device__ inline double over_pi4_15(double v) { return quotient(v, UGK_PI4_15, UGK_15_PI4); }
 
 // ---------------------------------------------------------------------------
 // Planck band integrals.  head(x) = int_0^x t^3/(e^t-1) dt below x = 2,
@@ -425,7 +468,7 @@ __device__ inline double planck_band_from_edges(double xl, double vl, double xh,
 __device__ inline double phi_from_band(double a, double c, double T, double band)
 {
     const double T2 = T * T;
-    return a * c * T2 * T2 * band * UGK_15_PI4;
+    return a * c * T2 * T2 * over_pi4_15(band);
 }
 
 // ---------------------------------------------------------------------------
@@ -468,14 +511,6 @@ constexpr SeriesCoefs kSeries = make_series_coefs();
 __device__ inline double coef_w(TabPtr t, double s)
 {
     return s < 1.0 ? s * poly<12>(t->w, s) : coef_c4(t, s) - exp_neg(t, s);
-}
-
-// n / d with r = 1/d at hand: one correction of n r (the quotient to the last
-// bit but for rare half-way cases), 3 instructions instead of a division's 11.
-__host__ __device__ inline double quotient(double n, double d, double r)
-{
-    const double q = n * r;
-    return fma(fma(-d, q, n), r, q);
 }
 
 // C2/dt = [2 C4 - 1 - e^{-s}] / s from s = 2 on; below, where that cancels, s times the

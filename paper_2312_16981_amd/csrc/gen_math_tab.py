@@ -44,6 +44,8 @@ def coefficients():
         # (e^{-r} - 1 + r) / r^2
         t["ex"] = interpolate(lambda r: sum((-1) ** n * r ** (n - 2) / mp.factorial(n) for n in range(2, 40)),
                               -half, half, 9)
+        t["exf"] = interpolate(lambda r: sum((-1) ** n * r ** (n - 2) / mp.factorial(n) for n in range(2, 40)),
+                               -half, half, 10)
         # (1 - e^{-x}) / x
         t["one_ex"] = interpolate(lambda x: sum((-1) ** n * x ** n / mp.factorial(n + 1) for n in range(60)),
                                   zero, two, 14)

@@ -153,7 +153,7 @@ __global__ void k_tables(Dev D, Consts K)
     D.sig[j] = sg;
     D.sv[j] = sv;
     const TabPtr t = math_tab();
-    D.es[j] = exp_neg(t, sv);
+    D.es[j] = exp_neg_fine(t, sv);
     D.c4[j] = coef_c4(t, sv);
     D.wc[j] = coef_w(t, sv);
 }
@@ -1591,7 +1591,7 @@ __global__ __launch_bounds__(SI_THREADS) void k_si_sweep(Dev D, Consts K, int k,
         const double we = edge_lane ? planck_edge_weight(mt, nu_lo / Tk) : 0.0;
         double wh = next_lane(we);
         if (work && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / Tk);
-        if (work && s.active) dph = 4.0 * phi / Tk + K.a * K.c * (Tk * Tk * Tk) * (we - wh) * UGK_15_PI4;
+        if (work && s.active) dph = 4.0 * phi / Tk + K.a * K.c * (Tk * Tk * Tk) * over_pi4_15(we - wh);
     }
     double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0, rl = 1.0;    // rl = 1 / (1 + lambda)
     if (work && s.active) {

@@ -22,8 +22,8 @@ __device__ __forceinline__ double group_factor(const Dev& D, const Consts& K, in
 {
     if (!K.stim) return D.simpson[edge_off + g];
     const double nl = D.nu[edge_off + g], nh = D.nu[edge_off + g + 1], nm = 0.5 * (nl + nh);
-    return (nu_pow(nl, K.nu_power) * stim_factor(K, nl, T) + 4.0 * nu_pow(nm, K.nu_power) * stim_factor(K, nm, T)
-            + nu_pow(nh, K.nu_power) * stim_factor(K, nh, T)) * (1.0 / 6.0);
+    return sixth(nu_pow(nl, K.nu_power) * stim_factor(K, nl, T) + 4.0 * nu_pow(nm, K.nu_power) * stim_factor(K, nm, T)
+                 + nu_pow(nh, K.nu_power) * stim_factor(K, nh, T));
 }
 
 // Group opacity from the table (Sec. 3.4-3.5's printed opacities, tabulated by the
@@ -44,7 +44,9 @@ __device__ inline TablePlace table_place(const Dev& D, const Consts& K, int m, d
     return p;
 }
 
-// sigma at Simpson point p (0 lower edge, 1 midpoint, 2 upper edge) of the group at edge e
+// sigma at Simpson point p (0 lower edge, 1 midpoint, 2 upper edge) of the group at edge e.
+// (The rounding of ln sigma, up to some 1e-15 of sigma, outweighs exp_neg's: exp_neg_fine
+// here cost 3% of Olson's 2-D sweeps.)
 __device__ inline double table_point(const Dev& D, const Consts& K, TabPtr mt, const TablePlace& t, int e, int p)
 {
     const double a = D.tab_ga[3 * e + p];
@@ -60,7 +62,7 @@ __device__ inline double table_group_sigma(const Dev& D, const Consts& K, int m,
     const TabPtr mt = math_tab();
     const TablePlace t = table_place(D, K, m, T);
     const double v0 = table_point(D, K, mt, t, e, 0), v1 = table_point(D, K, mt, t, e, 1);
-    return (v0 + 4.0 * v1 + table_point(D, K, mt, t, e, 2)) * (1.0 / 6.0);
+    return sixth(v0 + 4.0 * v1 + table_point(D, K, mt, t, e, 2));
 }
 
 // The same for the groups of a cell in consecutive lanes (g of Gp, edges g <= G, `on` for
@@ -79,7 +81,7 @@ __device__ inline double table_group_sigma_lanes(const Dev& D, const Consts& K, 
     }
     double v2 = next_lane(v0);
     if (on && g == G - 1 && G == Gp) v2 = table_point(D, K, mt, t, e, 2);
-    return (v0 + 4.0 * v1 + v2) * (1.0 / 6.0);
+    return sixth(v0 + 4.0 * v1 + v2);
 }
 
 // T^-q; the paper's q = 1/2 without pow().

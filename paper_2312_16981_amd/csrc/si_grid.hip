@@ -23,8 +23,13 @@ constexpr int GRID_LG = 9, GRID_THREADS = 1 << GRID_LG;
 __host__ __device__ inline int grid_lx(int lg) { return (GRID_LG - lg + 1) >> 1; }
 __host__ __device__ inline int grid_ly(int lg) { return (GRID_LG - lg) >> 1; }
 
+// Three blocks of 8 wavefronts per CU where the registers nearly allow it by themselves: 81 of
+// them left two (the first sweep of the mesh above 116 -> 137 us).
+template <int OP, bool EXT>
+constexpr int grid_min_waves() { return OP == OP_TABLE && !EXT ? 6 : 1; }
+
 template <bool FIRST, int OP, bool LIN, bool EXT>
-__global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k, const double* phi_in,
+__global__ __launch_bounds__(GRID_THREADS) __attribute__((amdgpu_waves_per_eu(grid_min_waves<OP, EXT>()))) void k_si_grid(Dev D, Consts K, int k, const double* phi_in,
                                                           double* phi_out, int decide_prev, const double* rho_in,
                                                           double* rho_out)
 {
@@ -242,7 +247,7 @@ __global__ __launch_bounds__(GRID_THREADS) void k_si_grid(Dev D, Consts K, int k
         const double we = ok && g <= G ? planck_edge_weight(mt, nu_lo / ht.Tk) : 0.0;
         double wh = next_lane(we);
         if (ok && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / ht.Tk);
-        if (act) dph = 4.0 * phi / ht.Tk + K.a * K.c * (ht.Tk * ht.Tk * ht.Tk) * (we - wh) * UGK_15_PI4;
+        if (act) dph = 4.0 * phi / ht.Tk + K.a * K.c * (ht.Tk * ht.Tk * ht.Tk) * over_pi4_15(we - wh);
     }
     if (TDEP) __syncthreads();
     double contrib = 0.0, dcon = 0.0, r = 0.0, b = 0.0, rl = 1.0;    // rl = 1 / (1 + lambda)

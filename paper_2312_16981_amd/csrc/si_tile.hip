@@ -241,7 +241,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
             const double we = ok && g <= G ? planck_edge_weight(mt, nu_lo / ht[r].Tk) : 0.0;
             double wh = next_lane(we);
             if (ok && g == G - 1 && G == Gp) wh = planck_edge_weight(mt, nu_top / ht[r].Tk);
-            if (act) dph[r] = 4.0 * phi[r] / ht[r].Tk + K.a * K.c * (ht[r].Tk * ht[r].Tk * ht[r].Tk) * (we - wh) * UGK_15_PI4;
+            if (act) dph[r] = 4.0 * phi[r] / ht[r].Tk + K.a * K.c * (ht[r].Tk * ht[r].Tk * ht[r].Tk) * over_pi4_15(we - wh);
         }
     }
     __syncthreads();
@@ -396,7 +396,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
                 rho[r] = rr;
                 phi[r] = pn;
                 Pn[l] = pn;
-                if (LIN) dph[r] = 4.0 * pn / Tnew + K.a * K.c * (Tnew * Tnew * Tnew) * (we - wh) * UGK_15_PI4;
+                if (LIN) dph[r] = 4.0 * pn / Tnew + K.a * K.c * (Tnew * Tnew * Tnew) * over_pi4_15(we - wh);
             }
             if (TDEP && m + 1 < rd.ns) {
                 if (TABLE) {

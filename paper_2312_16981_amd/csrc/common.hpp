@@ -89,6 +89,7 @@ struct Consts {
     // beyond the step before's, blocks, threads per block and cells per thread
     int tile_S, tile_H, tile_cap, tile_extra, tile_blocks, tile_threads, tile_cpt;
     int tile_reg;          // the Planck coefficients of the tile sweeps in registers
+    int tile_fold;         // a single instance's stopping test is taken by every block of the next launch
     int64_t n_cap;
     int64_t pool_cap;
     uint32_t flags;

@@ -636,7 +636,7 @@ struct ugkwp_ctx {
 
     void setup_tiles(Dev& d)
     {
-        K.tile_S = K.tile_H = K.tile_cap = K.tile_extra = K.tile_blocks = K.tile_threads = K.tile_cpt = K.tile_reg = 0;
+        K.tile_S = K.tile_H = K.tile_cap = K.tile_extra = K.tile_blocks = K.tile_threads = K.tile_cpt = K.tile_reg = K.tile_fold = 0;
         if (!tiled()) return;
         const size_t ncg = (size_t)K.n_cg;
         // sweep planes kept: as many as a launch of a small context takes, fewer for
@@ -688,24 +688,43 @@ struct ugkwp_ctx {
         d.tile_start = ds;
     }
 
-    // The tile shape of a single instance's next steps, for `sweeps` sweeps each: the
-    // block size and sweeps per round with the least estimated time, from a round's
-    // fixed cost (launch, loads, residuals: about 5 us), a sweep's chain (0.8 us) and
-    // its instructions (0.5 us per wavefront and SIMD, 1 us with a T-dependent opacity).
+    // The tile shape of a single instance's next steps, for `sweeps` sweeps each (the last of
+    // them beyond the step before's): the block size and sweeps per round with the least
+    // estimated time, from a round's fixed cost (launch, loads, residuals: about 5 us), a
+    // sweep's chain (0.8 us) and its instructions (0.5 us per wavefront and SIMD, 1 us with a
+    // T-dependent opacity).  Beyond three wavefronts a SIMD the loads of a round count too (1.2 us
+    // per wavefront and SIMD, twice that with the wave flux of every iterate: HBM), only the
+    // sweeps that a step takes do (r0 of round 0, S of each further one), and blocks of
+    // 128 and of 1024 threads take 1.3 times as long (100000 x 64 slots, one sweep a round:
+    // 128 to 1024 threads 470, 345, 343, 459 us).
+    static constexpr int64_t TILE_FULL = 3 * 64 * 1024;
+    // Up to this many tiles every block of the next launch takes the stopping test from all
+    // their entries, beyond it a launch of one block does: entries times blocks grow with the
+    // square of the mesh.  A step of 4000 x 64 slots (334 tiles) 67 us against 71 with the
+    // launch, 8000 x 64 (667) 94 and 95, (1334) 187 and 186, 30000 x 64 (5000) 635 and 364.
+    static constexpr int TILE_FOLD = 1024;
+
     void plan_tiles(int sweeps)
     {
         if (!tiled() || n_inst > 1) return;
         const Inst& I = inst[0];
+        const bool full = K.n_cg > TILE_FULL;
         double best = 1e300;
         for (int bt = 128; bt <= tile_max_threads(tile_tdep(), false); bt *= 2)
             for (int S = 1; S <= K.tile_cap; ++S) {
                 const int C = bt / I.Gp, W = C - 2 * tile_halo(S);
                 if (C < 2 || W < 1) continue;
                 const int64_t nb = (I.nx + W - 1) / W;
-                const double waves = std::max(bt / 256.0, (double)nb * bt / 64.0 / 1024.0);
+                const double per_simd = (double)nb * bt / 64.0 / 1024.0, waves = std::max(bt / 256.0, per_simd);
                 const double sweep = 0.8 + (tile_wit() ? 0.8 : 0.0) + (tile_tdep() ? 1.0 : 0.5) * waves;
                 const int rounds = (sweeps + S - 1) / S;
-                const double t = rounds * (5.0 + std::min(S, sweeps) * sweep);
+                double t = rounds * (5.0 + std::min(S, sweeps) * sweep);
+                if (full) {
+                    const int need = std::max(sweeps - 1, 1), r0 = std::min(need + 1, S), more = std::max(need - r0 + S - 1, 0) / S;
+                    t = (1 + more) * (5.0 + (tile_wit() ? 2.4 : 1.2) * per_simd) + (r0 + more * S) * sweep +
+                        4.0 * (rounds - 1 - more);
+                    if (bt == 128 || bt == 1024) t *= 1.3;
+                }
                 if (t < best) {
                     best = t;
                     K.tile_threads = bt;
@@ -717,8 +736,10 @@ struct ugkwp_ctx {
                     // sweep leaves room for them: a round of 300 x 24 slots 14.7 -> 13.7 us; with
                     // a T-dependent opacity they spill (Larsen's 27.5 -> 29.5, Olson's 19.2 -> 20.3)
                     K.tile_reg = !tile_wit() && !tile_tdep() && bt <= 512 && nb <= 256;
+                    K.tile_fold = nb <= TILE_FOLD;
                 }
             }
+        if (best == 1e300) fail(UGKWP_EHIP, "internal error: no tile shape for %d groups", I.G);
     }
 
     // Launches that take one sweep more than `last`: sweeps themselves, or rounds of tiles

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
     const int lane = threadIdx.x & (WAVE - 1);
     warm_args<sizeof(Dev) + sizeof(Consts)>();
     const uint32_t now = *D.step;
-    if (!FIRST && SINGLE) tile_gather(D, K, round - 1, dec);
+    if (!FIRST && SINGLE && K.tile_fold) tile_gather(D, K, round - 1, dec);
     if (!(K.gate == GATE_OFF || now == K.gate)) return;
     // the block's instance and tile
     Inst I;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
     }
     const TilePlan plan = tile_plan(K, D.prev_ist[inst].conv_sweeps);
     if (!FIRST) {
-        if (SINGLE) {
+        if (SINGLE && K.tile_fold) {
             __syncthreads();
             const int out = tile_outcome(K, round - 1, plan, dec);
             if (out != 0) {
@@ -452,6 +452,31 @@ __global__ void k_tile_decide(Dev D, Consts K, int round)
     }
 }
 
+// The same for a single instance of many tiles, by one block.  (Every block of the next
+// launch reading every entry is quadratic in the mesh.)
+constexpr int DECIDE_THREADS = 1024;
+__global__ __launch_bounds__(DECIDE_THREADS) void k_tile_decide_one(Dev D, Consts K, int round)
+{
+    if (!gate_open(D, K, 0) || D.ist[0].conv_sweeps != 0) return;
+    const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE;
+    const TileRound q = tile_round(K, tile_plan(K, D.prev_ist[0].conv_sweeps), round);
+    __shared__ Resid part[DECIDE_THREADS / WAVE];
+    for (int m = 0; m < q.ns; ++m) {
+        const Resid x = tile_wave_most(tile_most(D, K, round, m, threadIdx.x, K.tile_blocks, DECIDE_THREADS));
+        if (lane == 0) part[wid] = x;
+        __syncthreads();
+        Resid y = {0ull, 0ull, 0ull, 0ull};
+        if (lane < DECIDE_THREADS / WAVE) y = part[lane];
+        const int v = tile_verdict(K, tile_wave_most(y));      // every wavefront the same
+        if (v != 0) {
+            // (all wavefronts have read `conv_sweeps` before the first barrier)
+            if (threadIdx.x == 0) tile_record(D, 0, v > 0 ? q.k0 + m + 1 : -1);
+            return;
+        }
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 
@@ -498,6 +523,7 @@ void launch_si_rounds(const Dev& D, const Consts& K, int r0, int r1, hipStream_t
             if (op == OP_TABLE) lin ? tile_mode<true, OP_TABLE, true>(D, K, r, st) : tile_mode<true, OP_TABLE, false>(D, K, r, st);
             else if (op == OP_POWER) lin ? tile_mode<true, OP_POWER, true>(D, K, r, st) : tile_mode<true, OP_POWER, false>(D, K, r, st);
             else lin ? tile_mode<true, OP_FIXED, true>(D, K, r, st) : tile_mode<true, OP_FIXED, false>(D, K, r, st);
+            if (!K.tile_fold) k_tile_decide_one<<<1, DECIDE_THREADS, 0, st>>>(D, K, r);
         } else {
             if (op == OP_TABLE) lin ? tile_mode<false, OP_TABLE, true>(D, K, r, st) : tile_mode<false, OP_TABLE, false>(D, K, r, st);
             else if (op == OP_POWER) lin ? tile_mode<false, OP_POWER, true>(D, K, r, st) : tile_mode<false, OP_POWER, false>(D, K, r, st);

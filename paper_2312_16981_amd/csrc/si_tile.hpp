@@ -77,18 +77,17 @@ __device__ inline Resid* tile_res(const Dev& D, const Consts& K, int round, int 
     return D.tile_res + ((int64_t)(round & 1) * K.tile_cap + m) * K.tile_blocks;
 }
 
-// The stopping test of one sweep from its blocks' entries b0 .. b1-1, by a
-// wavefront: 1 converged, 0 not, -1 a temperature was non-positive or not finite.
-__device__ inline int tile_test(const Dev& D, const Consts& K, int round, int m, int b0, int b1, int lane)
+// The maxima of a sweep's entries b, b + step, .. below b1, for one thread.
+__device__ inline Resid tile_most(const Dev& D, const Consts& K, int round, int m, int b, int b1, int step)
 {
     const Resid* res = tile_res(D, K, round, m);
     Resid x = {0ull, 0ull, 0ull, 0ull};
-    for (int b = b0 + lane; b < b1; b += 4 * WAVE) {
+    for (; b < b1; b += 4 * step) {
         Resid y[4];            // four entries in flight
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             y[q] = Resid{0ull, 0ull, 0ull, 0ull};
-            if (b + q * WAVE < b1) y[q] = res[b + q * WAVE];
+            if (b + q * step < b1) y[q] = res[b + q * step];
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -98,14 +97,32 @@ __device__ inline int tile_test(const Dev& D, const Consts& K, int round, int m,
             x.T = max(x.T, y[q].T);
         }
     }
-    const double drho = bitsd(wave_max_bits(bitsd(x.drho))), mrho = bitsd(wave_max_bits(bitsd(x.rho)));
-    const double dT = bitsd(wave_max_bits(bitsd(x.dT))), mT = bitsd(wave_max_bits(bitsd(x.T)));
+    return x;
+}
+
+// The maxima over a wavefront's lanes.
+__device__ inline Resid tile_wave_most(const Resid& x)
+{
+    return {wave_max_bits(bitsd(x.drho)), wave_max_bits(bitsd(x.rho)), wave_max_bits(bitsd(x.dT)), wave_max_bits(bitsd(x.T))};
+}
+
+// The stopping test of a sweep from its maxima: 1 converged, 0 not, -1 a temperature was
+// non-positive or not finite.
+__device__ inline int tile_verdict(const Consts& K, const Resid& x)
+{
+    const double drho = bitsd(x.drho), mrho = bitsd(x.rho), dT = bitsd(x.dT), mT = bitsd(x.T);
     if (mT != mT) return -1;
     return drho <= K.si_tol * mrho && dT <= K.si_tol * mT ? 1 : 0;
 }
 
-// The outcome after a round for the only instance of a context, taken by every
-// thread of a block alike, in two parts: tile_gather tests every plane of the round
+// The test by a wavefront, from its blocks' entries b0 .. b1-1.
+__device__ inline int tile_test(const Dev& D, const Consts& K, int round, int m, int b0, int b1, int lane)
+{
+    return tile_verdict(K, tile_wave_most(tile_most(D, K, round, m, b0 + lane, b1, WAVE)));
+}
+
+// The outcome after a round for the only instance of a context (K.tile_fold: of few
+// tiles), taken by every thread of a block alike, in two parts: tile_gather tests every plane of the round
 // (a wavefront per plane; without waiting for the number of sweeps it took, so that
 // its loads go out with the kernel's first) and reads the recorded state once per
 // block (block 0 of the launch may record it meanwhile); after a barrier tile_outcome
@@ -134,7 +151,7 @@ __device__ inline int tile_outcome(const Consts& K, int round, const TilePlan& p
 }
 
 // Record the outcome of the iteration (block 0 of a single instance's launch, or
-// the decide kernel of a batch): the sweep count, or the failed temperature.
+// a decide kernel): the sweep count, or the failed temperature.
 __device__ inline void tile_record(const Dev& D, int inst, int out)
 {
     D.ist[inst].conv_sweeps = out;

@@ -1774,26 +1774,29 @@ constexpr int DIAG_THREADS = 256;
 // registers).
 // What bounds it: the chain of waits of a block, some 5 us, and the blocks in flight.
 // The walls' terms, which few wavefronts have, are formed last, when the energies no longer
-// hold registers (44 instead of 62 in 2-D, 64 instead of 104 with TDEP, which spills in
-// those terms alone), and 8 wavefronts a SIMD fit everywhere but in a single 1-D
-// instance, whose few blocks are all in flight and only get longer by spilling (128 x 24
-// slots: 9.6 us, 12 with the floor).  285 x 285 cells of 24 groups: 69 -> 42 us (11 of them by
-// the source's share in the block's sum instead of an atomic per wavefront), 256 x 256 of
-// 32: 37 -> 33, 256 slabs: 228 -> 158.
-template <int DIM, bool TDEP>
-constexpr int finish_min_waves() { return DIM == 2 && TDEP ? 8 : 1; }
+// hold registers.  FULL: more blocks than the chip holds at once (8 a CU).  There the walls'
+// loads wait too and the registers are kept to 8 wavefronts a SIMD (44 instead of 62 in 2-D, 64
+// instead of 104 with TDEP, which spills in the walls' terms alone).  Where all blocks run at
+// once the commit is as long as its longest wavefront, and spilling only lengthens it (128 x 24
+// slots 9.6 us, 12 with the floor); touching all arguments at the start and reading uniform
+// words by vector loads shorten that (2 slabs of 100 x 10: a step 58 us, 62 without) but stand
+// in the way of many blocks' loads (256 slabs: 158 us, 238 with them).  285 x 285 cells of 24
+// groups: 69 -> 43 us (11 of them by the source's share in the block's sum instead of an atomic
+// per wavefront), 256 x 256 of 32: 37 -> 30, 256 slabs: 228 -> 162.
+constexpr unsigned FINISH_FULL = 2048;
 
-template <bool SINGLE, int DIM, bool TDEP>
-__global__ __launch_bounds__(DIAG_THREADS) __attribute__((amdgpu_waves_per_eu(finish_min_waves<DIM, TDEP>())))
+template <int DIM, bool TDEP, bool FULL>
+constexpr int finish_min_waves() { return DIM == 2 && TDEP && FULL ? 8 : 1; }
+
+template <bool SINGLE, int DIM, bool TDEP, bool FULL>
+__global__ __launch_bounds__(DIAG_THREADS) __attribute__((amdgpu_waves_per_eu(finish_min_waves<DIM, TDEP, FULL>())))
 void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
 {
     const int64_t j = (int64_t)blockIdx.x * DIAG_THREADS + threadIdx.x;
     // the loads come first (nothing is stored before the gate): step count,
     // the stopping state of the last sweep (one instance), the slot's data
-    // (a batch fills the chip many times over: there both only stand in the way of its other
-    // loads, 238 against 158 us)
-    if (SINGLE) warm_args<sizeof(Dev) + sizeof(Consts)>();
-    const int z = SINGLE ? lane_zero() : 0;
+    if (!FULL) warm_args<sizeof(Dev) + sizeof(Consts)>();
+    const int z = FULL ? 0 : lane_zero();
     const uint32_t now = D.step[z];
     Inst I;
     const Slot s = decode_slot_rec<SINGLE>(D, K, j, I);
@@ -1841,9 +1844,10 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
             bnd[q] = q < 2 ? (lo ? ix == 0 : ix == nx - 1) : (lo ? iy == 0 : iy == I.ny - 1);
         }
     }
-    // a boundary slot's faces: with the other loads for a single 1-D instance, whose
-    // commit is as long as its longest wavefront; else where they are used (the few
-    // boundary wavefronts wait once more, and the others keep fewer registers)
+    // a boundary slot's faces: with the other loads where all blocks run at once, and the
+    // commit of a single instance is as long as its longest wavefront (48 x 48 cells of 8
+    // groups 7.0 us, 7.8 with the faces late); else where they are used (the few boundary
+    // wavefronts wait once more, and the others keep fewer registers)
     auto load_faces = [&]() {
         const double* phib = D.phib + (int64_t)s.inst * 4 * MAX_G;
 #pragma unroll
@@ -1858,7 +1862,7 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
             if (I.bc[q] == BC_PLANCK) pb[q] = phib[q * MAX_G + g];
         }
     };
-    constexpr bool faces_early = SINGLE && DIM == 1;
+    constexpr bool faces_early = SINGLE && !FULL;
     if (faces_early) load_faces();
     __shared__ int dec[TILE_S_MAX + 1];
     if (tiled && SINGLE && K.tile_fold) tile_gather(D, K, last_sweep, dec);
@@ -2431,16 +2435,25 @@ void launch_si_sweeps(const Dev& D, const Consts& K, int k0, int k1, hipStream_t
     }
 }
 
+template <int DIM, bool TDEP, bool FULL>
+static auto finish_kernel(const Consts& K)
+{
+    return K.n_inst == 1 ? k_finish<true, DIM, TDEP, FULL> : k_finish<false, DIM, TDEP, FULL>;
+}
+
+template <int DIM, bool TDEP>
+static auto finish_kernel(const Consts& K, unsigned nb)
+{
+    return nb > FINISH_FULL ? finish_kernel<DIM, TDEP, true>(K) : finish_kernel<DIM, TDEP, false>(K);
+}
+
 void launch_finish(const Dev& D, const Consts& K, bool reduce_diag, int last_sweep, int push_blocks, hipStream_t st)
 {
     const bool tdep = opacity_form(K) != OP_FIXED;
-    auto fin = K.inst0.dim == 1
-                   ? (K.n_inst == 1 ? (tdep ? k_finish<true, 1, true> : k_finish<true, 1, false>)
-                                    : (tdep ? k_finish<false, 1, true> : k_finish<false, 1, false>))
-                   : (K.n_inst == 1 ? (tdep ? k_finish<true, 2, true> : k_finish<true, 2, false>)
-                                    : (tdep ? k_finish<false, 2, true> : k_finish<false, 2, false>));
-    fin<<<blocks(K.n_cg, DIAG_THREADS), DIAG_THREADS, 0, st>>>(D, K, K.n_inst == 1 ? last_sweep : -1,
-                                                                   push_blocks);
+    const unsigned nb = blocks(K.n_cg, DIAG_THREADS);
+    auto fin = K.inst0.dim == 1 ? (tdep ? finish_kernel<1, true>(K, nb) : finish_kernel<1, false>(K, nb))
+                                : (tdep ? finish_kernel<2, true>(K, nb) : finish_kernel<2, false>(K, nb));
+    fin<<<nb, DIAG_THREADS, 0, st>>>(D, K, K.n_inst == 1 ? last_sweep : -1, push_blocks);
     if (reduce_diag) k_diag_reduce<<<blocks(K.n_inst, 64), 64, 0, st>>>(D, K);
 }
 

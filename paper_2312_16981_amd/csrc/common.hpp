@@ -89,7 +89,8 @@ struct Consts {
     // beyond the step before's, blocks, threads per block and cells per thread
     int tile_S, tile_H, tile_cap, tile_extra, tile_blocks, tile_threads, tile_cpt;
     int tile_reg;          // the Planck coefficients of the tile sweeps in registers
-    int tile_fold;         // a single instance's stopping test is taken by every block of the next launch
+    int tile_fold;         // sweeps of a round whose stopping test every block of a single instance's next
+                           // launch takes: tile_S, or 0 where a launch of its own does
     int64_t n_cap;
     int64_t pool_cap;
     uint32_t flags;

@@ -1865,7 +1865,7 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     constexpr bool faces_early = SINGLE && !FULL;
     if (faces_early) load_faces();
     __shared__ int dec[TILE_S_MAX + 1];
-    if (tiled && SINGLE && K.tile_fold) tile_gather(D, K, last_sweep, dec);
+    if (tiled && SINGLE) tile_gather(D, K, last_sweep, dec);
     const TilePlan plan = tile_plan(K, __builtin_amdgcn_readfirstlane(prev_sweeps));
     // the commit below advances *D.step while other blocks may still start:
     // both the step's own value and the next one open this launch
@@ -1888,12 +1888,9 @@ void k_finish(Dev D, Consts K, int last_sweep, int push_blocks)
     }
     int ns_single = 0;
     if (tiled && SINGLE) {
-        ns_single = cs0;
-        if (K.tile_fold) {
-            __syncthreads();
-            ns_single = tile_outcome(K, last_sweep, plan, dec);
-            if (blockIdx.x == 0 && threadIdx.x == 0 && ns_single != 0 && dec[TILE_S_MAX] == 0) tile_record(D, 0, ns_single);
-        }
+        __syncthreads();
+        ns_single = tile_outcome(K, last_sweep, plan, dec);
+        if (blockIdx.x == 0 && threadIdx.x == 0 && ns_single != 0 && dec[TILE_S_MAX] == 0) tile_record(D, 0, ns_single);
         if (err0 != 0 || ns_single <= 0) return;
     } else if (!tiled && last_sweep >= 0) {
         __shared__ int sh_ns;

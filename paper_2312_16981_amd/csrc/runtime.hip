@@ -736,7 +736,7 @@ struct ugkwp_ctx {
                     // sweep leaves room for them: a round of 300 x 24 slots 14.7 -> 13.7 us; with
                     // a T-dependent opacity they spill (Larsen's 27.5 -> 29.5, Olson's 19.2 -> 20.3)
                     K.tile_reg = !tile_wit() && !tile_tdep() && bt <= 512 && nb <= 256;
-                    K.tile_fold = nb <= TILE_FOLD;
+                    K.tile_fold = nb <= TILE_FOLD ? S : 0;
                 }
             }
         if (best == 1e300) fail(UGKWP_EHIP, "internal error: no tile shape for %d groups", I.G);

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
     const int lane = threadIdx.x & (WAVE - 1);
     warm_args<sizeof(Dev) + sizeof(Consts)>();
     const uint32_t now = *D.step;
-    if (!FIRST && SINGLE && K.tile_fold) tile_gather(D, K, round - 1, dec);
+    if (!FIRST && SINGLE) tile_gather(D, K, round - 1, dec);
     if (!(K.gate == GATE_OFF || now == K.gate)) return;
     // the block's instance and tile
     Inst I;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(SINGLE ? tile_max_threads(OP != OP_FIXED, REG) : TI
     }
     const TilePlan plan = tile_plan(K, D.prev_ist[inst].conv_sweeps);
     if (!FIRST) {
-        if (SINGLE && K.tile_fold) {
+        if (SINGLE) {
             __syncthreads();
             const int out = tile_outcome(K, round - 1, plan, dec);
             if (out != 0) {

@@ -121,8 +121,8 @@ __device__ inline int tile_test(const Dev& D, const Consts& K, int round, int m,
     return tile_verdict(K, tile_wave_most(tile_most(D, K, round, m, b0 + lane, b1, WAVE)));
 }
 
-// The outcome after a round for the only instance of a context (K.tile_fold: of few
-// tiles), taken by every thread of a block alike, in two parts: tile_gather tests every plane of the round
+// The outcome after a round for the only instance of a context, taken by every
+// thread of a block alike (for many tiles, K.tile_fold = 0, read only), in two parts: tile_gather tests every plane of the round
 // (a wavefront per plane; without waiting for the number of sweeps it took, so that
 // its loads go out with the kernel's first) and reads the recorded state once per
 // block (block 0 of the launch may record it meanwhile); after a barrier tile_outcome
@@ -132,7 +132,7 @@ __device__ inline void tile_gather(const Dev& D, const Consts& K, int round, int
 {
     if (threadIdx.x == 0) sh[TILE_S_MAX] = D.ist[0].conv_sweeps;
     const int lane = threadIdx.x & (WAVE - 1), wid = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
-    for (int m = wid; m < K.tile_S; m += nw) {
+    for (int m = wid; m < K.tile_fold; m += nw) {
         const int v = tile_test(D, K, round, m, 0, K.tile_blocks, lane);
         if (lane == 0) sh[m] = v;
     }
@@ -143,7 +143,7 @@ __device__ inline int tile_outcome(const Consts& K, int round, const TilePlan& p
     int out = sh[TILE_S_MAX];
     if (out != 0) return out;          // recorded by an earlier launch or just now
     const TileRound q = tile_round(K, p, round);
-    for (int m = q.ns - 1; m >= 0; --m) {
+    for (int m = min(q.ns, K.tile_fold) - 1; m >= 0; --m) {
         const int v = sh[m];
         if (v != 0) out = v > 0 ? q.k0 + m + 1 : -1;
     }

@@ -54,8 +54,8 @@ SI_STEP_BYTES_1D, SI_SWEEP_BYTES_1D = 88, 16
 # to those sources makes bench.py report the traffic as unknown.
 PUSH_SOURCES = ("kernels.hip", "device_math.hpp", "device_common.hpp", "si_common.hpp", "common.hpp")
 PUSH_TRAFFIC = {
-    "slab": {"sources": "48372a5027541f9d", "read_per_push": 45.04, "write_per_push": 12.90},
-    "lattice": {"sources": "48372a5027541f9d", "read_per_push": 62.25, "write_per_push": 21.62},
+    "slab": {"sources": "361ce1357ccba265", "read_per_push": 45.04, "write_per_push": 12.90},
+    "lattice": {"sources": "361ce1357ccba265", "read_per_push": 62.25, "write_per_push": 21.62},
 }
 
 

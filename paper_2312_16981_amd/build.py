@@ -15,7 +15,8 @@ LIB = os.path.join(HERE, "libugkwp.so")
 SOURCES = ["kernels.hip", "si_tile.hip", "si_grid.hip", "adjoint.hip", "runtime.hip"]
 # The tile sweeps loop over code full of 64-bit constants (exp, the Planck
 # polynomials); hoisted out of the loop they fill the register file (256 VGPRs and
-# spills instead of 76-135), so they are formed where they are used.
+# spills; as it is 48 to 239 VGPRs, 8 bytes of scratch in two forms), so they are
+# formed where they are used.
 EXTRA = {"si_tile.hip": ["-mllvm", "-disable-machine-licm"]}
 ARCH = os.environ.get("UGKWP_OFFLOAD_ARCH", "gfx950")
 

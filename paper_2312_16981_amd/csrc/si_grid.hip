@@ -9,7 +9,9 @@
 // cells (4 x 4 with 32 lanes a cell): the opacity, phi and A rho^h of the patch and of the
 // cells around it go to LDS, every face of the patch is computed once (2.5 a cell instead
 // of 4) and passed on, and what depends on a cell's temperature alone is evaluated by one
-// thread per cell: some 700 instructions, 71 us a sweep (103 the first).
+// thread per cell: some 700 instructions, 74 us a sweep (116 the first).  (Means over every
+// launch of Olson's problem in its first 80 steps, those past convergence included; over
+// its 225 steps 84 and 140 us, where a sweep that works takes 95 and one past convergence 22.)
 #include "common.hpp"
 #include "device_math.hpp"
 #include "device_common.hpp"

@@ -104,7 +104,9 @@ typedef struct {
     int64_t n_cap;       /* max particles sampled per (cell, group) and step       */
     int64_t pool_capacity; /* particle slots of the context (all instances), at most 2^29;
                               allocated as a run needs them (UGKWP_ENOMEM from the step that
-                              finds no device memory for more: its state stays as it was) */
+                              finds no device memory for more: its state stays as it was,
+                              unless others took the pool's memory while it moved to a larger
+                              one, where set_material has to put a state back)            */
     int si_max_iters;    /* source-iteration limit (Algorithm 2)                   */
     double si_tol;       /* relative max-norm tolerance on rho and on T            */
     uint32_t flags;      /* UGKWP_FLAG_*                                           */
